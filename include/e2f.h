@@ -175,37 +175,31 @@ typedef struct {
   const double* path_w;  /* host [(L+1)^3] w[a][f][o]; NULL => cutoff^-f on triangle-valid paths */
   const void* mix_w;     /* device [(L+1)][C][C] W[o][c_out][c_in] of mix_dtype; NULL => no mixing */
   e2f_dtype mix_dtype;   /* E2F_F32, or E2F_BF16 (mixing inputs rounded to bf16, fp32 accumulate) */
-  float tile_side;       /* side of the receiver tiles whose centres serve as local origins;
-                            0 => cutoff * (8, 8, 8, 6, 4, 3, 2) for L = 0..6 (fp32 precision of
-                            the binomial expansion; the cost does not depend on it) */
+  float tile_side;       /* two-kernel form and dense/global defaults: side of the receiver tiles whose centres
+                            serve as local origins; 0 => cutoff * (8, 8, 8, 6, 4, 3, 2) for L = 0..6 (fp32
+                            precision of the binomial expansion; the cost does not depend on it).  The fused
+                            form expands about each receiver and needs no tiles */
   int32_t y_norm;        /* 0: the layer above.  1: Alg. 1's per-degree attention weights
                             alpha_ij / D_ij^f on the paths of filter degree f, D_ij = |r_i - r_j|
                             (filters Y^(f) of the unit vector; the path f takes 0 at D = 0 for
-                            f > 0).  The factorised forward then aggregates once per f (L+1
-                            times the aggregation work).  The weights 1/D^f no longer damp the
-                            rounding of the binomial expansion (about eps ((|p_i| + |p_j|) /
-                            D_ij)^f per edge), so the tile side is capped at 2.31 times the
-                            shortest nonzero edge (found on the device), keeping that ratio
-                            below 5.  Forward entry points only (the backward returns
-                            E2F_EUNSUPPORTED) */
+                            f > 0).  The fused form evaluates the harmonics of the unit vector and
+                            costs what the plain layer costs.  The two-kernel form aggregates once
+                            per f (L+1 times the work); there the weights 1/D^f no longer damp the
+                            rounding of the binomial expansion, so the tile side is capped at 2.31
+                            times the shortest nonzero edge (found on the device).  Forward entry
+                            points only (the backward returns E2F_EUNSUPPORTED) */
   int32_t form;          /* which form of the aggregation and recouple the forward runs (e2f_form):
-                            E2F_FORM_FUSED: up to L = 4, with heads whose width is a multiple of 16,
-                            the aggregation applies the i-side recouple itself (with y_norm, per
-                            filter degree f with the weights alpha / D^f and the terms b + u = f,
-                            at L = 4 in two passes: degrees 3 and 2, then 4, 1 and 0) (the
-                            j-side coupling and the recouple of Thm. 3.3 composed into one
-                            (L+1)^2 x (L+1)^4 matrix per receiver), so S is never stored;
-                            elsewhere the split form.  E2F_FORM_SPLIT: S is written and recoupled
-                            by a second kernel.  E2F_FORM_AUTO (0): fused wherever it applies with
-                            y_norm (the split form then aggregates once per degree), and at L = 4
-                            where the split form's S (n dimT C floats) would exceed 256 MiB
-                            (beyond the on-die cache its round trip through HBM outweighs the
-                            fused form's extra matrix-core work per receiver), else split.  All forms give the same
-                            result up to rounding order: the fused form multiplies on the bf16
+                            E2F_FORM_AUTO (0) and E2F_FORM_FUSED: one kernel aggregates and couples, with
+                            the local expansion taken about the receiver itself (p_i = 0, so that the
+                            recoupling is the identity); S is never stored.  E2F_FORM_SPLIT: S about tile
+                            centres is written and recoupled by a second kernel.  All forms give the same
+                            result up to rounding (the split form loses the digits that the binomial
+                            expansion cancels).  From L = 4 on the fused form multiplies on the bf16
                             matrix cores with each float operand split into three bf16 parts
                             (x = hi + mid + lo exactly) and the six cross products that reach
                             2^-24 of the product accumulated in float, i.e. float products to
-                            within float rounding */
+                            within float rounding.  The workspace sizes do not depend on which kernel
+                            runs: they hold S, or a composed coupling matrix, per receiver */
 } e2f_conv_params;
 
 /* Workspace of e2f_wigner6j_conv_forward for n atoms and n_edges edges:
@@ -228,14 +222,17 @@ e2f_status e2f_wigner6j_workspace_min(e2f_ctx* ctx, const e2f_conv_params* param
 e2f_status e2f_wigner6j_prepare(e2f_ctx* ctx, const e2f_conv_params* params);
 
 /* Wigner-6j convolution forward (Thm. 3.3, Alg. 1): the layer above computed
- * by node factorisation.  Each receiver i takes as local origin o the centre
- * of its tile (a cube of side tile_side of its graph's bounding box).  With
- * p = r - o, the forward aggregates the uncoupled products of the neighbours,
+ * by node factorisation: with p = r - o for a local origin o, the forward
+ * aggregates the uncoupled products of the neighbours,
  *   G_i = sum_j alpha_ij R(p_j) (x) h_j   (the j-side node product before
  *   its CG coupling, Alg. 1 clebsch_gorden_tp; linear in h_j (x) R(p_j)),
  * couples them into S_i^(a,b,d) = [h (x) R^(b)]^(d) summed over j (the
  * einsum "ijh,jhds->ihds"), and recouples at the receiver,
- *   y_i = sum K(a,b,d,u,o) [R^(u)(p_i) (x) S_i^(a,b,d)]^(o)   (Wigner6jTP),
+ *   y_i = sum K(a,b,d,u,o) [R^(u)(p_i) (x) S_i^(a,b,d)]^(o)   (Wigner6jTP).
+ * The fused form takes o = r_i: only u = 0 is left of the receiver's
+ * harmonics, K is the identity on d = o, and y_i is G_i coupled once.  The
+ * two-kernel form (E2F_FORM_SPLIT) takes o at the centre of the receiver's
+ * tile (a cube of side tile_side of its graph's bounding box).  The forward
  * then mixes.  graph_id: [N] or NULL (must match the graph's).  alpha:
  * [E][H] or NULL (all ones).  out: [N][(L+1)^2][C].  Isolated atoms get zero
  * rows.

@@ -16,6 +16,7 @@
 
 #include "../../include/e2f.h"
 
+#include "agg_layout.h"
 #include "e2f_internal.h"
 #include "e2f_launch.h"
 
@@ -65,18 +66,9 @@ struct e2f_ctx {
     const double* rc_coef = nullptr;
     std::vector<const double*> rcf_coef;  // per filter degree f
     const float* w_f = nullptr;
-    // fused recouple tensor (L <= kFuseMaxL): CSR over the positions of F
-    // in the layout of nkr K rows
-    struct FuseTab {
-      const int* ptr = nullptr;
-      const int* idx = nullptr;
-      const double* coef = nullptr;
-      int nkr = 0;
-    };
-    FuseTab f;
-    // the passes of alpha / D^f (ynorm_passes), their degrees stacked in the
-    // K rows
-    std::vector<FuseTab> fy;
+    // fused aggregation, per column group width 16, 8, 4 (P = 1, 2, 4)
+    const int* agg_index[3] = {};
+    const float* agg_coef[3] = {};
   };
   std::vector<std::vector<CoefSet>> coefs;
   // per L and filter degree f: the recouple schedule restricted to b + u = f
@@ -98,11 +90,6 @@ struct e2f_ctx {
   };
   std::vector<Rec> recs;
   std::vector<hipEvent_t> pool;
-  // a second stream of the context's device and the events that fork work
-  // onto it and join it back (the forward re-lays the features there while
-  // the plan runs on the caller's stream)
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
   // coupling schedules of the aggregation of uncoupled products, per (L, groups)
   struct Couple {
     int k = 0, ntab = 0;
@@ -418,18 +405,10 @@ e2f_status coef_of(e2f_ctx* ctx, int L, const std::vector<double>& w, bool allow
   }
   std::vector<float> wf(w.begin(), w.end());  // o[4 + L]
   push_array(blob, o, wf);
-  const int all_degs[1] = {-1};
-  const FuseTable ft = fuse_table(t, w, all_degs, 1, t.nk);  // o[5 + L] .. o[7 + L] (empty above kFuseMaxL)
-  push_array(blob, o, ft.ptr);
-  push_array(blob, o, ft.idx);
-  push_array(blob, o, ft.coef);
-  YnormPass yps[kYnormMaxPasses];  // o[8 + L + 3q] .. o[10 + L + 3q]
-  const int nyp = ft.coef.empty() ? 0 : ynorm_passes(L, yps);
-  for (int q = 0; q < nyp; ++q) {
-    const FuseTable fp = fuse_table(t, w, yps[q].degs, yps[q].nd, fuse_krows(t.nk, yps[q].degs, yps[q].nd));
-    push_array(blob, o, fp.ptr);
-    push_array(blob, o, fp.idx);
-    push_array(blob, o, fp.coef);
+  for (int P = 1; P <= 4; P *= 2) {  // o[5 + L] .. o[10 + L]
+    const AggTables ag = agg_tables(t, w, P);
+    push_array(blob, o, ag.index);
+    push_array(blob, o, ag.coef);
   }
   if (sets.size() >= kMaxCoefSets) {  // the oldest set may still be read by queued work
     E2F_HIP(hipDeviceSynchronize());
@@ -450,13 +429,9 @@ e2f_status coef_of(e2f_ctx* ctx, int L, const std::vector<double>& w, bool allow
   c.rc_coef = (const double*)((char*)mem + o[2]);
   for (int f = 0; f <= L; ++f) c.rcf_coef.push_back((const double*)((char*)mem + o[3 + f]));
   c.w_f = (const float*)((char*)mem + o[4 + L]);
-  if (!ft.coef.empty()) {
-    auto tab = [&](size_t k, int nkr) {
-      return e2f_ctx::CoefSet::FuseTab{(const int*)((char*)mem + o[k]), (const int*)((char*)mem + o[k + 1]),
-                                       (const double*)((char*)mem + o[k + 2]), nkr};
-    };
-    c.f = tab(5 + L, t.nk);
-    for (int q = 0; q < nyp; ++q) c.fy.push_back(tab(8 + L + 3 * q, fuse_krows(t.nk, yps[q].degs, yps[q].nd)));
+  for (int q = 0; q < 3; ++q) {
+    c.agg_index[q] = (const int*)((char*)mem + o[5 + L + 2 * q]);
+    c.agg_coef[q] = (const float*)((char*)mem + o[6 + L + 2 * q]);
   }
   sets.push_back(std::move(c));
   out = &sets.back();
@@ -588,36 +563,27 @@ constexpr int64_t kMinSlice = 256;
 // fixed part), then S for a slice of receivers.
 struct FwdLayout {
   size_t stats = 0, dmin = 0, grid = 0, tile_of = 0, keys = 0, keys_out = 0, vals = 0, order = 0, sort_tmp = 0;
-  size_t sort_b = 0, Re = 0, Rr = 0, alpha_hm = 0, erows = 0, y = 0, featq = 0, S = 0;
+  size_t sort_b = 0, Re = 0, Rr = 0, alpha_hm = 0, erows = 0, y = 0, S = 0;
   size_t fixed = 0;  // bytes before S
   size_t s_row = 0;  // S bytes per receiver
   size_t total(int64_t slice) const { return fixed + s_row * (size_t)std::max<int64_t>(slice, 0); }
 };
 
-// The split of each head into channel groups of 16 with which the
-// aggregation applies the recouple itself (L <= 4, head width a multiple of
-// 16; with y_norm the filter degrees stacked in the K rows of one or two
-// passes); 0 where the forward writes S.  The automatic choice takes the
-// fused form with y_norm (the two-kernel form then aggregates once per
-// degree: 20,000 atoms, L = 1 .. 4, 1.47 ms fused vs 2.16, 2.04 vs 4.74,
-// 4.79 vs 9.77, 10.6 vs 34.5),
-// and otherwise at L = 4 once S would outgrow the 256 MiB on-die cache
-// (measured: 1,000 atoms with 32 neighbours at L = 4, S 232 MB, 0.31 ms
-// split vs 0.34 fused; 2,000 atoms with 72, S 465 MB, 0.90 vs 0.84; 20,000
-// with 80, 7.17 vs 6.27; at L = 3 the split form was as fast or faster at
-// every size).
-int fused_split(const e2f_conv_params* p, int64_t n) {
-  const int dh = p->channels / p->heads;
-  if (p->form == E2F_FORM_SPLIT || dh % 16 != 0) return 0;
-  if (!outer_fused_supported(p->lmax, p->channels, p->channels / 16, n)) return 0;
-  if (p->form == E2F_FORM_FUSED || p->y_norm) return dh / 16;
+// Whether the workspace is sized by a composed coupling matrix per receiver
+// (fused_row_floats) instead of S.  Callers allocate by these sizes and the
+// slices follow from them, so they stay what they are, although the fused
+// aggregation keeps neither in memory.
+bool fused_sizes(const e2f_conv_params* p, int64_t n) {
+  const int dh = p->channels / p->heads, groups = (nk_of(p->lmax) + 3) / 4;
+  if (p->form == E2F_FORM_SPLIT || dh % 16 != 0 || p->lmax > kFuseMaxL) return false;
+  if (n * groups * p->channels > 0xffffffffll) return false;
+  if (p->form == E2F_FORM_FUSED || p->y_norm) return true;
   const double s_bytes = 4.0 * (double)n * (double)node_tp_dim(p->lmax) * p->channels;
-  return p->lmax == kFuseMaxL && s_bytes > 256.0 * 1024 * 1024 ? dh / 16 : 0;
+  return p->lmax == kFuseMaxL && s_bytes > 256.0 * 1024 * 1024;
 }
 
-// Floats of one receiver's F in the fused form: the largest layout among
-// the forward's passes (the alpha / D^f passes stack degrees in more K
-// rows).
+// Floats of one receiver's composed matrix, the largest layout among the
+// stacked alpha / D^f passes (ynorm_passes).
 int fused_row_floats(const e2f_conv_params* p) {
   const int L = p->lmax, nk = nk_of(L);
   int fl = fuse_stride(nk, nk);
@@ -653,14 +619,12 @@ FwdLayout fwd_layout(const e2f_conv_params* p, int n, int64_t E, bool have_alpha
   f.alpha_hm = take(sizeof(float) * ((size_t)E * H * na + kEdgePad));
   f.erows = take(sizeof(int32_t) * (size_t)E);
   f.y = take(p->mix_w ? sizeof(float) * (size_t)n * nk * C : 0);
-  // the fused aggregation's copy of the features (groups of four components,
-  // each value split into three bfloat16 parts: 6 bytes)
-  f.featq = take(fused_split(p, n) > 0 ? sizeof(float) * (size_t)n * C * 6 * fuse_groups(L) : 0);
+  if (fused_sizes(p, n)) take(sizeof(float) * (size_t)n * C * 6 * ((nk + 3) / 4));
   f.S = off;
   f.fixed = off;
-  // per receiver of a slice: F_i (fused; the largest layout of its passes) or S_i
-  f.s_row = fused_split(p, n) > 0 ? sizeof(float) * (size_t)fused_row_floats(p)
-                                  : al256(sizeof(float) * (size_t)node_tp_dim(L) * C);
+  // per receiver of a slice (fused_sizes)
+  f.s_row = fused_sizes(p, n) ? sizeof(float) * (size_t)fused_row_floats(p)
+                              : al256(sizeof(float) * (size_t)node_tp_dim(L) * C);
   return f;
 }
 
@@ -692,18 +656,18 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
   const int L = p->lmax, C = p->channels, H = p->heads, nk = nk_of(L);
   const e2f_ctx::CoefSet* cs = nullptr;
   if ((rs = coef_of(ctx, L, path_weights(p), allow_upload, cs)) != E2F_OK) return rs;
-  const int fsplit = fused_split(p, n);
-  const int hdiv = fsplit > 0 ? fsplit : head_split(L, C, H);
-  if (hdiv < 1) return fail(E2F_EUNSUPPORTED, "no head split of width %d fits the aggregation", C / H);
-  const int Hv = H * hdiv, dv = C / Hv;
-  const int cgroups = outer_agg_groups(L, C, Hv);
+  // the two-kernel form where the caller asks for it; else the fused one
+  const bool fused = p->form != E2F_FORM_SPLIT;
+  int Hv = 0, dv = 0, hdiv = 0, cgroups = 0;
   const e2f_ctx::Couple* cpl = nullptr;
-  if (fsplit == 0) {
+  if (!fused) {
+    if ((hdiv = head_split(L, C, H)) < 1)
+      return fail(E2F_EUNSUPPORTED, "no head split of width %d fits the aggregation", C / H);
+    Hv = H * hdiv, dv = C / Hv;
+    cgroups = outer_agg_groups(L, C, Hv);
     if (!allow_upload && ctx->couple.find(std::make_pair(L, cgroups)) == ctx->couple.end())
       return fail(E2F_EINVAL, "the coupling schedule is not resident on the context; call e2f_wigner6j_prepare first");
     if ((rs = couple_of(ctx, L, cgroups, cpl)) != E2F_OK) return rs;
-  } else if (!cs->f.ptr || (p->y_norm && cs->fy.empty())) {
-    return fail(E2F_EDEVICE, "the fused recouple table of L = %d is missing", L);
   }
   if (n == 0) return E2F_OK;
   const bool ynorm = p->y_norm != 0;
@@ -732,27 +696,37 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
   float* alpha_hm = (alpha || ynorm) ? (float*)(ws + f.alpha_hm) : nullptr;
   float* y = p->mix_w ? (float*)(ws + f.y) : out;
   float* S = (float*)(ws + f.S);
-  // ---- plan: bounding box, attention weights head-major (per filter degree
-  // under alpha / D^f, with the shortest edge), tile grid, receiver order,
-  // solid harmonics of the edges and receivers
+  const int64_t slice = std::min<int64_t>(n, (int64_t)((workspace_bytes - f.fixed) / f.s_row));
+  int64_t slices = 0;
+  const double side = (p->tile_side > 0.0f ? (double)p->tile_side : kTileCutoffs[L] * (double)p->cutoff) * kGrid;
+  if (fused) {
+    // ---- the receiver order (their own, up to kPlanSmallMax atoms), the
+    // harmonics of the edges, then per slice of receivers the aggregation
+    if (n > kPlanSmallMax) {
+      E2F_TIMED("bbox", launch_plan_bbox(pos, graph_id, n, stats, nullptr, s));
+      E2F_TIMED("tile_plan", launch_plan_grid(stats, nullptr, side, kYnormTileScale, grid, s));
+      E2F_TIMED("tile_plan", launch_plan_order(pos, graph_id, n, grid, tile_of, (uint64_t*)(ws + f.keys),
+                                               (uint64_t*)(ws + f.keys_out), (int32_t*)(ws + f.vals), order,
+                                               ws + f.sort_tmp, f.sort_b, s));
+    }
+    E2F_TIMED("sh", launch_edge_sh(t, pos, row_ptr, col_idx, n, n_edges, ynorm, Re, s));
+    const int dh = agg_group(C, H), which = dh == 16 ? 0 : dh == 8 ? 1 : 2;
+    for (int64_t q0 = 0; q0 < n; q0 += slice, ++slices)
+      E2F_TIMED("aggregate", launch_aggregate_fused(L, Re, row_ptr, col_idx, alpha, n_edges, feat,
+                                                    n > kPlanSmallMax ? order : nullptr, (int)q0,
+                                                    (int)std::min<int64_t>(slice, n - q0), C, H, n,
+                                                    cs->agg_index[which], cs->agg_coef[which], y, s));
+    if (p->mix_w) E2F_TIMED("mix", launch_mix(L, y, p->mix_w, p->mix_dtype == E2F_BF16, n, C, out, s));
+    ctx->last_slices = slices;
+    return E2F_OK;
+  }
+  // ---- two-kernel form.  The plan: bounding box, attention weights
+  // head-major (per filter degree under alpha / D^f, with the shortest edge),
+  // tile grid, receiver order, solid harmonics of the edges and receivers
   int32_t* erows = (int32_t*)(ws + f.erows);
   // (a graph of at most kPlanSmallMax atoms takes the whole plan in one
   // workgroup: box, grid, tiles and the sorted order in one launch)
   const bool small_plan = n <= kPlanSmallMax;
-  // the fused form's copy of the features needs only the features: it is
-  // made on the context's second stream while the plan runs on this one
-  // (the fork waits for the work already queued here; the join comes before
-  // the aggregation)
-  float* featq = (float*)(ws + f.featq);
-  if (fsplit > 0) {
-    E2F_HIP(hipEventRecord(ctx->fork, s));
-    E2F_HIP(hipStreamWaitEvent(ctx->side, ctx->fork, 0));
-    {
-      hipStream_t s = ctx->side;  // (E2F_TIMED records on s)
-      E2F_TIMED("feat_qmajor", launch_feat_qmajor(L, feat, n, C, featq, s));
-    }
-    E2F_HIP(hipEventRecord(ctx->join, ctx->side));
-  }
   if (!small_plan) E2F_TIMED("bbox", launch_plan_bbox(pos, graph_id, n, stats, ynorm ? dmin : nullptr, s));
   else if (ynorm) E2F_TIMED("bbox", launch_plan_init(stats, dmin, s));
   // (the receiver of every edge, and in the same launch the weights
@@ -763,7 +737,6 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
     E2F_TIMED("alpha_hm", launch_plan_dmin(pos, erows, col_idx, n, n_edges, dmin, s));
     E2F_TIMED("alpha_hm", launch_alpha_dnorm(pos, nullptr, col_idx, alpha, n, n_edges, H, L, erows, alpha_hm, s));
   }
-  const double side = (p->tile_side > 0.0f ? (double)p->tile_side : kTileCutoffs[L] * (double)p->cutoff) * kGrid;
   if (small_plan) {
     E2F_TIMED("tile_plan", launch_plan_small(pos, graph_id, n, ynorm ? dmin : nullptr, side, kYnormTileScale, stats,
                                              grid, tile_of, order, s));
@@ -776,45 +749,9 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
   E2F_TIMED("sh", launch_plan_sh(t, pos, erows, col_idx, n, n_edges, tile_of, grid, Rr, Re, s));
   // ---- aggregation and recouple per slice of receivers (S of one slice
   // at a time in the workspace)
-  const int64_t slice = std::min<int64_t>(n, (int64_t)((workspace_bytes - f.fixed) / f.s_row));
-  int64_t slices = 0;
-  if (fsplit > 0) E2F_HIP(hipStreamWaitEvent(s, ctx->join, 0));
   for (int64_t q0 = 0; q0 < n; q0 += slice, ++slices) {
     const int nb = (int)std::min<int64_t>(slice, n - q0);
     const int32_t* ord = order + q0;
-    if (fsplit > 0) {
-      // per pass: F of the slice (from a table whose K rows stack the pass's
-      // filter degrees), then the aggregation with the recouple applied; the
-      // passes after the first add to y.  The plain layer: one pass.  With
-      // y_norm the weights alpha / D^f and the terms b + u = f of each degree
-      // f, in (f+1)^2 K rows: the passes of ynorm_passes (one below L = 4;
-      // at L = 4 degrees 3 and 2, then 4, 1 and 0).
-      int npass = 0;
-      const int all_degs[1] = {-1};
-      auto pass = [&](const e2f_ctx::CoefSet::FuseTab& tab, const int* degs, int nd) -> e2f_status {
-        FusedSegs sg{};
-        sg.n = nd;
-        for (int q = 0, r = 0; q < nd; ++q) {
-          sg.alpha_hm[q] = degs[q] < 0 ? alpha_hm : alpha_hm + (size_t)degs[q] * H * n_edges;
-          sg.start[q] = r;
-          r += degs[q] < 0 ? nk : (degs[q] + 1) * (degs[q] + 1);
-        }
-        E2F_TIMED("fuse_build", launch_fuse_build(L, tab.nkr, tab.ptr, tab.idx, tab.coef, Rr, ord, nb, S, s));
-        E2F_TIMED("aggregate", launch_outer_fused(L, tab.nkr, Re, row_ptr, col_idx, sg, n_edges, featq, ord, S, nb, C,
-                                                  Hv, hdiv, n, npass++ > 0, y, s));
-        return E2F_OK;
-      };
-      if (!ynorm) {
-        if ((rs = pass(cs->f, all_degs, 1)) != E2F_OK) return rs;
-      } else {
-        YnormPass yps[kYnormMaxPasses];
-        const int nyp = ynorm_passes(L, yps);
-        if (nyp != (int)cs->fy.size()) return fail(E2F_EDEVICE, "the alpha / D^f tables of L = %d are missing", L);
-        for (int q = 0; q < nyp; ++q)
-          if ((rs = pass(cs->fy[q], yps[q].degs, yps[q].nd)) != E2F_OK) return rs;
-      }
-      continue;
-    }
     if (!ynorm) {
       E2F_TIMED("aggregate", launch_outer_agg(t, Re, row_ptr, col_idx, alpha_hm, n_edges, feat, ord, cpl->meta,
                                               cpl->coef, cpl->pmeta, cpl->tab, cpl->ntab, cpl->k, cgroups, nb, C, Hv,
@@ -880,10 +817,6 @@ e2f_status e2f_create(int lmax_max, int device, e2f_ctx** out) {
         st = fail(E2F_EDEVICE, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
       }
     }
-    if (st == E2F_OK && (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess ||
-                         hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming) != hipSuccess ||
-                         hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming) != hipSuccess))
-      st = fail(E2F_EDEVICE, "side stream or its events: %s", hipGetErrorString(hipGetLastError()));
     if (st != E2F_OK) {
       e2f_destroy(ctx);
       return st;
@@ -921,9 +854,6 @@ void e2f_destroy(e2f_ctx* ctx) {
       ctx->pool.push_back(r.stop);
     }
     for (hipEvent_t e : ctx->pool) (void)hipEventDestroy(e);
-    if (ctx->fork) (void)hipEventDestroy(ctx->fork);
-    if (ctx->join) (void)hipEventDestroy(ctx->join);
-    if (ctx->side) (void)hipStreamDestroy(ctx->side);
     if (ctx->stats) (void)hipFree(ctx->stats);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->pinned_plan) (void)hipHostFree(ctx->pinned_plan);
@@ -1128,16 +1058,9 @@ e2f_status e2f_wigner6j_prepare(e2f_ctx* ctx, const e2f_conv_params* p) {
   DeviceGuard g(ctx->device);
   const e2f_ctx::CoefSet* cs = nullptr;
   if (e2f_status rs = coef_of(ctx, p->lmax, path_weights(p), true, cs); rs != E2F_OK) return rs;
-  // the coupling schedule of the two-kernel form as well (the forward takes
-  // it for atom counts whose re-laid features exceed 32-bit offsets); the
-  // fused table is part of the coefficient set
+  // the coupling schedule of the two-kernel form as well, for a later call with it
   const int hdiv = head_split(p->lmax, p->channels, p->heads);
-  if (hdiv < 1) {
-    e2f_conv_params pf = *p;
-    pf.form = E2F_FORM_FUSED;
-    if (fused_split(&pf, 1) > 0) return E2F_OK;
-    return fail(E2F_EUNSUPPORTED, "no head split of width %d fits the aggregation", p->channels / p->heads);
-  }
+  if (hdiv < 1) return E2F_OK;
   const e2f_ctx::Couple* cpl = nullptr;
   return couple_of(ctx, p->lmax, outer_agg_groups(p->lmax, p->channels, p->heads * hdiv), cpl);
 }

@@ -790,474 +790,6 @@ __global__ __launch_bounds__(LB) void k_outer_agg(DevTables t, const float* __re
   }  // receivers of the workgroup
 }
 
-// ------------------------------------------------------------ fused recouple
-// Up to L = 4 with heads of 16 channels the recouple is applied where G is
-// made: per receiver the matrix F_i = Q_i CG (the j-side coupling composed
-// with the i-side recouple, built once per receiver by k_fuse_build) takes
-// the aggregated uncoupled products straight to the output,
-//     y_i[k][h*16 + t] = sum_{be, q} F_i[k][be, q] G_i^h[be][q][t],
-// so neither the coupled S_i nor a second kernel's read of it exists.
-
-// F_i = sum_x R_x(p_i) K_x in float64, rounded once to float: a workgroup
-// builds kFuseRecv receivers' rows (the receivers order[r0 ..] of the slice,
-// row r0 + b), each thread a set of positions; position p sums its entries
-// fidx/fcoef[fptr[p] .. fptr[p+1]).
-constexpr int kFuseRecv = 16;
-__global__ __launch_bounds__(256) void k_fuse_build(const int* __restrict__ fptr, const int* __restrict__ fidx,
-                                                    const double* __restrict__ fcoef, int np, int nk,
-                                                    const double* __restrict__ R, const int32_t* __restrict__ order,
-                                                    int nb, float* __restrict__ F) {
-  __shared__ double Rl[kFuseRecv][(kFuseMaxL + 1) * (kFuseMaxL + 1)];
-  const int r0 = blockIdx.x * kFuseRecv;
-  const int nr = min(kFuseRecv, nb - r0);
-  for (int q = threadIdx.x; q < kFuseRecv * nk; q += blockDim.x) {
-    const int b = q / nk, x = q % nk;
-    Rl[b][x] = b < nr ? R[(size_t)order[r0 + b] * nk + x] : 0.0;
-  }
-  __syncthreads();
-  for (int p = threadIdx.x; p < np; p += blockDim.x) {
-    double acc[kFuseRecv];
-#pragma unroll
-    for (int b = 0; b < kFuseRecv; ++b) acc[b] = 0.0;
-    const int e1 = fptr[p + 1];
-    for (int e = fptr[p]; e < e1; ++e) {
-      const double c = fcoef[e];
-      const int x = fidx[e];
-#pragma unroll
-      for (int b = 0; b < kFuseRecv; ++b) acc[b] += c * Rl[b][x];
-    }
-#pragma unroll
-    for (int b = 0; b < kFuseRecv; ++b)
-      if (b < nr) F[(size_t)(r0 + b) * np + p] = (float)acc[b];
-  }
-}
-
-
-// x = hi + mid + lo exactly, each part a bfloat16 rounded to nearest even
-// (8 + 8 + 8 significant bits hold a float's 24), returned as bit patterns.
-// The products of the split operands that reach 2^-24 relative (hi hi,
-// hi mid, mid hi, hi lo, mid mid, lo hi) are exact in float and summed in
-// float by the matrix cores, so six bf16 products stand in for one float
-// product within float rounding.
-__device__ __forceinline__ void split_bf16x3(float x, unsigned& hi, unsigned& mid, unsigned& lo) {
-  const __bf16 h = (__bf16)x;
-  const float r = x - (float)h;
-  const __bf16 m = (__bf16)r;
-  const __bf16 l = (__bf16)(r - (float)m);
-  hi = __builtin_bit_cast(unsigned short, h);
-  mid = __builtin_bit_cast(unsigned short, m);
-  lo = __builtin_bit_cast(unsigned short, l);
-}
-
-// The fused aggregation's groups of components, one product wave each: NG =
-// ceil(NK / 4) groups of at most four, as even as possible (NK = 25: 4, 4, 4,
-// 4, 3, 3, 3), so that two product waves sharing a SIMD hold at most 7 of the
-// 25 component tiles; group g holds the components fuse_g0(NK, g) ..
-// fuse_g0(NK, g) + fuse_gn(NK, g) - 1.
-__host__ __device__ constexpr int fuse_gn(int nk, int g) {
-  return nk / ((nk + 3) / 4) + (g < nk % ((nk + 3) / 4) ? 1 : 0);
-}
-__host__ __device__ constexpr int fuse_g0(int nk, int g) {
-  return g * (nk / ((nk + 3) / 4)) + (g < nk % ((nk + 3) / 4) ? g : nk % ((nk + 3) / 4));
-}
-static_assert(fuse_g0(25, 6) + fuse_gn(25, 6) == 25 && fuse_gn(25, 3) == 4 && fuse_gn(25, 4) == 3,
-              "groups of 25 components: 4, 4, 4, 4, 3, 3, 3");
-static_assert(fuse_g0(16, 3) == 12 && fuse_gn(16, 3) == 4 && fuse_g0(9, 2) == 6 && fuse_gn(1, 0) == 1,
-              "groups of 16, 9 and 1 components");
-
-// The features in the order of the fused aggregation's B operand, each value
-// split into three bfloat16 parts: per node and head of 16 channels, the
-// groups of components above (slot i of group g: component fuse_g0(NK, g) +
-// i, zero from fuse_gn(NK, g) on), each group [t][i] (t the channel in the
-// head): a uint4 of the four components' hi | mid << 16
-// and, in the second array (same index), a uint2 of their lo parts
-// (components 0, 1 in the first word, low half first).  Lane t of a wave
-// reads its group's four components with one 16-byte and one 8-byte load; a
-// group of 16 lanes reads 256 + 128 contiguous bytes.
-__global__ void k_feat_qmajor3(const float* __restrict__ feat, int n, int nk, int C, int ng,
-                               uint4* __restrict__ hm, uint2* __restrict__ lo) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (node, head, group, t)
-  const int H = C / 16;
-  if (q >= (int64_t)n * H * ng * 16) return;
-  const int t = (int)(q % 16);
-  const int64_t r = q / 16;
-  const int g = (int)(r % ng), h = (int)(r / ng % H);
-  const int64_t j = r / ((int64_t)ng * H);
-  const float* src = feat + (size_t)j * nk * C + h * 16 + t;
-  unsigned a[4], b[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    unsigned x, y, z;
-    split_bf16x3(i < fuse_gn(nk, g) ? src[(size_t)(fuse_g0(nk, g) + i) * C] : 0.0f, x, y, z);
-    a[i] = x | y << 16;
-    b[i] = z;
-  }
-  hm[q] = make_uint4(a[0], a[1], a[2], a[3]);
-  lo[q] = make_uint2(b[0] | b[1] << 16, b[2] | b[3] << 16);
-}
-
-// The aggregation with the recouple applied in registers.  Work split as in
-// k_outer_agg (a workgroup: rpw consecutive receivers of one head h of 16
-// channels), but tile w of wave v holds the 16 channels t = l16 of one
-// component q = fuse_g0(NK, v) + w, so that after the products the accumulator element
-// s of a lane (l16, k4), G[16 mt + 4 k4 + s][q][l16], is exactly the B
-// operand of K step s of F_i G when the K index of that step is ordered as
-// be = 16 mt + 4 k4 + s; F_i is stored in the matching order.  Each wave sums
-// its components' share of y (rows 16 rt + 4 k4 + v, channel l16); the
-// shares meet in LDS and one pass stores the head's 16 channels of y_i.
-//
-// The workgroup walks its receivers' chunks of up to kOuterEdges edges (an
-// isolated receiver is one empty chunk).  Waves 0 .. NG-1 multiply (wave v:
-// the fuse_gn(NK, v) components of group v); the last wave stages: while the others multiply
-// chunk k from one LDS buffer it loads chunk k+1 (alpha, R of the edges, the
-// senders) and writes alpha R and the senders' offsets into the other, so
-// the products never wait for a chunk's loads.  One barrier per chunk (two
-// more after a receiver's last chunk, for the shares of y, which reuse the
-// finished buffer).
-// The K rows of G and F (KR of them; the plain layer: KR = NK, row be the
-// component be of R(p_j)) may stack several filter degrees of alpha / D^f:
-// segment s of the K rows (from sg.start[s]) holds the components be =
-// row - start of R(p_j) weighted by alpha_hm[s], so that one gather of the
-// senders serves several degrees.
-// register pipeline of the fused products: kFuseStages - 1 steps ahead
-constexpr int kFuseStages = 3;
-constexpr int kFuseRows = kOuterEdges + 4 * (2 * kFuseStages - 2);  // staging rows with the prefetch padding
-
-template <int L, int LB, int KR>
-__global__ __launch_bounds__(LB) void k_outer_fused(const float* __restrict__ Re, const int64_t* __restrict__ row_ptr,
-                                                    const int32_t* __restrict__ col, FusedSegs sg, int64_t n_edges,
-                                                    const uint4* __restrict__ fhm, const uint2* __restrict__ flo,
-                                                    const int32_t* __restrict__ order, const float* __restrict__ F,
-                                                    int n, int nrx, int rpw, int C, int H, int hdiv, int n_nodes,
-                                                    bool accumulate, float* __restrict__ y) {
-  constexpr int NK = (L + 1) * (L + 1), MT = (NK + 15) / 16, MP = 16 * MT;  // rows k of y and F
-  constexpr int MK = (KR + 15) / 16, MPK = 16 * MK;                         // K rows of G and F
-  constexpr int EC = kOuterEdges;
-  // staging row stride in words: two words per component (a 64-bit read per
-  // lane), odd rows rotated by 16 components where 2 MP is a multiple of 64,
-  // so rows 4 st + k4 of one step alternate between the two halves of the
-  // banks
-  constexpr int AS = 2 * MPK;
-  constexpr int ROT = (2 * MPK) % 64 == 0 ? 16 : 0;
-  constexpr int QB = fuse_qblock(NK, KR), FS = fuse_stride(NK, KR);
-  constexpr int NG = (NK + 3) / 4;  // groups of at most four components (fuse_gn): one product wave each
-  // rows EC .. SR-1 of a buffer are padding (zero weights, sender offset 0):
-  // the last iteration of the step loop starts at a step st <= ns - 1 and
-  // loads up to step st + 2 (kFuseStages - 1) ahead, i.e. rows up to
-  // 4 (ns - 1 + 2 (kFuseStages - 1)) + 3 <= EC + 8 kFuseStages - 9
-  constexpr int SR = kFuseRows, SB = SR * AS;
-  static_assert(SR - EC >= 8 * kFuseStages - 8, "padding rows must cover the prefetch past a full chunk");
-  static_assert(NG * MP * 16 <= SB, "the shares of y must fit one staging buffer");
-  constexpr int RPI = 64 / MPK;           // rows the staging wave covers per pass (lane: K row lane % MPK)
-  constexpr int ITER = EC / RPI;          // passes over a full chunk
-  extern __shared__ float sm[];
-  float* Alb = sm;                        // [2][SR][AS] alpha R of the chunk's edges, split (zero past its rows)
-  int* job = (int*)(sm + 2 * SB);         // [2][SR] the senders' offsets in the re-laid features
-  float* sa = sm + 2 * SB + 2 * SR;       // [sg.n][EC] the staging wave's copy of the chunk's weights
-  const int bid = blockIdx.x, xcd = bid % 8, local = bid / 8;
-  const int h = local % H, rfirst = xcd * nrx + (local / H) * rpw;
-  const int rlast = min(min(rfirst + rpw, (xcd + 1) * nrx), n);  // uniform over the workgroup
-  if (rfirst >= rlast) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int l16 = lane & 15, k4 = lane >> 4;
-  const bool stager = wave == NG;  // uniform over the wave
-  // a product wave's live tiles (the components q0 .. q0 + nl - 1 of its
-  // group) and the lane's entry of a sender: its wave's group, channel t = l16
-  const int nl = stager ? 0 : __builtin_amdgcn_readfirstlane(fuse_gn(NK, wave));
-  const int q0 = stager ? 0 : fuse_g0(NK, wave);
-  const unsigned fstride = (unsigned)(H * NG * 16);
-  const unsigned foff = (unsigned)((h * NG + min(wave, NG - 1)) * 16 + l16);
-  for (int q = threadIdx.x; q < 2 * (SR - EC) * AS; q += blockDim.x) {
-    const int b = q / ((SR - EC) * AS);
-    Alb[b * SB + EC * AS + q % ((SR - EC) * AS)] = 0.0f;
-  }
-  for (int q = threadIdx.x; q < 2 * (SR - EC); q += blockDim.x) job[(q / (SR - EC)) * SR + EC + q % (SR - EC)] = 0;
-  // edge range of receiver row r (clamped to [0, E]: a malformed graph
-  // cannot move a read outside the caller's buffers)
-  auto bounds = [&](int r, int64_t& e0, int64_t& e1) {
-    const int i = order[r];
-    const int64_t rb0 = row_ptr[i], rb1 = row_ptr[i + 1];
-    e0 = rb0 < 0 ? 0 : (rb0 > n_edges ? n_edges : rb0);
-    e1 = rb1 < e0 ? e0 : (rb1 > n_edges ? n_edges : rb1);
-  };
-  // the staging wave: chunk [c0, c0 + ne) into buffer b.  Every sender
-  // offset below EC is written (0 past ne); the weight rows read by the
-  // chunk's steps (4 ceil(ne / 4)) are written whole, zero past ne and in
-  // the columns NK .. MP-1.  Lane: component be = lane % MP of rows
-  // rs + RPI it; the R values load in batches of BT rows per lane, the next
-  // batch in flight while the current one is stored (clamped addresses, so
-  // the loads are unconditional; an empty chunk loads none).
-  auto stage = [&](int64_t c0, int ne, int b) {
-    float* Al = Alb + b * SB;
-    int* jo = job + b * SR;
-    if (ne == 0) {  // an isolated receiver: zero weights, sender offsets 0
-#pragma unroll
-      for (int u = 0; u < EC / 64; ++u) {
-#pragma unroll
-        for (int sgm = 0; sgm < kFusedSegs; ++sgm)
-          if (sgm < sg.n) sa[sgm * EC + lane + 64 * u] = 0.0f;
-        jo[lane + 64 * u] = 0;
-      }
-      return;
-    }
-    // unconditional loads (the compiler can then keep every batch in flight):
-    // the weights and harmonics of edges c0 .. c0 + EC - 1 lie inside their
-    // arrays, which carry kEdgePad rows of padding past the last edge (a
-    // missing weight array reads the harmonics instead); the caller's senders
-    // are read at a clamped index.  Rows past ne are masked by selects.
-    float av[kFusedSegs][EC / 64];
-    int jv[EC / 64];
-#pragma unroll
-    for (int u = 0; u < EC / 64; ++u) {
-      const int nb = lane + 64 * u;
-#pragma unroll
-      for (int sgm = 0; sgm < kFusedSegs; ++sgm) {
-        if (sgm >= sg.n) break;
-        const float* ah = sg.alpha_hm[sgm] ? sg.alpha_hm[sgm] + (int64_t)(h / hdiv) * n_edges : nullptr;
-        const float a = (ah ? ah : Re)[c0 + nb];
-        av[sgm][u] = nb < ne ? (ah ? a : 1.0f) : 0.0f;
-      }
-      const int j = col[c0 + min(nb, ne - 1)];
-      jv[u] = nb < ne && (unsigned)j < (unsigned)n_nodes ? j : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < EC / 64; ++u) {
-#pragma unroll
-      for (int sgm = 0; sgm < kFusedSegs; ++sgm)
-        if (sgm < sg.n) sa[sgm * EC + lane + 64 * u] = av[sgm][u];
-      jo[lane + 64 * u] = (int)((unsigned)jv[u] * fstride);
-    }
-    __builtin_amdgcn_wave_barrier();
-    const int nrow = 4 * ((ne + 3) / 4);
-    // the lane's position p = lane % MPK of the row holds K row kr (the K
-    // order of F: within tile p / 16, row 16 (p / 16) + j at 4 (j / ks) +
-    // j % ks), or nothing (zeros) where no row takes it; K row kr of segment
-    // sgm is the harmonics' component kr - sg.start[sgm] with that segment's
-    // weights
-    const int p = lane % MPK, rs = lane / MPK;
-    const int pt = p / 16, pk4 = (p % 16) / 4, ps = p % 4, ks = fuse_ks(KR, pt);
-    const int pj = pk4 * ks + ps;
-    const bool bok = pt * 16 < KR && ps < ks && pj < fuse_rows(KR, pt);
-    const int kr = 16 * pt + pj;
-    int seg = 0, s0 = 0;
-#pragma unroll
-    for (int sgm = 1; sgm < kFusedSegs; ++sgm)
-      if (sgm < sg.n && kr >= sg.start[sgm]) {
-        seg = sgm;
-        s0 = sg.start[sgm];
-      }
-    const int be = bok ? kr - s0 : 0;  // the harmonics' component (< NK: checked by the launcher)
-    const float* wsrc = sa + seg * EC;
-    // the lane's rows rs + RPI (BT bt + k): one base per batch, immediate
-    // offsets within it
-    const float* src = Re + (size_t)(c0 + rs) * NK + be;
-    constexpr int BT = 16, NBT = ITER / BT;
-    static_assert(ITER % BT == 0, "batches must cover a chunk");
-    static_assert(kEdgePad >= EC, "the per-edge arrays must be padded by a chunk");
-    float cur[BT], nxt[BT];
-    auto load = [&](int bt, float* d) {
-      const float* sb = src + (size_t)bt * BT * RPI * NK;
-#pragma unroll
-      for (int k = 0; k < BT; ++k) d[k] = sb[k * RPI * NK];
-    };
-    load(0, cur);
-#pragma unroll 1
-    for (int bt = 0; bt < NBT && bt * BT * RPI < nrow; ++bt) {
-      const bool more_rows = bt + 1 < NBT && (bt + 1) * BT * RPI < nrow;
-      if (more_rows) load(bt + 1, nxt);
-#pragma unroll
-      for (int k = 0; k < BT; ++k) {
-        const int nb = (bt * BT + k) * RPI + rs;
-        const float w = cur[k] * wsrc[nb];
-        const float v = bok && nb < ne ? w : 0.0f;
-        if (nb < nrow) {
-          // A of the split products: words hi | mid << 16 and hi | lo << 16
-          unsigned hi, mid, lo;
-          split_bf16x3(v, hi, mid, lo);
-          ((uint2*)(Al + nb * AS))[(p + (nb & 1) * ROT) % MPK] = make_uint2(hi | mid << 16, hi | lo << 16);
-        }
-      }
-      if (more_rows) {
-#pragma unroll
-        for (int k = 0; k < BT; ++k) cur[k] = nxt[k];
-      }
-    }
-  };
-  int r = rfirst;
-  int64_t e0, e1;
-  bounds(r, e0, e1);
-  int64_t c0 = e0;
-  if (stager) stage(c0, (int)min((int64_t)EC, e1 - c0), 0);
-  __syncthreads();
-  v4f acc[MK][4];
-#pragma unroll
-  for (int mt = 0; mt < MK; ++mt)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) acc[mt][w] = (v4f){0.f, 0.f, 0.f, 0.f};
-  for (int kb = 0;; kb ^= 1) {
-    const int ne = (int)min((int64_t)EC, e1 - c0);  // 0 for an isolated receiver
-    const bool last = c0 + EC >= e1;                 // the receiver's last chunk (uniform)
-    int rn = r;
-    int64_t c0n = c0 + EC, e0n = e0, e1n = e1;
-    if (last) {
-      rn = r + 1;
-      if (rn < rlast) {
-        bounds(rn, e0n, e1n);
-        c0n = e0n;
-      }
-    }
-    const bool more = rn < rlast;
-    if (stager) {
-      if (more) stage(c0n, (int)min((int64_t)EC, e1n - c0n), kb ^ 1);
-    } else {
-      const float* Al = Alb + kb * SB;
-      const int* jo = job + kb * SR;
-      const int ns = (ne + 3) / 4;
-      // pipeline of the products: the operands of steps st+1, st+2 are
-      // loaded while the MFMAs of step st run; steps past ns read rows of
-      // zeros or stale weights with valid senders and are never multiplied.
-      // NL (the wave's live tiles) is a constant of each copy of the loop.
-      // The products are split: K of one v_mfma_f32_16x16x32_bf16 is 4
-      // edges (k4) x 8 slots, six of them the cross products of the parts,
-      //   A = {hi|mid, hi|lo, hi|mid, 0}, B = {hi|mid, mid|hi, lo|hi, 0}
-      // (A from the staging words, B from the lane's uint4 / uint2 of the
-      // sender), so a step is two loads, MT 64-bit LDS reads, two ALU
-      // operations per tile and NL MT MFMAs of half the fp32 cost.
-      auto products = [&](auto nlc) {
-        constexpr int NL = decltype(nlc)::value;
-        uint2 aq[kFuseStages][MK];
-        uint4 bh[kFuseStages];
-        uint2 bl[kFuseStages];
-        auto loadb = [&](int st, uint2* a, uint4& h4, uint2& l2) {
-          const int nb = min(4 * st + k4, SR - 1);  // < SR without the clamp (see SR)
-          const unsigned o = (unsigned)jo[nb] + foff;
-          h4 = fhm[o];
-          l2 = flo[o];
-          const uint2* row = (const uint2*)(Al + nb * AS);
-#pragma unroll
-          for (int mt = 0; mt < MK; ++mt) a[mt] = row[(mt * 16 + l16 + (nb & 1) * ROT) % MPK];
-        };
-        auto mma = [&](const uint2* a, const uint4& h4, const uint2& l2) {
-          const unsigned hw[4] = {h4.x, h4.y, h4.z, h4.w};
-          const unsigned lw[4] = {l2.x & 0xffffu, l2.x >> 16, l2.y & 0xffffu, l2.y >> 16};
-#pragma unroll
-          for (int w = 0; w < NL; ++w) {
-            const v8bf bv =
-                __builtin_bit_cast(v8bf, (v4u){hw[w], (hw[w] >> 16) | (hw[w] << 16), lw[w] | (hw[w] << 16), 0u});
-#pragma unroll
-            for (int mt = 0; mt < MK; ++mt) {
-              const v8bf av = __builtin_bit_cast(v8bf, (v4u){a[mt].x, a[mt].y, a[mt].x, 0u});
-              acc[mt][w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[mt][w], 0, 0, 0);
-            }
-          }
-        };
-#pragma unroll
-        for (int u = 0; u + 1 < kFuseStages; ++u) loadb(u, aq[u], bh[u], bl[u]);
-        for (int st = 0; st < ns; st += kFuseStages) {
-#pragma unroll
-          for (int u = 0; u < kFuseStages; ++u) {
-            const int w = (u + kFuseStages - 1) % kFuseStages;
-            loadb(st + u + kFuseStages - 1, aq[w], bh[w], bl[w]);
-            __builtin_amdgcn_sched_barrier(0);
-            if (u == 0 || st + u < ns) mma(aq[u], bh[u], bl[u]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      };
-      if (nl == 4) products(std::integral_constant<int, 4>{});
-      else if (nl == 3) products(std::integral_constant<int, 3>{});
-      else if (nl == 2) products(std::integral_constant<int, 2>{});
-      else if (nl == 1) products(std::integral_constant<int, 1>{});
-    }
-    if (last) {
-      // this wave's share of y_i: A = F_i (rows k, K = the K rows in the step
-      // order above, zero past KR), B = the accumulators.  The F loads are
-      // unconditional (lanes past a sub-block's rows or K values read a
-      // valid element and take zero), so the wait counts stay exact; the
-      // next component's values load while this one's MFMAs run.
-      const float* Fr = F + (size_t)r * FS;
-      v4f ya[MT];
-#pragma unroll
-      for (int rt = 0; rt < MT; ++rt) ya[rt] = (v4f){0.f, 0.f, 0.f, 0.f};
-      auto recouple = [&](auto nlc) {
-        constexpr int NL = decltype(nlc)::value;
-        float4 fv[2][MT][MK];
-        auto loadf = [&](int w, float4 (*f)[MK]) {
-          const int q = q0 + w;  // < NK for w < NL
-#pragma unroll
-          for (int rt = 0; rt < MT; ++rt)
-#pragma unroll
-            for (int mt = 0; mt < MK; ++mt) {
-              // (a 0/1 factor rather than a select: a value every lane uses
-              // keeps the compiler from predicating the load)
-              const bool ok = l16 < fuse_rows(NK, rt) && k4 < fuse_kc(KR, mt);
-              const float z = ok ? 1.0f : 0.0f;
-              const float4 v = *(const float4*)(Fr + q * QB + fuse_blk(NK, KR, rt, mt) +
-                                                (ok ? (k4 * fuse_rows(NK, rt) + l16) * 4 : 0));
-              f[rt][mt] = make_float4(v.x * z, v.y * z, v.z * z, v.w * z);
-            }
-        };
-        // (scheduling barriers keep the next component's loads ahead of
-        // this one's MFMAs; without them the loads sink to their first use
-        // and every F block waits out a full L2 round trip)
-        loadf(0, fv[0]);
-#pragma unroll
-        for (int w = 0; w < NL; ++w) {
-          if (w + 1 < NL) loadf(w + 1, fv[(w + 1) & 1]);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int mt = 0; mt < MK; ++mt)
-#pragma unroll
-            for (int rt = 0; rt < MT; ++rt) {
-              // K steps s >= fuse_ks(KR, mt) hold no K row (zero F and G):
-              // skipped (mt is a constant of the unrolled loop)
-              const float4 f = fv[w & 1][rt][mt];
-              ya[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.x, acc[mt][w][0], ya[rt], 0, 0, 0);
-              if (fuse_ks(KR, mt) > 1)
-                ya[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.y, acc[mt][w][1], ya[rt], 0, 0, 0);
-              if (fuse_ks(KR, mt) > 2)
-                ya[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.z, acc[mt][w][2], ya[rt], 0, 0, 0);
-              if (fuse_ks(KR, mt) > 3)
-                ya[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.w, acc[mt][w][3], ya[rt], 0, 0, 0);
-            }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      };
-      if (nl == 4) recouple(std::integral_constant<int, 4>{});
-      else if (nl == 3) recouple(std::integral_constant<int, 3>{});
-      else if (nl == 2) recouple(std::integral_constant<int, 2>{});
-      else if (nl == 1) recouple(std::integral_constant<int, 1>{});
-      __syncthreads();  // every product wave is done with buffer kb: it takes the shares of y
-      float* yp = Alb + kb * SB;  // [NG][MP][16]
-      if (!stager) {
-#pragma unroll
-        for (int rt = 0; rt < MT; ++rt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) yp[(wave * MP + 16 * rt + 4 * k4 + v) * 16 + l16] = ya[rt][v];
-      }
-      __syncthreads();
-      const int i = order[r];
-      for (int idx = threadIdx.x; idx < NK * 16; idx += blockDim.x) {
-        const int row = idx >> 4, t = idx & 15;
-        float sum = 0.0f;
-        for (int wv = 0; wv < NG; ++wv) sum += yp[(wv * MP + row) * 16 + t];
-        float* yo = y + ((size_t)i * NK + row) * C + h * 16 + t;
-        *yo = accumulate ? *yo + sum : sum;  // (accumulate: the sum over the filter degrees of alpha / D^f)
-      }
-#pragma unroll
-      for (int mt = 0; mt < MK; ++mt)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) acc[mt][w] = (v4f){0.f, 0.f, 0.f, 0.f};
-    }
-    if (!more) break;
-    __syncthreads();  // buffer kb ^ 1 is staged; buffer kb (and the shares of y) is free
-    r = rn;
-    c0 = c0n;
-    e0 = e0n;
-    e1 = e1n;
-  }
-}
-
 // ------------------------------------------------------------ i-side recouple
 // y_i[k][c] = sum_r Q_i[k][r] S_i[r][c] over the T rows r, with the per-node
 // matrix Q_i[(o,m)][(a,b,d,de)] = sum_u K(a,b,d,u,o) sum_ga C^{o m}_{u ga, d de}
@@ -2265,97 +1797,6 @@ hipError_t launch_outer_agg(const DevTables& t, const float* Re, const int64_t* 
 #undef E2F_CASE
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-int fuse_groups(int L) { return ((L + 1) * (L + 1) + 3) / 4; }
-
-bool outer_fused_supported(int L, int C, int H, int64_t n_nodes) {
-  return L >= 0 && L <= kFuseMaxL && H >= 1 && C == 16 * H &&
-         (uint64_t)n_nodes * H * fuse_groups(L) * 16 <= 0xffffffffull;
-}
-
-hipError_t launch_fuse_build(int L, int nkr, const int* fptr, const int* fidx, const double* fcoef,
-                             const double* R, const int32_t* order, int n, float* F, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  if (L < 0 || L > kFuseMaxL || nkr < 1) return hipErrorInvalidValue;
-  const int nk = (L + 1) * (L + 1);
-  k_fuse_build<<<(n + kFuseRecv - 1) / kFuseRecv, 256, 0, s>>>(fptr, fidx, fcoef, fuse_stride(nk, nkr), nk, R, order,
-                                                                 n, F);
-  return hipGetLastError();
-}
-
-hipError_t launch_feat_qmajor(int L, const float* feat, int n, int C, float* featq, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  if (C % 16) return hipErrorInvalidValue;
-  const int64_t total = (int64_t)n * (C / 16) * fuse_groups(L) * 16;
-  if ((total + 255) / 256 > 0x7fffffff) return hipErrorInvalidValue;
-  k_feat_qmajor3<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(feat, n, (L + 1) * (L + 1), C, fuse_groups(L),
-                                                                  (uint4*)featq, (uint2*)featq + 2 * total);
-  return hipGetLastError();
-}
-
-// (the stacked alpha / D^f passes: 5, 14 and 30 K rows at L = 1, 2, 3, and
-// 30 at L = 4)
-bool fused_krows_supported(int L, int nkr) {
-  const int nk = (L + 1) * (L + 1);
-  return L >= 0 && L <= kFuseMaxL && (nkr == nk || (L == 1 && nkr == 5) || (L == 2 && nkr == 14) || (L >= 3 && nkr == 30));
-}
-
-hipError_t launch_outer_fused(int L, int nkr, const float* Re, const int64_t* row_ptr, const int32_t* col,
-                              const FusedSegs& sg, int64_t n_edges, const float* featq, const int32_t* order,
-                              const float* F, int n, int C, int H, int hdiv, int n_nodes, bool accumulate, float* y,
-                              hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  if (!outer_fused_supported(L, C, H, n_nodes) || !fused_krows_supported(L, nkr)) return hipErrorInvalidValue;
-  const int nk = (L + 1) * (L + 1), mpk = 16 * ((nkr + 15) / 16);
-  // segments: start[0] = 0, increasing, each at most nk rows (the harmonics'
-  // component kr - start stays below nk)
-  if (sg.n < 1 || sg.n > kFusedSegs || sg.start[0] != 0) return hipErrorInvalidValue;
-  for (int q = 0; q < sg.n; ++q) {
-    const int end = q + 1 < sg.n ? sg.start[q + 1] : nkr;
-    if (end <= sg.start[q] || end - sg.start[q] > nk) return hipErrorInvalidValue;
-  }
-  const int nw = (nk + 3) / 4 + 1;  // a product wave per group of four components, and the staging wave
-  const size_t lds =
-      sizeof(float) * (2 * (size_t)kFuseRows * 2 * mpk + 2 * (size_t)kFuseRows + (size_t)sg.n * kOuterEdges);
-  const size_t nq = (size_t)n_nodes * H * fuse_groups(L) * 16;  // entries of the re-laid features
-  const uint4* fhm = (const uint4*)featq;
-  const uint2* flo = (const uint2*)(fhm + nq);
-  static const int rpw_env = [] {
-    const char* v = getenv("E2F_OUTER_RPW");
-    return v ? atoi(v) : 0;
-  }();
-  const int rpw = rpw_env > 0 ? rpw_env : 8;
-  const int nrx = (n + kXcds - 1) / kXcds;
-  const int64_t blocks = (int64_t)kXcds * ((nrx + rpw - 1) / rpw) * H;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-#define E2F_LAUNCH(LL, KK)                                                                                     \
-  do {                                                                                                         \
-    if (hipError_t e = allow_lds(k_outer_fused<LL, 512, KK>, lds); e != hipSuccess) return e;                  \
-    k_outer_fused<LL, 512, KK><<<(unsigned)blocks, 64 * nw, lds, s>>>(Re, row_ptr, col, sg, n_edges, fhm, flo,  \
-                                                                      order, F, n, nrx, rpw, C, H, hdiv,       \
-                                                                      n_nodes, accumulate, y);                 \
-  } while (0)
-  if (nkr != nk) {
-    switch (L) {
-      case 1: E2F_LAUNCH(1, 5); break;
-      case 2: E2F_LAUNCH(2, 14); break;
-      case 3: E2F_LAUNCH(3, 30); break;
-      case 4: E2F_LAUNCH(4, 30); break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    switch (L) {
-      case 0: E2F_LAUNCH(0, 1); break;
-      case 1: E2F_LAUNCH(1, 4); break;
-      case 2: E2F_LAUNCH(2, 9); break;
-      case 3: E2F_LAUNCH(3, 16); break;
-      case 4: E2F_LAUNCH(4, 25); break;
-      default: return hipErrorInvalidValue;
-    }
-  }
-#undef E2F_LAUNCH
   return hipGetLastError();
 }
 

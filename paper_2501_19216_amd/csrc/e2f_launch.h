@@ -61,6 +61,10 @@ hipError_t launch_plan_order(const float* pos, const int32_t* graph_id, int n, c
 hipError_t launch_plan_sh(const DevTables& t, const float* pos, const int32_t* rows, const int32_t* col, int n,
                           int64_t n_edges, const int32_t* tile_of, const TileGridDev* grid, double* Rr, float* Re,
                           hipStream_t s);
+// Re [E][nk] float32: the harmonics of r_i - r_j of every edge (unit: of the
+// unit vector, the zero vector's where the atoms coincide)
+hipError_t launch_edge_sh(const DevTables& t, const float* pos, const int64_t* row_ptr, const int32_t* col, int n,
+                          int64_t n_edges, bool unit, float* Re, hipStream_t s);
 // rows [E] = the receiver of every edge; with alpha (and alpha_hm), the same
 // launch copies the weights [E][H] head-major into alpha_hm [H][E]
 hipError_t launch_plan_edge_rows(const int64_t* row_ptr, int n, int64_t n_edges, int32_t* rows, const float* alpha,
@@ -159,44 +163,15 @@ hipError_t launch_outer_agg(const DevTables& t, const float* Re, const int64_t* 
                             const int32_t* order, const int* cmeta, const float* ccoef, const int* pmeta,
                             const float* ptab, int ntab, int ck, int cgroups, int n, int C, int H, int hdiv,
                             int n_nodes, float* S, hipStream_t s);
-// Fused aggregation and recouple (L <= kFuseMaxL, H virtual heads of 16
-// channels, C = 16 H): F rows r < n (receivers order[r]) of fuse_stride(nk)
-// floats from the fused table (fptr/fidx/fcoef, fuse_table) and R [N][nk]
-// float64; then y[order[r]] directly from the aggregated products and F row r
-// (other arguments as for launch_outer_agg)
-// (L <= kFuseMaxL, C = 16 H, and the re-laid features of n_nodes atoms
-// addressable with 32-bit entry offsets)
-bool outer_fused_supported(int L, int C, int H, int64_t n_nodes);
-// nkr: the K rows of the table's layout (fuse_stride(nk, nkr) floats a row)
-hipError_t launch_fuse_build(int L, int nkr, const int* fptr, const int* fidx, const double* fcoef,
-                             const double* R, const int32_t* order, int n, float* F, hipStream_t s);
-// featq: the features re-laid and split into bfloat16 parts by
-// launch_feat_qmajor, n_nodes * C * 6 * fuse_groups(L) floats of space (a
-// 16-byte and an 8-byte array of n_nodes * C / 16 * fuse_groups(L) * 16
-// entries each)
-int fuse_groups(int L);
-hipError_t launch_feat_qmajor(int L, const float* feat, int n, int C, float* featq, hipStream_t s);
-// The segments of the K rows of one fused aggregation (nkr rows, F from a
-// table of that layout): segment q, from K row start[q] to the next start
-// (or nkr), holds the components 0 .. of R(p_j) weighted by alpha_hm[q]
-// ([H / hdiv][n_edges] head-major, NULL: weight 1).  The plain layer: one
-// segment of nk rows; alpha / D^f: a segment per filter degree f of the
-// table, (f+1)^2 rows with the weights alpha / D^f.
-constexpr int kFusedSegs = 5;
-struct FusedSegs {
-  const float* alpha_hm[kFusedSegs];
-  int start[kFusedSegs];  // start[0] = 0, increasing; no segment longer than nk
-  int n;                  // 1 .. kFusedSegs
-};
-// K row counts the fused aggregation is built for: nk, and those of the
-// stacked alpha / D^f passes (5, 14, 30 at L = 1, 2, 3; 30 at L = 4)
-bool fused_krows_supported(int L, int nkr);
-// accumulate: the result is added to y (the sum over the filter degrees of
-// alpha / D^f), else stored
-hipError_t launch_outer_fused(int L, int nkr, const float* Re, const int64_t* row_ptr, const int32_t* col,
-                              const FusedSegs& sg, int64_t n_edges, const float* featq, const int32_t* order,
-                              const float* F, int n, int C, int H, int hdiv, int n_nodes, bool accumulate, float* y,
-                              hipStream_t s);
+// The fused aggregation (fused.hip): y[i] whole for the n receivers i =
+// order[first + r], or first + r where order is NULL, from Re
+// (launch_edge_sh), alpha [E][H] or NULL (ones) and feat; index and coef:
+// agg_tables for P = 16 / agg_group(C, H)
+int agg_group(int C, int H);
+hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr, const int32_t* col,
+                                  const float* alpha, int64_t n_edges, const float* feat, const int32_t* order,
+                                  int first, int n, int C, int H, int n_nodes, const int* index, const float* coef,
+                                  float* y, hipStream_t s);
 // y[order[r]] from S row r (head-major like T), r < n; shared_s: every r
 // reads S row 0; accumulate: y += the product instead of y = (one writer per
 // element)

@@ -506,6 +506,44 @@ __global__ __launch_bounds__(256) void k_plan_sh(DevTables t, const float* __res
   for (int q = threadIdx.x; q < cnt * NK; q += 256) dst[q] = buf[(q / NK) * NKP + q % NK];
 }
 
+// Harmonics of every edge's vector r_i - r_j, Re [E][NK] float32 (evaluated in
+// float64 from the positions, whose difference is exact there; with UNIT those
+// of the unit vector, the zero vector's at r = 0).  A thread per edge; its
+// receiver is the last row that starts at or before it, found by bisection
+// (about log2 n reads of row_ptr that the edges of a workgroup share, against
+// a launch that writes the receiver of every edge to memory and a read of it
+// here).  Rows leave through LDS as one contiguous block per workgroup.
+template <int L, bool UNIT>
+__global__ __launch_bounds__(256) void k_edge_sh(DevTables t, const float* __restrict__ pos,
+                                                 const int64_t* __restrict__ row_ptr,
+                                                 const int32_t* __restrict__ col, int n, int64_t n_edges,
+                                                 float* __restrict__ Re) {
+  constexpr int NK = (L + 1) * (L + 1), NKP = NK | 1;  // odd row stride: conflict-free LDS stores
+  __shared__ float buf[256 * NKP];
+  const int64_t e0 = (int64_t)blockIdx.x * 256, e = e0 + threadIdx.x;
+  const int cnt = (int)min((int64_t)256, n_edges - e0);
+  if (e < n_edges) {
+    int i = 0;
+    for (int hi = n; hi - i > 1;) {
+      const int mid = (i + hi) >> 1;
+      if (row_ptr[mid] <= e) i = mid;
+      else hi = mid;
+    }
+    const int j = clamp_node(col[e], n);
+    double x = (double)pos[3 * i] - (double)pos[3 * j], y = (double)pos[3 * i + 1] - (double)pos[3 * j + 1],
+           z = (double)pos[3 * i + 2] - (double)pos[3 * j + 2];
+    if constexpr (UNIT) {
+      const double d = sqrt(x * x + y * y + z * z), s = d > 0.0 ? 1.0 / d : 0.0;
+      x *= s, y *= s, z *= s;
+    }
+    float* b = buf + threadIdx.x * NKP;
+    sh_dense<L>(t, x, y, z, [&](int k, double v) { b[k] = (float)v; });
+  }
+  __syncthreads();
+  float* dst = Re + e0 * NK;
+  for (int q = threadIdx.x; q < cnt * NK; q += 256) dst[q] = buf[(q / NK) * NKP + q % NK];
+}
+
 // The receiver of every edge (rows [E]), clamped like every CSR read: a
 // wave per receiver, its lanes over the receiver's edges, in the blocks
 // below rblocks; with alpha, the blocks after copy the attention weights
@@ -638,6 +676,24 @@ hipError_t launch_plan_sh(const DevTables& t, const float* pos, const int32_t* r
 #define E2F_SH(LL)                                                                                             \
   case LL:                                                                                                     \
     k_plan_sh<LL><<<(unsigned)blocks, 256, 0, s>>>(t, pos, rows, col, n, n_edges, eblocks, tile_of, grid, Re, Rr); \
+    break;
+    E2F_SH(0) E2F_SH(1) E2F_SH(2) E2F_SH(3) E2F_SH(4) E2F_SH(5) E2F_SH(6)
+#undef E2F_SH
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_edge_sh(const DevTables& t, const float* pos, const int64_t* row_ptr, const int32_t* col, int n,
+                          int64_t n_edges, bool unit, float* Re, hipStream_t s) {
+  const int64_t blocks = (n_edges + 255) / 256;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  if (blocks == 0) return hipSuccess;
+  switch (t.L) {
+#define E2F_SH(LL)                                                                                              \
+  case LL:                                                                                                      \
+    if (unit) k_edge_sh<LL, true><<<(unsigned)blocks, 256, 0, s>>>(t, pos, row_ptr, col, n, n_edges, Re);        \
+    else k_edge_sh<LL, false><<<(unsigned)blocks, 256, 0, s>>>(t, pos, row_ptr, col, n, n_edges, Re);            \
     break;
     E2F_SH(0) E2F_SH(1) E2F_SH(2) E2F_SH(3) E2F_SH(4) E2F_SH(5) E2F_SH(6)
 #undef E2F_SH

@@ -25,7 +25,7 @@
 #include <map>
 #include <tuple>
 
-#include "e2f_internal.h"
+#include "agg_layout.h"
 
 namespace e2f {
 namespace {
@@ -605,6 +605,36 @@ FuseTable fuse_table(const LayerTables& t, const std::vector<double>& w, const i
     ft.ptr.push_back((int)ft.idx.size());
   }
   return ft;
+}
+
+AggTables agg_tables(const LayerTables& t, const std::vector<double>& w, int P) {
+  const AggMap a = agg_map(t.L, P);
+  const int nk = t.nk, nq = (a.ng * a.rb + 3) / 4;
+  std::vector<double> K((size_t)nk * nk * nk, 0.0);  // [o][q][be]
+  for (size_t s = 0; s + 1 < t.k_ptr.size(); ++s)
+    for (int e = t.k_ptr[s]; e < t.k_ptr[s + 1]; ++e) K[s * nk + t.k_ridx[e]] += t.k_unit[e] * w[t.k_path[e]];
+  AggTables r;
+  for (int be = 0; be < nk; ++be) r.index.push_back(a.pos[be]);
+  for (int v = 0; v < a.nw; ++v)
+    for (int i = 0; i < a.tw; ++i)
+      for (int p = 0; p < P; ++p) {
+        const int q = a.slotq[v][i][p];
+        r.index.push_back(q >= 0 ? q : std::max(a.slotq[v][i][0], 0));
+      }
+  for (int k = 0; k < nk; ++k) r.index.push_back(a.kkey[k] * a.rb * a.dh + a.kidx[k]);
+  r.coef.assign((size_t)a.nw * a.tw * nq * 256, 0.0f);
+  for (int v = 0; v < a.nw; ++v)
+    for (int i = 0; i < a.tw; ++i)
+      for (int m = 0; m < a.ng * a.rb; ++m)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int g = m / a.rb, row = lane % 16, p = row / a.dh;
+          const int be = a.gbe[g][lane / 16], q = a.slotq[v][i][p];
+          const int o = a.rows[a.gkey[g] ^ a.skey[i] ^ a.wkey[v]][(m % a.rb) * a.dh + row % a.dh];
+          if (be < 0 || q < 0 || o < 0) continue;
+          r.coef[((size_t)((v * a.tw + i) * nq + m / 4) * 64 + lane) * 4 + m % 4] =
+              (float)K[((size_t)o * nk + q) * nk + be];
+        }
+  return r;
 }
 
 }  // namespace e2f
