@@ -36,8 +36,9 @@ __device__ __forceinline__ v4f mfma_bf16(v4u a, v4u b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
 }
 
-// One workgroup: rpw consecutive receivers of one group of DH = 16 / P
-// channels of a head.  Edges are taken 16 a step; edge 4 r + k4 of a step
+constexpr int kAggStride = 64;
+
+// One workgroup: rpw receivers of one group of DH = 16 / P channels of a head.  Edges are taken 16 a step; edge 4 r + k4 of a step
 // belongs to lane group k4 (r < 4).  A slot is a column tile of P components
 // q x DH channels; G of a slot stays in its wave's accumulators over the whole
 // row, and the coupling reads it there: element s of the accumulator of row
@@ -61,22 +62,27 @@ __global__ __launch_bounds__(64 * agg_waves(L, P)) __attribute__((amdgpu_waves_p
 void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__ row_ptr,
                        const int32_t* __restrict__ col, const float* __restrict__ alpha, int n_edges,
                        const float* __restrict__ feat, const int32_t* __restrict__ order, int first, int n, int rpw,
-                       int nblk, int per_xcd, int C, int H, int uph, int n_nodes, const int* __restrict__ index,
+                       int nblk, int lg, int per_xcd, int C, int H, int uph, int n_nodes, const int* __restrict__ index,
                        const float4* __restrict__ coef, float* __restrict__ y) {
   constexpr AggMap M = agg_map(L, P);
   constexpr int NK = M.nk, DH = M.dh, MT = M.mt, NW = M.nw, TW = M.tw, NG = M.ng, RB = M.rb, KEYS = M.keys;
   constexpr int NT = 64 * NW, NACC = KEYS * RB, NQ = (NG * RB + 3) / 4;
+  constexpr bool PIPE = MT == 2;
   constexpr int NST = (4 * NK + NT - 1) / NT;  // staging passes: a thread per (component, k4)
-  __shared__ float4 la[2][MT * 64];                   // alpha R: split {lo01, lo23, hi01, hi23}, else four floats
-  __shared__ uint2 lm[SPLIT ? 2 : 1][SPLIT ? MT * 64 : 1];  // {mid01, mid23}
+  __shared__ float4 la[2][MT * 64 + 1];  // alpha R: split {lo01, lo23, hi01, hi23}, else four floats
+  __shared__ uint2 lm[SPLIT ? 2 : 1][SPLIT ? MT * 64 + 1 : 1];  // {mid01, mid23} (the last entries: idle threads')
   __shared__ float red[NW * P > 1 ? NW * NACC * 256 : 1];
-  // a contiguous range of (column group, receivers) items per XCD, column
-  // group major: the workgroups in flight on an XCD read the same channels of
-  // neighbouring atoms, which then stay in its L2
-  const int xcd = blockIdx.x % 8, item = xcd * per_xcd + blockIdx.x / 8;
-  const int unit = item / nblk, r0 = (item % nblk) * rpw;
-  if (unit >= C / DH || (int)(blockIdx.x / 8) >= per_xcd) return;
-  const int nrec = min(rpw, n - r0);
+  // XCD x takes a contiguous range of items; an item is a receiver set and a
+  // column group, the column groups of one 128-byte line (lg of them) first,
+  // then the sets, then the lines: the workgroups in flight on an XCD read the
+  // same lines of neighbouring atoms, which then stay in its L2.  The rpw
+  // receivers of a set are kAggStride apart, so that the kAggStride sets in
+  // flight side by side move through the order together.
+  const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int unit = item / (nblk * lg) * lg + item % lg, set = item / lg % nblk;
+  const int r0 = set / kAggStride * (kAggStride * rpw) + set % kAggStride;
+  if (unit >= C / DH || r0 >= n) return;
+  const int nrec = min(rpw, (n - 1 - r0) / kAggStride + 1);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
   const int l16 = lane & 15, k4 = lane >> 4;
@@ -85,7 +91,8 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
   // malformed graph cannot move a read outside the caller's buffers)
   int vi = 0, va = 0, vb = 0;
   if (lane < nrec) {
-    vi = order ? order[first + r0 + lane] : first + r0 + lane;
+    vi = first + r0 + lane * kAggStride;
+    if (order) vi = order[vi];
     const int64_t p0 = row_ptr[vi], p1 = row_ptr[vi + 1];
     va = (int)max((int64_t)0, min(p0, (int64_t)n_edges));
     vb = (int)max((int64_t)va, min(p1, (int64_t)n_edges));
@@ -119,9 +126,12 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
   const char* fbase = (const char*)(feat + c0);
   const OFF loff = P == 1 ? (OFF)l16 * 4 : 0;
   const OFF stride = (OFF)NK * C * 4;
+  // (edge e of a step: a uniform base and a lane offset; past the row's end
+  // the last edge)
   auto senders = [&](Step s, int (&j)[4]) {
+    const int* cb = col + s.e;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) j[r] = col[min(s.e + 4 * r + k4, s.end - 1)];
+    for (int r = 0; r < 4; ++r) j[r] = cb[(unsigned)min(4 * r + k4, s.end - s.e - 1)];
   };
   auto offsets = [&](const int (&j)[4], OFF (&o)[4]) {
 #pragma unroll
@@ -134,27 +144,28 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
   // staging: thread (component be, lane group g) holds the step's four edges
   // 4 r + g
   int sbe[NST], sg[NST], spos[NST];
-  bool son[NST];
 #pragma unroll
   for (int u = 0; u < NST; ++u) {
     const int t = tid + u * NT;
-    son[u] = t < 4 * NK;
-    sbe[u] = son[u] ? t % NK : 0;
-    sg[u] = son[u] ? t / NK : 0;
+    const bool son = t < 4 * NK;
+    sbe[u] = son ? t % NK : 0;
+    sg[u] = son ? t / NK : 0;
     const int p = index[sbe[u]];
-    spos[u] = (p >> 4) * 64 + sg[u] * 16 + (p & 15);
+    spos[u] = son ? (p >> 4) * 64 + sg[u] * 16 + (p & 15) : MT * 64;
   }
   float sr[NST][4], sw[NST][4];
   const float* wbase = alpha ? alpha + head : Re;  // without weights any readable float
   const int wstride = alpha ? H : 0;
   auto fetch = [&](Step s) {
+    const float* rb = Re + (size_t)s.e * NK;
+    const float* wb = wbase + (size_t)s.e * wstride;
 #pragma unroll
     for (int u = 0; u < NST; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int e = s.e + 4 * r + sg[u], ec = min(e, s.end - 1);
-        sr[u][r] = Re[(size_t)ec * NK + sbe[u]];
-        sw[u][r] = wbase[(size_t)ec * wstride];
+        const unsigned e = min(4 * r + sg[u], s.end - s.e - 1);
+        sr[u][r] = rb[__umul24(e, NK) + sbe[u]];
+        sw[u][r] = wb[__umul24(e, wstride)];
       }
   };
   auto store = [&](Step s, int b) {
@@ -162,8 +173,7 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
     for (int u = 0; u < NST; ++u) {
       float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = s.e + 4 * r + sg[u] < s.end ? (alpha ? sw[u][r] : 1.0f) * sr[u][r] : 0.0f;
-      if (!son[u]) continue;
+      for (int r = 0; r < 4; ++r) v[r] = 4 * r + sg[u] < s.end - s.e ? (alpha ? sw[u][r] : 1.0f) * sr[u][r] : 0.0f;
       if constexpr (SPLIT) {
         unsigned h[2], m[2], l[2];
         split_pair(v[0], v[1], h[0], m[0], l[0]);
@@ -181,7 +191,7 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[i][mt] = (v4f){0.f, 0.f, 0.f, 0.f};
   // rows without a component stay zero
-  for (int q = tid; q < 2 * MT * 64; q += NT) {
+  for (int q = tid; q < 2 * (MT * 64 + 1); q += NT) {
     (&la[0][0])[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     if constexpr (SPLIT) (&lm[0][0])[q] = make_uint2(0, 0);
   }
@@ -203,11 +213,16 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
   for (int b = 0;; b ^= 1) {
     __syncthreads();  // alpha R of s0 is staged; the other buffer is free
     const Step s2 = next(s1);
-    store(s1, b ^ 1);
-    fetch(s2);
     offsets(jn, o);
-    senders(s2, jn);
+    // the next step's alpha R goes to the other buffer, and the loads of the
+    // one after start
+    auto stage = [&] {
+      store(s1, b ^ 1);
+      fetch(s2);
+      senders(s2, jn);
+    };
     if constexpr (SPLIT) {
+      if (!PIPE) stage();
       v4u a0[MT], a1[MT], a2[MT];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
@@ -216,22 +231,39 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
         a0[mt] = (v4u){a2[mt][2], a2[mt][3], a2[mt][2], a2[mt][3]};
         a1[mt] = (v4u){m.x, m.y, m.x, m.y};
       }
-#pragma unroll
-      for (int i = 0; i < TW; ++i) {
-        unsigned h[2], m[2], l[2];
-        split_pair(f[i][0], f[i][1], h[0], m[0], l[0]);
-        split_pair(f[i][2], f[i][3], h[1], m[1], l[1]);
+      unsigned h[2][2], m[2][2], l[2][2];  // the split values of two slots
+      auto split = [&](int i) {
+        split_pair(f[i][0], f[i][1], h[i & 1][0], m[i & 1][0], l[i & 1][0]);
+        split_pair(f[i][2], f[i][3], h[i & 1][1], m[i & 1][1], l[i & 1][1]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) f[i][r] = value(i, o[r]);
-        const v4u bm = {m[0], m[1], h[0], h[1]}, bl = {h[0], h[1], l[0], l[1]};
+      };
+      if (PIPE) split(0);
+#pragma unroll
+      for (int i = 0; i < TW; ++i) {
+        if (!PIPE) split(i);
+        else if (i + 1 < TW) split(i + 1);
+        if (PIPE && i == TW / 2) stage();
+        const int w = i & 1;
+        const v4u bm = {m[w][0], m[w][1], h[w][0], h[w][1]}, bl = {h[w][0], h[w][1], l[w][0], l[w][1]};
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[i][mt] = mfma_bf16(a0[mt], bm, acc[i][mt]);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[i][mt] = mfma_bf16(a1[mt], bm, acc[i][mt]);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[i][mt] = mfma_bf16(a2[mt], bl, acc[i][mt]);
+        // the next slot's split and loads between this one's matrix
+        // instructions: a wave issues in order, and a burst of them would
+        // keep its own ALU work waiting behind the matrix core
+#pragma unroll
+        for (int u = 0; u < 3 * MT && PIPE; ++u) {
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, (28 + (P > 1 ? 4 : 0) + 3 * MT - 1) / (3 * MT), 0);
+          if (u >= 3 * MT - 4) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+        }
       }
     } else {
+      stage();
       float4 a[MT];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) a[mt] = la[b][mt * 64 + lane];
@@ -336,6 +368,8 @@ hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr
   if (n <= 0) return hipSuccess;
   const int dh = agg_group(C, H), P = 16 / dh, units = C / dh;
   const int nk = nk_of(L);
+  int lg = std::min(32 / dh, units);  // column groups of one line
+  while (units % lg) --lg;
   const bool wide = (double)n_nodes * nk * C * 4.0 > 4.0e9;
 #define E2F_AGG(LL, PP, SP)                                                                                        \
   if (L == LL && P == PP) {                                                                                        \
@@ -343,16 +377,16 @@ hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr
     /* receivers a workgroup: the steps of consecutive ones overlap, as long as every CU has work */              \
     const int64_t slots = 256 * (LL >= 4 ? 8 : 12) / nw;                                                           \
     const int rpw = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)n * units / (slots * 4)));             \
-    const int nblk = (n + rpw - 1) / rpw;                                                                          \
+    const int nblk = (n + kAggStride * rpw - 1) / (kAggStride * rpw) * kAggStride;                                 \
     const int64_t per = ((int64_t)nblk * units + 7) / 8;                                                           \
     if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                         \
     if (wide)                                                                                                      \
       k_aggregate_fused<LL, PP, SP, uint64_t><<<(unsigned)(8 * per), 64 * nw, 0, s>>>(                             \
-          Re, row_ptr, col, alpha, (int)n_edges, feat, order, first, n, rpw, nblk, (int)per, C, H, C / H / dh,     \
+          Re, row_ptr, col, alpha, (int)n_edges, feat, order, first, n, rpw, nblk, lg, (int)per, C, H, C / H / dh,     \
           n_nodes, index, (const float4*)coef, y);                                                                 \
     else                                                                                                           \
       k_aggregate_fused<LL, PP, SP, uint32_t><<<(unsigned)(8 * per), 64 * nw, 0, s>>>(                             \
-          Re, row_ptr, col, alpha, (int)n_edges, feat, order, first, n, rpw, nblk, (int)per, C, H, C / H / dh,     \
+          Re, row_ptr, col, alpha, (int)n_edges, feat, order, first, n, rpw, nblk, lg, (int)per, C, H, C / H / dh,     \
           n_nodes, index, (const float4*)coef, y);                                                                 \
     return hipGetLastError();                                                                                      \
   }
