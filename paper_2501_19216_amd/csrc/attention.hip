@@ -4,17 +4,22 @@
 //   mu_r = r cutoff / (R - 1), sigma = cutoff / (R - 1), d = |r_i - r_j|,
 //   alpha[(i,j)][h] = env(d) * softmax over the row of logit[.][h],
 //   env(d) = (cos(pi d / cutoff) + 1) / 2 below the cutoff, 0 from it on.
-// One wave per receiver row: lane l takes head l % Hp (Hp = H rounded up to a
-// power of two) and every (64/Hp)-th edge, so a wave's accesses of alpha
-// [E][H] are contiguous and the per-head max and sum are xor-shuffle
-// reductions over the lanes of one head (fixed order: deterministic).  The
-// logits are computed once and kept in alpha between the passes.
+// One wave per receiver row.  Distances, envelopes and radial functions belong
+// to an edge, not to a head: the wave evaluates them a lane per edge, 64 edges
+// at a time, into LDS.  Then lane l takes head l % Hp (Hp = H rounded up to a
+// power of two) and every (64/Hp)-th edge, so a wave's accesses of alpha [E][H]
+// and of a sender's k are contiguous and the per-head max and sum are
+// xor-shuffle reductions over the lanes of one head (fixed order:
+// deterministic).  The logits of rows up to kAttnIter 64/Hp edges stay in
+// registers; longer rows keep them in alpha between the passes.
 #include <hip/hip_runtime.h>
 
 #include "e2f_launch.h"
 
 namespace e2f {
 namespace {
+
+constexpr int kAttnIter = 16;
 
 template <int HP>
 __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos, const float* __restrict__ q,
@@ -23,9 +28,13 @@ __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos
                                                    const int64_t* __restrict__ row_ptr,
                                                    const int32_t* __restrict__ col, float* __restrict__ alpha) {
   constexpr int EPI = 64 / HP;  // edges per wave iteration
+  extern __shared__ float sm[];
   const int i = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-  if (i >= n) return;  // uniform over the wave
+  if (i >= n) return;  // uniform over the wave (no barrier below)
   const int lane = threadIdx.x & 63;
+  // the wave's 64 rows: R radial functions, envelope, sender (odd stride)
+  const int ld = (R + 2) | 1;
+  float* rows = sm + (threadIdx.x >> 6) * 64 * ld;
   const int h = lane % HP, el = lane / HP;
   const bool hv = h < H;
   const int hc = hv ? h : 0;
@@ -44,10 +53,27 @@ __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos
   for (int t = 0; t < 16; ++t)
     q4[t] = (vec && 4 * t < dk) ? ((const float4*)qi)[t] : make_float4(0.f, 0.f, 0.f, 0.f);
   const float kPi = 3.14159265358979f;
-  auto logit = [&](int64_t e, float& env) {
-    const int j = col[e];
-    const float dx = xi - pos[3 * j], dy = yi - pos[3 * j + 1], dz = zi - pos[3 * j + 2];
-    const float d = sqrtf(dx * dx + dy * dy + dz * dz);
+  // the rows of the 64 edges from c on
+  auto fill = [&](int64_t c) {
+    __builtin_amdgcn_wave_barrier();
+    const int64_t e = c + lane;
+    if (e < e1) {
+      const int j = col[e];
+      const float dx = xi - pos[3 * j], dy = yi - pos[3 * j + 1], dz = zi - pos[3 * j + 2];
+      const float d = sqrtf(dx * dx + dy * dy + dz * dz);
+      float* o = rows + lane * ld;
+      for (int r = 0; r < R; ++r) {
+        const float z = (d - (float)r * sigma) * inv;
+        o[r] = expf(-z * z);
+      }
+      o[R] = d < rc ? 0.5f * (cosf(kPi * d / rc) + 1.0f) : 0.0f;
+      o[R + 1] = __int_as_float(j);
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  // logit of the edge whose row is o
+  auto logit = [&](const float* o) {
+    const int j = __float_as_int(o[R + 1]);
     const float* kj = kf + ((size_t)j * H + hc) * dk;
     float l = 0.0f;
     if (vec) {
@@ -62,26 +88,50 @@ __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos
       for (int t = 0; t < dk; ++t) l += qi[t] * kj[t];
     }
 #pragma unroll
-    for (int r = 0; r < kAttnMaxRbf; ++r) {
-      if (r < R) {
-        const float z = (d - (float)r * sigma) * inv;
-        l += w[r] * expf(-z * z);
-      }
-    }
-    env = d < rc ? 0.5f * (cosf(kPi * d / rc) + 1.0f) : 0.0f;
+    for (int r = 0; r < kAttnMaxRbf; ++r)
+      if (r < R) l += w[r] * o[r];
     return l;
   };
+  float mx = -INFINITY, den = 0.0f;
+  if (e1 - e0 <= kAttnIter * EPI) {
+    float l[kAttnIter], env[kAttnIter];
+    const int deg = (int)(e1 - e0);
+#pragma unroll
+    for (int it = 0; it < kAttnIter; ++it) {
+      l[it] = -INFINITY, env[it] = 0.0f;
+      if (it * EPI >= deg) continue;  // uniform
+      if (it % HP == 0) fill(e0 + it * EPI);
+      const float* o = rows + (it % HP * EPI + el) * ld;
+      if (it * EPI + el < deg) l[it] = logit(o), env[it] = o[R];
+      mx = fmaxf(mx, l[it]);
+    }
+#pragma unroll
+    for (int o = 32; o >= HP; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+#pragma unroll
+    for (int it = 0; it < kAttnIter; ++it) {
+      if (it * EPI >= deg) continue;
+      l[it] = it * EPI + el < deg ? expf(l[it] - mx) : 0.0f;
+      den += l[it];
+    }
+#pragma unroll
+    for (int o = 32; o >= HP; o >>= 1) den += __shfl_xor(den, o);
+    const float rden = 1.0f / den;
+#pragma unroll
+    for (int it = 0; it < kAttnIter; ++it)
+      if (it * EPI + el < deg && hv) alpha[(e0 + it * EPI + el) * H + h] = env[it] * l[it] * rden;
+    return;
+  }
   // pass 1: logits, kept in the output; pass 2: exponentials; pass 3: scale
-  float mx = -INFINITY;
-  for (int64_t e = e0 + el; e < e1; e += EPI) {
-    float env;
-    const float l = logit(e, env);
-    if (hv) alpha[e * H + h] = l;
-    mx = fmaxf(mx, l);
+  for (int64_t c = e0; c < e1; c += 64) {
+    fill(c);
+    for (int64_t e = c + el; e < min(c + 64, e1); e += EPI) {
+      const float l = logit(rows + (e - c) * ld);
+      if (hv) alpha[e * H + h] = l;
+      mx = fmaxf(mx, l);
+    }
   }
 #pragma unroll
   for (int o = 32; o >= HP; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-  float den = 0.0f;
   for (int64_t e = e0 + el; e < e1; e += EPI) {
     if (!hv) continue;
     const float ex = expf(alpha[e * H + h] - mx);
@@ -91,13 +141,10 @@ __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos
 #pragma unroll
   for (int o = 32; o >= HP; o >>= 1) den += __shfl_xor(den, o);
   const float rden = 1.0f / den;
-  for (int64_t e = e0 + el; e < e1; e += EPI) {
-    if (!hv) continue;
-    const int j = col[e];
-    const float dx = xi - pos[3 * j], dy = yi - pos[3 * j + 1], dz = zi - pos[3 * j + 2];
-    const float d = sqrtf(dx * dx + dy * dy + dz * dz);
-    const float env = d < rc ? 0.5f * (cosf(kPi * d / rc) + 1.0f) : 0.0f;
-    alpha[e * H + h] = env * alpha[e * H + h] * rden;
+  for (int64_t c = e0; c < e1; c += 64) {
+    fill(c);
+    for (int64_t e = c + el; e < min(c + 64, e1); e += EPI)
+      if (hv) alpha[e * H + h] = rows[(e - c) * ld + R] * alpha[e * H + h] * rden;
   }
 }
 
@@ -110,10 +157,11 @@ hipError_t launch_attention(const float* pos, const float* q, const float* k, in
   int hp = 1;
   while (hp < H) hp <<= 1;
   const unsigned grid = (unsigned)((n + 3) / 4);
+  const size_t lds = sizeof(float) * 4 * 64 * ((R + 2) | 1);  // at most 35 KB
   switch (hp) {
 #define E2F_ATT(P)                                                                                     \
   case P:                                                                                              \
-    k_attention<P><<<grid, 256, 0, s>>>(pos, q, k, n, H, dk, rbf_w, R, rc, row_ptr, col_idx, alpha);   \
+    k_attention<P><<<grid, 256, lds, s>>>(pos, q, k, n, H, dk, rbf_w, R, rc, row_ptr, col_idx, alpha);   \
     break;
     E2F_ATT(1) E2F_ATT(2) E2F_ATT(4) E2F_ATT(8) E2F_ATT(16) E2F_ATT(32) E2F_ATT(64)
 #undef E2F_ATT
