@@ -69,6 +69,7 @@ struct e2f_ctx {
     // fused aggregation, per column group width 16, 8, 4 (P = 1, 2, 4)
     const int* agg_index[3] = {};
     const float* agg_coef[3] = {};
+    const float* grad_coef = nullptr;  // the backward's per-edge products
   };
   std::vector<std::vector<CoefSet>> coefs;
   // per L and filter degree f: the recouple schedule restricted to b + u = f
@@ -99,14 +100,6 @@ struct e2f_ctx {
     float* tab = nullptr;
   };
   std::map<std::pair<int, int>, Couple> couple;
-  // schedules of the backward's filter contraction, per (L, rows per pass)
-  struct Geom {
-    int qc = 0, tot = 0;  // filter rows per pass, schedule entries
-    int* meta = nullptr;
-    float* unit = nullptr;
-    int* oc = nullptr;  // [nchunk][2]: offset, steps
-  };
-  std::map<std::pair<int, int>, Geom> geom;  // per (L, head width)
 };
 
 namespace {
@@ -226,37 +219,6 @@ e2f_status couple_of(e2f_ctx* ctx, int L, int groups, const e2f_ctx::Couple*& ou
       E2F_HIP(hipMemcpy(c.tab, cs.tab.data(), sizeof(float) * cs.tab.size(), hipMemcpyHostToDevice));
     }
     it = ctx->couple.emplace(key, c).first;
-  }
-  out = &it->second;
-  return E2F_OK;
-}
-
-// The backward's filter-contraction schedule for (L, head width dh), uploaded
-// on first use: the most filter rows per pass whose LDS (gy slice, schedule
-// up to L = 4, Z) fits 40 KB, so that four workgroups share a CU; else one
-// row per pass.
-e2f_status geom_of(e2f_ctx* ctx, int L, int dh, const e2f_ctx::Geom*& out) {
-  auto key = std::make_pair(L, dh);
-  auto it = ctx->geom.find(key);
-  if (it == ctx->geom.end()) {
-    const LayerTables& t = ctx->host[L];
-    GeomSchedule gs;
-    for (int qc = t.nk; qc >= 1; --qc) {
-      gs = geom_schedule(t, qc);
-      if (edge_geom_lds(L, dh, qc, (int)gs.meta.size()) <= 40960) break;
-    }
-    std::vector<int> oc;
-    for (int c = 0; c < gs.nchunk; ++c) oc.push_back(gs.off[c]), oc.push_back(gs.ck[c]);
-    e2f_ctx::Geom g;
-    g.qc = gs.qc;
-    g.tot = (int)gs.meta.size();
-    E2F_HIP(hipMalloc((void**)&g.meta, sizeof(int) * std::max<size_t>(gs.meta.size(), 1)));
-    E2F_HIP(hipMalloc((void**)&g.unit, sizeof(float) * std::max<size_t>(gs.unit.size(), 1)));
-    E2F_HIP(hipMalloc((void**)&g.oc, sizeof(int) * std::max<size_t>(oc.size(), 1)));
-    E2F_HIP(hipMemcpy(g.meta, gs.meta.data(), sizeof(int) * gs.meta.size(), hipMemcpyHostToDevice));
-    E2F_HIP(hipMemcpy(g.unit, gs.unit.data(), sizeof(float) * gs.unit.size(), hipMemcpyHostToDevice));
-    E2F_HIP(hipMemcpy(g.oc, oc.data(), sizeof(int) * oc.size(), hipMemcpyHostToDevice));
-    it = ctx->geom.emplace(key, g).first;
   }
   out = &it->second;
   return E2F_OK;
@@ -410,6 +372,7 @@ e2f_status coef_of(e2f_ctx* ctx, int L, const std::vector<double>& w, bool allow
     push_array(blob, o, ag.index);
     push_array(blob, o, ag.coef);
   }
+  push_array(blob, o, grad_table(t, w));  // o[11 + L]
   if (sets.size() >= kMaxCoefSets) {  // the oldest set may still be read by queued work
     E2F_HIP(hipDeviceSynchronize());
     E2F_HIP(hipFree(sets.front().mem));
@@ -433,6 +396,7 @@ e2f_status coef_of(e2f_ctx* ctx, int L, const std::vector<double>& w, bool allow
     c.agg_index[q] = (const int*)((char*)mem + o[5 + L + 2 * q]);
     c.agg_coef[q] = (const float*)((char*)mem + o[6 + L + 2 * q]);
   }
+  c.grad_coef = (const float*)((char*)mem + o[11 + L]);
   sets.push_back(std::move(c));
   out = &sets.back();
   return E2F_OK;
@@ -843,11 +807,6 @@ void e2f_destroy(e2f_ctx* ctx) {
       if (kv.second.coef) (void)hipFree(kv.second.coef);
       if (kv.second.pmeta) (void)hipFree(kv.second.pmeta);
       if (kv.second.tab) (void)hipFree(kv.second.tab);
-    }
-    for (auto& kv : ctx->geom) {
-      if (kv.second.meta) (void)hipFree(kv.second.meta);
-      if (kv.second.unit) (void)hipFree(kv.second.unit);
-      if (kv.second.oc) (void)hipFree(kv.second.oc);
     }
     for (auto& r : ctx->recs) {
       ctx->pool.push_back(r.start);
@@ -1272,7 +1231,9 @@ e2f_status e2f_wigner6j_conv_backward(e2f_ctx* ctx, const e2f_conv_params* p, co
                       (want_t ? 5 * al256(sizeof(int32_t) * (size_t)n_edges) + 2 * al256(sizeof(int64_t) * (n + 1)) +
                                     al256(sizeof(float) * (size_t)n_edges * H) + al256(tmp_b)
                               : 0) +
-                      (grad_pos ? al256(sizeof(float) * (size_t)n_edges * 3) : 0) + al256(gt_bytes) + 256;
+                      (grad_pos ? al256(sizeof(float) * (size_t)n_edges * 3) : 0) + al256(gt_bytes) +
+                      (grad_pos && H > 1 ? al256(sizeof(float) * (size_t)n_edges * 3 * H) : 0) +
+                      (grad_alpha ? al256(sizeof(float) * (size_t)n_edges * nk) : 0) + 256;
   rs = ensure(ctx, ctx->d, need, s);
   if (rs != E2F_OK) return rs;
   Carver cd{(char*)ctx->d.p};
@@ -1313,13 +1274,13 @@ e2f_status e2f_wigner6j_conv_backward(e2f_ctx* ctx, const e2f_conv_params* p, co
   // (receiver, head); then per atom the forces received minus those sent
   float* gedge = grad_pos ? cd.take<float>((size_t)n_edges * 3) : nullptr;
   float* Gt = gt_bytes ? cd.take<float>(gt_bytes / sizeof(float)) : nullptr;
-  if (Gt) E2F_TIMED("edge_geom", launch_edge_shgrad(tw, pos, rows, col_idx, n_edges, Gt, s));
+  if (Gt) E2F_TIMED("edge_geom", launch_edge_shgrad(tw, pos, rows, col_idx, n, n_edges, Gt, s));
   if (grad_alpha || gedge) {
-    const e2f_ctx::Geom* gsch = nullptr;
-    if ((rs = geom_of(ctx, L, C / H, gsch)) != E2F_OK) return rs;
-    E2F_TIMED("edge_geom", launch_edge_geom(tw, pos, feat, gy, row_ptr, col_idx, alpha, n, C, H, gsch->qc,
-                                            gsch->meta, gsch->unit, gsch->oc, gsch->tot, Gt, n_edges, grad_alpha,
-                                            gedge, s));
+    float* Re = grad_alpha ? cd.take<float>((size_t)n_edges * nk) : nullptr;
+    if (Re) E2F_TIMED("sh", launch_edge_sh(tw, pos, row_ptr, col_idx, n, n_edges, false, Re, s));
+    float* gpart = gedge && H > 1 ? cd.take<float>((size_t)n_edges * 3 * H) : nullptr;
+    E2F_TIMED("edge_geom", launch_edge_grad(tw, pos, Re, Gt, feat, gy, row_ptr, col_idx, alpha, nullptr, n, C, H,
+                                            n_edges, cs->grad_coef, grad_alpha, gpart, gedge, s));
   }
   if (gedge) E2F_TIMED("force_gather", launch_force_gather(row_ptr, rowT, perm, gedge, n, grad_pos, s));
   // ---- features: the same layer on the transposed graph, input degree o,

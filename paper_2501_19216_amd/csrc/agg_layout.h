@@ -145,5 +145,10 @@ struct AggTables {
   std::vector<float> coef;
 };
 AggTables agg_tables(const LayerTables& t, const std::vector<double>& w, int P);
+// The coupling as the backward's per-edge products read it (edge_grad.hip):
+// element (q ng + g) * 64 + lane of agg_map(L, 1)'s groups and keys, K[o][be][q]
+// for o = member lane / 16 of group g and be = member lane % 16 of key gkey[g]
+// ^ key(q).
+std::vector<float> grad_table(const LayerTables& t, const std::vector<double>& w);
 
 }  // namespace e2f

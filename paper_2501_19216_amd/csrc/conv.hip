@@ -41,31 +41,6 @@ __device__ __forceinline__ F sh_poly(const DevTables& t, int k, F x, F y, F z) {
   return acc;
 }
 
-// Gradient of one solid harmonic from its monomials: d/dx of c x^a y^b z^e
-// is c a x^(a-1) y^b z^e (no term when a = 0).
-template <typename F>
-__device__ __forceinline__ void sh_poly_grad(const DevTables& t, int k, F x, F y, F z, F& gx, F& gy, F& gz) {
-  // per monomial one power loop per coordinate: b^(n-1) (1 for n = 0, where
-  // the derivative's factor n is 0), then b^n = b^(n-1) b selected without a
-  // branch
-  auto pm1 = [](F b, int n) {
-    F r = 1;
-    for (int q = 1; q < n; ++q) r *= b;
-    return r;
-  };
-  gx = 0, gy = 0, gz = 0;
-  for (int e = t.sh_ptr[k]; e < t.sh_ptr[k + 1]; ++e) {
-    const int pw = t.sh_pow[e];
-    const int ex = pw & 15, ey = (pw >> 4) & 15, ez = (pw >> 8) & 15;
-    const F c = (F)t.sh_coef[e];
-    const F xm = pm1(x, ex), ym = pm1(y, ey), zm = pm1(z, ez);
-    const F X = ex > 0 ? xm * x : (F)1, Y = ey > 0 ? ym * y : (F)1, Z = ez > 0 ? zm * z : (F)1;
-    gx += c * (F)ex * xm * Y * Z;
-    gy += c * (F)ey * X * ym * Z;
-    gz += c * (F)ez * X * Y * zm;
-  }
-}
-
 __global__ void k_sh(DevTables t, const float* __restrict__ pos, const int32_t* __restrict__ node_of,
                      const double* __restrict__ origins_d, const float* __restrict__ origins_f,
                      const int32_t* __restrict__ origin_id, int origin_mod, int n, double* __restrict__ out_d,
@@ -1059,260 +1034,6 @@ __global__ __launch_bounds__(64 * kMixWaves) void k_mix_mfma(const float* __rest
   }
 }
 
-// ------------------------------------------------------------ backward
-// Both per-edge products of the backward from one matrix product per
-// (receiver, head).  The edge filter is linear in the solid harmonics,
-// K_e[k][q] = sum_be R_be(r_e) Kc[be][k][q] with Kc the path-weighted filter
-// coefficients, so the receiver's output gradient folds into
-//   Z_i[be][q][c] = sum_k gy_i[k][c] Kc[be][k][q]
-// and per head h one contraction over (q, c of h),
-//   X_h[be][e] = sum_{q, c of h} Z_i[be][q][c] h_{j(e)}[q][c],
-// gives both outputs of edge e = (i, j), r_e = r_i - r_j:
-//   galpha[e][h] = sum_be R_be(r_e) X_h[be][e],
-//   gedge[e][x]  = sum_be dR_be/dx(r_e) W[be][e],  W = sum_h alpha_eh X_h.
-// The contraction runs on v_mfma_f32_16x16x4f32 with be as rows (MT tiles
-// of 16), edges as columns (tiles of 16 edges; NTE tiles per wave, the
-// wave's tiles are wave + NW et) and kappa = q dh + c as the reduction:
-// step st covers kappa in [16 st, 16 st + 16), lane group k4 takes kappa =
-// 16 st + 4 k4 .. + 3 (four channels of one row q, as 4 | dh) as one float4,
-// and MFMA w of four uses component w.  LDS holds, per workgroup, the schedule of the Z
-// sums (path weights folded in, staged once; read from global memory above
-// L = 4, where it outgrows LDS), the head's slice of gy_i and Z
-// for qc rows q at a time (Z[be][kappa - q0 dh]), with a row stride of
-// qc dh + 4 or + 8 floats, an odd number of quadruples (the 16 rows be of an
-// operand read start in distinct bank quadruples).  A workgroup takes
-// rpw consecutive receivers; edge chunks of NW NTE 16 edges, Z rebuilt per
-// chunk, head and row pass.  Each output element has one writer.
-template <int L, int NTE, bool WA, bool WP, bool GT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_edge_geom(DevTables t, const float* __restrict__ pos,
-                                                   const float* __restrict__ feat, const float* __restrict__ gy,
-                                                   const int64_t* __restrict__ row_ptr,
-                                                   const int32_t* __restrict__ col, const float* __restrict__ alpha,
-                                                   int n, int rpw, int C, int H, int qc,
-                                                   const int* __restrict__ gmeta, const float* __restrict__ gunit,
-                                                   const int* __restrict__ goc, int gtot,
-                                                   const float* __restrict__ Gt, int64_t n_edges,
-                                                   float* __restrict__ galpha, float* __restrict__ gedge) {
-  constexpr int NK = (L + 1) * (L + 1), MT = (NK + 15) / 16;
-  constexpr bool STAGED = L <= 4;  // the schedule in LDS (it outgrows LDS above L = 4)
-  extern __shared__ float4 sm4[];
-  const int dh = C / H, dq = dh >> 2, ZS = qc * dh + (((qc * dh) >> 2) & 1 ? 8 : 4);
-  float* gyl = (float*)sm4;  // [NK][dh]: gy_i of the head
-  // STAGED: [gtot] schedule, [gtot] its coefficients times the path weights
-  int* smeta = (int*)(gyl + NK * dh);
-  float* sunit = gyl + NK * dh + gtot;
-  float* Z = gyl + NK * dh + (STAGED ? 2 * gtot : 0);  // [NK be][ZS]: Z[be][qq][c] at be*ZS + qq*dh + c
-  if (STAGED)
-    for (int x = threadIdx.x; x < gtot; x += blockDim.x) {
-      const int m = gmeta[x];
-      smeta[x] = m;
-      sunit[x] = gunit[x] * t.w_f[(m >> 18) & 511];
-    }
-  // workgroup -> rpw consecutive receivers; the receivers of one XCD are contiguous
-  const int nxr = (n + 7) / 8, xcd = blockIdx.x % 8;
-  const int rfirst = xcd * nxr + (blockIdx.x / 8) * rpw;
-  const int rlast = min(min(rfirst + rpw, (xcd + 1) * nxr), n);  // uniform over the workgroup
-  const int NW = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int l16 = lane & 15, k4 = lane >> 4;
-  const int grp = threadIdx.x >> 2, sub = threadIdx.x & 3;  // kGeomGroups groups of four threads
-  for (int i = rfirst; i < rlast; ++i) {
-    const int64_t e0 = row_ptr[i], e1 = row_ptr[i + 1];
-    const float xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
-    const float* gyi = gy + (size_t)i * NK * C;
-    for (int64_t c0 = e0; c0 < e1; c0 += NW * NTE * 16) {
-      const int ne = (int)min((int64_t)NW * NTE * 16, e1 - c0);
-      const int ntiles = (ne + 15) / 16;
-      int jn[NTE];
-      bool ev[NTE], tlive[NTE];
-#pragma unroll
-      for (int et = 0; et < NTE; ++et) tlive[et] = __builtin_amdgcn_readfirstlane(wave + NW * et < ntiles ? 1 : 0) != 0;
-      float dx[NTE], dy[NTE], dz[NTE];
-      float Rv[NTE][MT][4];
-      v4f W[NTE][MT];
-#pragma unroll
-      for (int et = 0; et < NTE; ++et) {
-        const int nb = (wave + NW * et) * 16 + l16;
-        ev[et] = nb < ne;
-        jn[et] = col[c0 + (ev[et] ? nb : 0)];  // columns past ne read a valid sender, never stored
-        dx[et] = xi - pos[3 * jn[et]], dy[et] = yi - pos[3 * jn[et] + 1], dz[et] = zi - pos[3 * jn[et] + 2];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          W[et][mt] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int be = mt * 16 + 4 * k4 + v;
-            Rv[et][mt][v] = (WA && be < NK) ? sh_poly<float>(t, be, dx[et], dy[et], dz[et]) : 0.0f;
-          }
-        }
-      }
-      for (int h = 0; h < H; ++h) {
-        // every thread has passed a barrier since the last Z sums read gyl
-        for (int x = threadIdx.x; x < NK * dq; x += blockDim.x)
-          *(float4*)(gyl + 4 * x) = *(const float4*)(gyi + (size_t)(x / dq) * C + h * dh + 4 * (x % dq));
-        v4f X[NTE][MT];
-#pragma unroll
-        for (int et = 0; et < NTE; ++et)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) X[et][mt] = (v4f){0.f, 0.f, 0.f, 0.f};
-        for (int q0 = 0; q0 < NK; q0 += qc) {
-          const int nq = min(qc, NK - q0);
-          __syncthreads();  // gyl is staged; the previous steps have read Z
-          {
-            // Z rows of this pass: group grp walks its schedule entries, each
-            // of its four threads takes the channel quads sub, sub + 4, ..
-            const int ch = q0 / qc, off = goc[2 * ch], ck = goc[2 * ch + 1];
-            for (int cq = sub; cq < dq && grp < kGeomGroups; cq += 4) {
-              float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-              for (int k = 0; k < ck; ++k) {
-                const int x = off + k * kGeomGroups + grp;
-                const int m = STAGED ? smeta[x] : gmeta[x];
-                const float cf = STAGED ? sunit[x] : gunit[x] * t.w_f[(m >> 18) & 511];
-                const float4 g = *(const float4*)(gyl + (m & 63) * dh + 4 * cq);
-                v.x += cf * g.x, v.y += cf * g.y, v.z += cf * g.z, v.w += cf * g.w;
-                if (m < 0) {
-                  *(float4*)(Z + ((m >> 6) & 63) * ZS + ((m >> 12) & 63) * dh + 4 * cq) = v;
-                  v = make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-              }
-            }
-          }
-          __syncthreads();
-          // three-stage pipeline: the features of steps st+1, st+2 load while
-          // the MFMAs of st run
-          const int nkap = nq * dh, nst = (nkap + 15) / 16;
-          // each stage holds both operands of a step (A from LDS, B from the
-          // senders' features), so no wait precedes the MFMAs
-          // branch-free: clamped addresses, zeros selected after the loads
-          auto loadb = [&](int st, float4* a, float4* b) {
-            const int kap = 16 * min(st, nst - 1) + 4 * k4;
-            const bool kok = kap < nkap;
-            const unsigned kc = kok ? kap : 0;  // past the pass: a valid row, A = 0
-            const unsigned q = q0 + kc / (unsigned)dh, c = kc % (unsigned)dh;
-#pragma unroll
-            for (int et = 0; et < NTE; ++et)
-              b[et] = *(const float4*)(feat + ((size_t)jn[et] * NK + q) * C + h * dh + c);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-              const int be = mt * 16 + l16;
-              const float4 z = *(const float4*)(Z + (be < NK ? be : 0) * ZS + kc);
-              a[mt] = (be < NK && kok) ? z : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-          };
-          auto mma = [&](const float4* a, const float4* b) {
-#pragma unroll
-            for (int et = 0; et < NTE; ++et) {
-              if (!tlive[et]) continue;  // scalar: uniform over the wave
-#pragma unroll
-              for (int mt = 0; mt < MT; ++mt) {
-                X[et][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt].x, b[et].x, X[et][mt], 0, 0, 0);
-                X[et][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt].y, b[et].y, X[et][mt], 0, 0, 0);
-                X[et][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt].z, b[et].z, X[et][mt], 0, 0, 0);
-                X[et][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt].w, b[et].w, X[et][mt], 0, 0, 0);
-              }
-            }
-          };
-          float4 aA[MT], aB[MT], aC[MT], bA[NTE], bB[NTE], bC[NTE];
-          loadb(0, aA, bA);
-          loadb(1, aB, bB);
-          for (int st = 0; st < nst; st += 3) {
-            loadb(st + 2, aC, bC);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(aA, bA);
-            __builtin_amdgcn_sched_barrier(0);
-            loadb(st + 3, aA, bA);
-            __builtin_amdgcn_sched_barrier(0);
-            if (st + 1 < nst) mma(aB, bB);
-            __builtin_amdgcn_sched_barrier(0);
-            loadb(st + 4, aB, bB);
-            __builtin_amdgcn_sched_barrier(0);
-            if (st + 2 < nst) mma(aC, bC);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-        // lane (k4, l16) holds X_h[be = mt*16 + 4 k4 + v][edge column l16]
-#pragma unroll
-        for (int et = 0; et < NTE; ++et) {
-          if (wave + NW * et >= ntiles) continue;  // uniform over the wave
-          const int64_t e = c0 + (wave + NW * et) * 16 + l16;
-          if (WA) {
-            float p = 0.0f;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) p += Rv[et][mt][v] * X[et][mt][v];
-            p += __shfl_xor(p, 16);
-            p += __shfl_xor(p, 32);
-            if (k4 == 0 && ev[et]) galpha[e * H + h] = p;
-          }
-          if (WP) {
-            const float aw = (alpha && ev[et]) ? alpha[e * H + h] : 1.0f;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) W[et][mt] += aw * X[et][mt];
-          }
-        }
-      }
-      if (WP) {
-#pragma unroll
-        for (int et = 0; et < NTE; ++et) {
-          if (wave + NW * et >= ntiles) continue;  // uniform over the wave
-          float fx = 0.f, fy = 0.f, fz = 0.f;
-          if (GT) {
-            // the gradients from the per-edge table [3][NK][E] (consecutive
-            // lanes l16 read consecutive edges)
-            const int64_t ec = c0 + (ev[et] ? (wave + NW * et) * 16 + l16 : 0);
-            const size_t plane = (size_t)NK * n_edges;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) {
-                const int be = mt * 16 + 4 * k4 + v;
-                if (be < NK) {
-                  const float* gp = Gt + (size_t)be * n_edges + ec;
-                  const float w = W[et][mt][v];
-                  fx += gp[0] * w, fy += gp[plane] * w, fz += gp[2 * plane] * w;
-                }
-              }
-          } else {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) {
-                const int be = mt * 16 + 4 * k4 + v;
-                if (be < NK) {
-                  float gx, gyy, gz;
-                  sh_poly_grad<float>(t, be, dx[et], dy[et], dz[et], gx, gyy, gz);
-                  fx += gx * W[et][mt][v], fy += gyy * W[et][mt][v], fz += gz * W[et][mt][v];
-                }
-              }
-          }
-          fx += __shfl_xor(fx, 16), fy += __shfl_xor(fy, 16), fz += __shfl_xor(fz, 16);
-          fx += __shfl_xor(fx, 32), fy += __shfl_xor(fy, 32), fz += __shfl_xor(fz, 32);
-          if (k4 == 0 && ev[et]) {
-            const int64_t e = c0 + (wave + NW * et) * 16 + l16;
-            gedge[e * 3] = fx, gedge[e * 3 + 1] = fy, gedge[e * 3 + 2] = fz;
-          }
-        }
-      }
-    }
-  }
-}
-
-// Per atom a: the forces of the edges it receives minus those it sends,
-// each in ascending order (the sent edges through the transposed graph).
-__global__ void k_force_gather(const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ rowT,
-                               const int32_t* __restrict__ perm, const float* __restrict__ gedge, int n,
-                               float* __restrict__ gpos) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (int64_t)n * 3) return;
-  const int a = (int)(q / 3), x = (int)(q % 3);
-  float s = 0.0f;
-  for (int64_t e = row_ptr[a]; e < row_ptr[a + 1]; ++e) s += gedge[e * 3 + x];
-  for (int64_t t = rowT[a]; t < rowT[a + 1]; ++t) s -= gedge[(int64_t)perm[t] * 3 + x];
-  gpos[q] = s;
-}
-
-// transposed graph: rows[e] = receiver of edge e; counts of every sender
 __global__ void k_edge_rows(const int64_t* __restrict__ row_ptr, int n, int32_t* __restrict__ rows) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -1927,87 +1648,6 @@ hipError_t launch_iota(int n, int32_t* v, hipStream_t s) {
   k_iota<<<(n + 255) / 256, 256, 0, s>>>(n, v);
   return hipGetLastError();
 }
-
-bool edge_geom_supported(int C, int H) {
-  return C % H == 0 && (C / H) % 4 == 0 && C <= 256;
-}
-
-size_t edge_geom_lds(int L, int dh, int qc, int gtot) {
-  const size_t nk = (size_t)(L + 1) * (L + 1);
-  const size_t zs = (size_t)qc * dh + (((qc * dh) >> 2) & 1 ? 8 : 4);
-  return sizeof(float) * (nk * dh + (L <= 4 ? 2 * (size_t)gtot : 0) + nk * zs);
-}
-
-hipError_t launch_edge_geom(const DevTables& t, const float* pos, const float* feat, const float* gy,
-                            const int64_t* row_ptr, const int32_t* col_idx, const float* alpha, int n, int C, int H,
-                            int qc, const int* gmeta, const float* gunit, const int* goc, int gtot, const float* Gt,
-                            int64_t n_edges, float* galpha, float* gedge, hipStream_t s) {
-  if (n == 0 || (!galpha && !gedge)) return hipSuccess;
-  if (!edge_geom_supported(C, H) || qc < 1 || qc > t.nk) return hipErrorInvalidValue;
-  const int dh = C / H;
-  const size_t lds = edge_geom_lds(t.L, dh, qc, gtot);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  const int mode = (galpha ? 1 : 0) + (gedge ? 2 : 0);
-  int rpw = 4;
-  if (const char* v = getenv("E2F_GEOM_RPW")) rpw = std::max(1, atoi(v));
-  const int nxr = (n + 7) / 8;
-  const unsigned grid = 8u * (unsigned)((nxr + rpw - 1) / rpw);
-  const int geom_threads = 256;  // four waves of two edge tiles (the schedule's 128 threads build Z)
-  switch (t.L * 8 + mode + (Gt && gedge ? 4 : 0)) {
-#define E2F_G(LL, WA_, WP_, GT_)                                                                              \
-  case LL * 8 + (WA_ ? 1 : 0) + (WP_ ? 2 : 0) + (GT_ ? 4 : 0):                                                \
-    if (hipError_t e = allow_lds(k_edge_geom<LL, 2, WA_, WP_, GT_>, lds); e != hipSuccess) return e;          \
-    k_edge_geom<LL, 2, WA_, WP_, GT_><<<grid, geom_threads, lds, s>>>(t, pos, feat, gy, row_ptr, col_idx,      \
-                                                                         alpha, n, rpw, C, H, qc, gmeta,     \
-                                                                         gunit, goc, gtot, Gt, n_edges,      \
-                                                                         galpha, gedge);                     \
-    break;
-#define E2F_GL(LL)                                                                                            \
-  E2F_G(LL, true, false, false) E2F_G(LL, false, true, false) E2F_G(LL, true, true, false)                    \
-  E2F_G(LL, false, true, true) E2F_G(LL, true, true, true)
-    E2F_GL(0) E2F_GL(1) E2F_GL(2) E2F_GL(3) E2F_GL(4) E2F_GL(5) E2F_GL(6)
-#undef E2F_GL
-#undef E2F_G
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-// Gradients of the solid harmonics of every edge, r_e = r_i - r_j:
-// Gt[c][be][e] = dR_be/dr_c (c = x, y, z) for be < nk.  Component-major:
-// blockIdx.y = be, so a wave evaluates one polynomial (no divergence, its
-// table reads uniform) and stores consecutive edges.
-__global__ void k_edge_shgrad(DevTables t, const float* __restrict__ pos, const int32_t* __restrict__ rows,
-                              const int32_t* __restrict__ col, int64_t n_edges, float* __restrict__ Gt) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int be = blockIdx.y;
-  if (e >= n_edges) return;
-  const int i = rows[e], j = col[e];
-  float gx, gyy, gz;
-  sh_poly_grad<float>(t, be, pos[3 * i] - pos[3 * j], pos[3 * i + 1] - pos[3 * j + 1], pos[3 * i + 2] - pos[3 * j + 2],
-                      gx, gyy, gz);
-  const size_t plane = (size_t)t.nk * n_edges, x = (size_t)be * n_edges + e;
-  Gt[x] = gx;
-  Gt[plane + x] = gyy;
-  Gt[2 * plane + x] = gz;
-}
-
-hipError_t launch_edge_shgrad(const DevTables& t, const float* pos, const int32_t* rows, const int32_t* col,
-                              int64_t n_edges, float* Gt, hipStream_t s) {
-  if (n_edges == 0) return hipSuccess;
-  const int64_t blocks = (n_edges + 255) / 256;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  k_edge_shgrad<<<dim3((unsigned)blocks, (unsigned)t.nk), 256, 0, s>>>(t, pos, rows, col, n_edges, Gt);
-  return hipGetLastError();
-}
-
-hipError_t launch_force_gather(const int64_t* row_ptr, const int64_t* rowT, const int32_t* perm, const float* gedge,
-                               int n, float* gpos, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_force_gather<<<(unsigned)(((int64_t)n * 3 + 255) / 256), 256, 0, s>>>(row_ptr, rowT, perm, gedge, n, gpos);
-  return hipGetLastError();
-}
-
 
 size_t transpose_tmp_bytes(int n, int64_t E) {
   size_t a = 0, b = 0;

@@ -193,20 +193,18 @@ hipError_t launch_attention(const float* pos, const float* q, const float* k, in
 // ---- backward
 // Both per-edge backward products in one pass (either output may be NULL):
 // galpha[e][h] = sum_{c of h} <gy_i[.][c], (K_e h_j)[.][c]> [E][H] and the
-// position gradient per edge gedge [E][3]; needs 4 | C/H and C <= 256.
-// launch_force_gather then sums per atom the edges it receives minus those it
-// sends (rowT, perm: the transposed graph).
-bool edge_geom_supported(int C, int H);
-// LDS bytes of the backward kernel for qc filter rows per pass and a
-// schedule of gtot entries (staged in LDS up to L = 4)
-size_t edge_geom_lds(int L, int dh, int qc, int gtot);
-hipError_t launch_edge_geom(const DevTables& t, const float* pos, const float* feat, const float* gy,
-                            const int64_t* row_ptr, const int32_t* col_idx, const float* alpha, int n, int C, int H,
-                            int qc, const int* gmeta, const float* gunit, const int* goc, int gtot, const float* Gt,
-                            int64_t n_edges, float* galpha, float* gedge, hipStream_t s);
-// Gt [3][nk][E]: the harmonic gradients of every edge (rows: the receiver of
-// each edge), read by launch_edge_geom when not NULL
-hipError_t launch_edge_shgrad(const DevTables& t, const float* pos, const int32_t* rows, const int32_t* col,
+// position gradient per edge gedge [E][3]; coef: grad_table, Re [E][nk]:
+// launch_edge_sh (read for galpha); gpart [H][E][3]: scratch of gedge when H >
+// 1; order: the receivers, or NULL (by index).  launch_force_gather then sums per atom
+// the edges it receives minus those it sends (rowT, perm: the transposed
+// graph).
+hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* Re, const float* Gt, const float* feat,
+                            const float* gy, const int64_t* row_ptr, const int32_t* col, const float* alpha,
+                            const int32_t* order, int n, int C, int H, int64_t n_edges, const float* coef,
+                            float* galpha, float* gpart, float* gedge, hipStream_t s);
+// Gt [E][3][nk]: the harmonic gradients of every edge (rows: the receiver of
+// each edge); launch_edge_grad evaluates them itself when given NULL
+hipError_t launch_edge_shgrad(const DevTables& t, const float* pos, const int32_t* rows, const int32_t* col, int n,
                               int64_t n_edges, float* Gt, hipStream_t s);
 hipError_t launch_force_gather(const int64_t* row_ptr, const int64_t* rowT, const int32_t* perm, const float* gedge,
                                int n, float* gpos, hipStream_t s);

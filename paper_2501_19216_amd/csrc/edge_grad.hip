@@ -1,0 +1,428 @@
+// The per-edge products of the backward: the gradients of the attention
+// weights and of the positions.  The message of edge e = (i, j) is linear in
+// the harmonics of r_i - r_j, so with the receiver's output gradient gy_i
+//   X_h[e][be] = sum_{q, c of head h} Z_i[q][c][be] h_j[q][c],
+//   Z_i[q][c][be] = sum_o gy_i[o][c] K[o][be][q],
+//   galpha[e][h] = sum_be R_be(r_e) X_h[e][be],
+//   gedge[e][x]  = sum_be dR_be/dx(r_e) sum_h alpha_eh X_h[e][be].
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "agg_layout.h"
+#include "e2f_launch.h"
+
+namespace e2f {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Gradient of one solid harmonic from its monomials: d/dx of c x^a y^b z^e
+// is c a x^(a-1) y^b z^e (no term when a = 0).
+template <typename F>
+__device__ __forceinline__ void sh_poly_grad(const DevTables& t, int k, F x, F y, F z, F& gx, F& gy, F& gz) {
+  // per monomial one power loop per coordinate: b^(n-1) (1 for n = 0, where
+  // the derivative's factor n is 0), then b^n = b^(n-1) b selected without a
+  // branch
+  auto pm1 = [](F b, int n) {
+    F r = 1;
+    for (int q = 1; q < n; ++q) r *= b;
+    return r;
+  };
+  gx = 0, gy = 0, gz = 0;
+  for (int e = t.sh_ptr[k]; e < t.sh_ptr[k + 1]; ++e) {
+    const int pw = t.sh_pow[e];
+    const int ex = pw & 15, ey = (pw >> 4) & 15, ez = (pw >> 8) & 15;
+    const F c = (F)t.sh_coef[e];
+    const F xm = pm1(x, ex), ym = pm1(y, ey), zm = pm1(z, ez);
+    const F X = ex > 0 ? xm * x : (F)1, Y = ey > 0 ? ym * y : (F)1, Z = ez > 0 ? zm * z : (F)1;
+    gx += c * (F)ex * xm * Y * Z;
+    gy += c * (F)ey * X * ym * Z;
+    gz += c * (F)ez * X * Y * zm;
+  }
+}
+
+// Sum over the 16 lanes of a lane group (rotations within a row of 16 lanes).
+__device__ __forceinline__ float sum16(float v) {
+#define E2F_ROR(n) \
+  __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 | n, 0xf, 0xf, true))
+  v += E2F_ROR(8);
+  v += E2F_ROR(4);
+  v += E2F_ROR(2);
+  v += E2F_ROR(1);
+#undef E2F_ROR
+  return v;
+}
+
+// Row tiles of 16 edges a wave holds at a time: X takes 4 registers per tile
+// and key, the features of two steps eight per tile.
+constexpr int grad_tiles(int L) { return L <= 4 ? 6 : 3; }
+constexpr int kGradWaves = 4;
+
+// A wave takes one head of one receiver at a time.  Both products run on
+// v_mfma_f32_16x16x4f32 and the first feeds the second from its accumulators:
+// for a component q
+//   Z^T[(p, c)][be] = sum_o gy^T[(p, c)][o] K_q[o][be]
+// comes out with column be = l16 and rows 4 k4 + v, which is the B operand of
+// step v of X[e][be] += sum_{(p, c)} h[e][(p, c)] Z^T[(p, c)][be] when step v
+// takes the slots 4 k4 + v; its A operand is then component v of one float4 of
+// the sender's features.  The 16 slots (p, c) are P components q (of one key)
+// of DH = 16 / P channels.  Columns be are the components of one key at a time
+// (agg_layout.h): the outputs o of key x reach, through q of key y, be of key
+// x ^ y alone, four of them a step.  K_q[o][be] comes from a table (element
+// ((q NG + g) 64 + lane): o = member k4 of group g, be = member l16 of key
+// gkey[g] ^ key(q)), in LDS where it fits (LT).
+//
+// As in the fused aggregation an XCD takes a contiguous range of items (a set
+// of receivers and a head, the heads of one 128-byte line first), so that the
+// lines its waves gather stay in its L2; gedge is therefore written per head
+// ([H][E][3]) and summed over the heads by k_edge_sum.
+// T: grad_tiles, or 2 for graphs of short rows (more waves share a SIMD).
+template <int L, int P, bool LT, int T>
+__global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu(T > 2 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
+void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __restrict__ Re,
+                 const float* __restrict__ Gt, const float* __restrict__ feat, const float* __restrict__ gy,
+                 const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+                 const float* __restrict__ alpha, const int32_t* __restrict__ order, int n, int rpw, int nset, int lg,
+                 int per_xcd, int C, int H, int64_t n_edges, const float* __restrict__ coef,
+                 float* __restrict__ galpha, float* __restrict__ gedge) {
+  constexpr AggMap M = agg_map(L, 1);
+  constexpr int NK = M.nk, NG = M.ng, KEYS = M.keys, DH = 16 / P;
+  extern __shared__ float sm[];
+  const float* tab = LT ? sm : coef;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, k4 = lane >> 4;
+  const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int h = item / (nset * lg) * lg + item % lg, set = item / lg % nset;
+  if (h >= H) return;
+  if constexpr (LT) {
+    constexpr int NV = NK * NG * 16, IT = (NV + 64 * kGradWaves - 1) / (64 * kGradWaves);
+    float4 v[IT];  // every load in flight before the first store
+#pragma unroll
+    for (int x = 0; x < IT; ++x) v[x] = ((const float4*)coef)[min((int)threadIdx.x + x * 64 * kGradWaves, NV - 1)];
+#pragma unroll
+    for (int x = 0; x < IT; ++x)
+      if ((int)threadIdx.x + x * 64 * kGradWaves < NV) ((float4*)sm)[threadIdx.x + x * 64 * kGradWaves] = v[x];
+    __syncthreads();
+  }
+  // the lane's component o of every group, its column be of every key (-1: none)
+  int go[NG], cb[KEYS];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    int o = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o = k4 == k && M.gbe[g][k] > 0 ? M.gbe[g][k] : o;
+    go[g] = o;  // (a missing one: component 0, its table entries are zero)
+  }
+#pragma unroll
+  for (int x = 0; x < KEYS; ++x) {
+    cb[x] = -1;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) cb[x] = l16 == k ? M.rows[x][k] : cb[x];
+  }
+  const int dh = C / H, uph = dh / DH;
+  const int pl = 4 * k4 / DH, cl = 4 * k4 % DH;  // the lane's slots 4 k4 .. + 3: component pl, channels cl ..
+  // bounds of a receiver (clamped to [0, E]; E < 2^31), loaded while the one
+  // before is worked on
+  auto receiver = [&](int k, int& i, int64_t& b0, int64_t& b1) {
+    const int at = min((set * rpw + min(k, rpw - 1)) * kGradWaves + wave, n - 1);
+    i = order ? order[at] : at;
+    b0 = row_ptr[i], b1 = row_ptr[i + 1];
+  };
+  int in;
+  int64_t b0, b1;
+  receiver(0, in, b0, b1);
+  for (int k = 0; k < rpw; ++k) {
+    if ((set * rpw + k) * kGradWaves + wave >= n) return;
+    const int i = __builtin_amdgcn_readfirstlane(in);
+    const int e0 = __builtin_amdgcn_readfirstlane((int)max((int64_t)0, min(b0, n_edges)));
+    const int e1 = __builtin_amdgcn_readfirstlane((int)max((int64_t)e0, min(b1, n_edges)));
+    receiver(k + 1, in, b0, b1);
+    const float* gyi = gy + (size_t)i * NK * C;
+    const int all = (e1 - e0 + 15) / 16;
+    const int chunks = (all + T - 1) / T, per = chunks ? (all + chunks - 1) / chunks : 0;
+    for (int ch = 0; ch < chunks; ++ch) {
+      const int64_t c0 = e0 + ch * per * 16;
+      const int nt = min(per, all - ch * per);
+      const int cnt = (int)(e1 - c0);  // edges from here to the row's end
+      const float* fj[T];
+#pragma unroll
+      for (int u = 0; u < T; ++u) {
+        const int j = (col + c0)[(unsigned)min(16 * u + l16, cnt - 1)];
+        fj[u] = feat + (size_t)((unsigned)j < (unsigned)n ? j : 0) * NK * C + cl;
+      }
+      v4f X[T][KEYS];
+#pragma unroll
+      for (int u = 0; u < T; ++u)
+#pragma unroll
+        for (int x = 0; x < KEYS; ++x) X[u][x] = (v4f){0.f, 0.f, 0.f, 0.f};
+      for (int un = 0; un < uph; ++un) {
+        const int hc = h * dh + un * DH;
+        float ga[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) ga[g] = gyi[(size_t)go[g] * C + hc + l16 % DH];
+        // (waited for here: loads return in order, and a wait inside the loop
+        // would be one for the features of its next step)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) asm volatile("" : "+v"(ga[g]));
+#pragma unroll
+        for (int y = 0; y < KEYS; ++y) {
+          // members of key y, P at a time
+          int ny = 0;
+#pragma unroll
+          for (int z = 0; z < 16; ++z) ny += M.rows[y][z] >= 0 ? 1 : 0;
+          const int steps = (ny + P - 1) / P;
+          auto member = [&](int z) {  // component z of key y (uniform or per lane)
+            int q = M.rows[y][0];
+#pragma unroll
+            for (int m = 1; m < 16; ++m)
+              if (M.rows[y][m] >= 0) q = z == m ? M.rows[y][m] : q;
+            return q;
+          };
+          // unconditional loads (a tile past nt repeats the row's last sender),
+          // two register sets in turn: the waits then count exactly
+          float4 fa[T], fb[T];
+          auto load = [&](int s, float4* d) {
+            const int q = member(min(s * P + pl, ny - 1));
+            const unsigned off = (unsigned)(q * C + hc);
+#pragma unroll
+            for (int u = 0; u < T; ++u) d[u] = *(const float4*)(fj[u] + off);
+          };
+          auto step = [&](int s, const float4* f) {
+            v4f z[KEYS];
+#pragma unroll
+            for (int x = 0; x < KEYS; ++x) z[x] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll(P == 4 && L >= 5 ? 1 : P)
+            for (int p = 0; p < P; ++p) {
+              if (s * P + p >= ny) break;
+              const float* kq = tab + (size_t)member(s * P + p) * NG * 64 + lane;
+#pragma unroll
+              for (int g = 0; g < NG; ++g) {
+                const float a = P == 1 || l16 / DH == p ? ga[g] : 0.0f;
+                z[M.gkey[g]] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, kq[g * 64], z[M.gkey[g]], 0, 0, 0);
+              }
+            }
+            // (z[x] holds the columns of key x ^ y)
+#pragma unroll
+            for (int u = 0; u < T; ++u)
+              if (u < nt) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                  for (int x = 0; x < KEYS; ++x)
+                    X[u][x ^ y] =
+                        __builtin_amdgcn_mfma_f32_16x16x4f32((&f[u].x)[v], z[x][v], X[u][x ^ y], 0, 0, 0);
+              }
+          };
+          load(0, fa);
+#pragma unroll 1
+          for (int s = 0; s < steps; s += 2) {
+            load(s + 1, fb);  // (past the end: the last component again)
+            step(s, fa);
+            load(s + 2, fa);
+            if (s + 1 < steps) step(s + 1, fb);
+          }
+        }
+      }
+      // lane (l16, k4) holds X of the columns be = cb[x], edges 16 u + 4 k4 + v:
+      // the sums over be for galpha (with R) and gedge (with its gradients)
+      const float* Rc = Re + c0 * NK;
+      const float* Gc = Gt + c0 * 3 * NK;
+      const float* ac = alpha + c0 * H + h;
+      float* gc = gedge + ((size_t)h * n_edges + c0) * 3;
+      // (a pass over the tiles per output: its loads are in flight together)
+      auto edge = [&](int u, int v) { return (unsigned)min(16 * u + 4 * k4 + v, cnt - 1); };
+      if (galpha) {
+        float r[T][4][KEYS];
+#pragma unroll
+        for (int u = 0; u < T; ++u)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int x = 0; x < KEYS; ++x) r[u][v][x] = Rc[edge(u, v) * NK + max(cb[x], 0)];
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+          float p[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            p[v] = 0.0f;
+#pragma unroll
+            for (int x = 0; x < KEYS; ++x) p[v] += cb[x] >= 0 ? r[u][v][x] * X[u][x][v] : 0.0f;
+            p[v] = sum16(p[v]);
+          }
+          const int e = 16 * u + 4 * k4 + l16;
+          const float a = l16 == 0 ? p[0] : l16 == 1 ? p[1] : l16 == 2 ? p[2] : p[3];
+          if (l16 < 4 && e < cnt && u < nt) galpha[(c0 + e) * H + h] = a;
+        }
+      }
+      if (gedge) {
+        if (alpha) {
+#pragma unroll
+          for (int u = 0; u < T; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const float w = ac[edge(u, v) * H];
+#pragma unroll
+              for (int x = 0; x < KEYS; ++x) X[u][x][v] *= w;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          float g[T][4][KEYS];
+#pragma unroll
+          for (int u = 0; u < T; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+              for (int x = 0; x < KEYS; ++x) {
+                const unsigned e = edge(u, v);
+                const int be = max(cb[x], 0);
+                if (Gt) {
+                  g[u][v][x] = Gc[(e * 3 + d) * NK + be];
+                } else {
+                  const int j = (col + c0)[e], jc = (unsigned)j < (unsigned)n ? j : 0;
+                  float dx, dy, dz;
+                  sh_poly_grad<float>(t, be, pos[3 * i] - pos[3 * jc], pos[3 * i + 1] - pos[3 * jc + 1],
+                                      pos[3 * i + 2] - pos[3 * jc + 2], dx, dy, dz);
+                  g[u][v][x] = d == 0 ? dx : d == 1 ? dy : dz;
+                }
+              }
+#pragma unroll
+          for (int u = 0; u < T; ++u) {
+            float p[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              p[v] = 0.0f;
+#pragma unroll
+              for (int x = 0; x < KEYS; ++x) p[v] += cb[x] >= 0 ? g[u][v][x] * X[u][x][v] : 0.0f;
+              p[v] = sum16(p[v]);
+            }
+            const int e = 16 * u + 4 * k4 + l16;
+            const float a = l16 == 0 ? p[0] : l16 == 1 ? p[1] : l16 == 2 ? p[2] : p[3];
+            if (l16 < 4 && e < cnt && u < nt) gc[(unsigned)(3 * e + d)] = a;
+          }
+        }
+      }
+    }
+  }
+}
+
+// gedge = the sum of the heads' parts, in order.
+__global__ __launch_bounds__(256) void k_edge_sum(const float* __restrict__ part, int H, int64_t count,
+                                                  float* __restrict__ gedge) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (q >= count) return;
+  float s = 0.0f;
+  for (int h = 0; h < H; ++h) s += part[h * count + q];
+  gedge[q] = s;
+}
+
+// Gradients of the harmonics of every edge, Gt [E][3][NK]: 64 edges a
+// workgroup, rows through LDS (odd stride) so that they leave contiguously.
+__global__ __launch_bounds__(256) void k_edge_shgrad(DevTables t, const float* __restrict__ pos,
+                                                     const int32_t* __restrict__ rows,
+                                                     const int32_t* __restrict__ col, int n, int64_t n_edges,
+                                                     float* __restrict__ Gt) {
+  extern __shared__ float sm[];
+  const int nk = t.nk, ld = 3 * nk | 1, lane = threadIdx.x & 63;
+  const int64_t e0 = (int64_t)blockIdx.x * 64, e = e0 + lane;
+  const int cnt = (int)min((int64_t)64, n_edges - e0);
+  if (lane < cnt) {
+    const int i = rows[e], j = col[e], jc = (unsigned)j < (unsigned)n ? j : 0;
+    const float x = pos[3 * i] - pos[3 * jc], y = pos[3 * i + 1] - pos[3 * jc + 1], z = pos[3 * i + 2] - pos[3 * jc + 2];
+    for (int be = threadIdx.x >> 6; be < nk; be += 4) {
+      float g[3];
+      sh_poly_grad<float>(t, be, x, y, z, g[0], g[1], g[2]);
+      for (int d = 0; d < 3; ++d) sm[lane * ld + d * nk + be] = g[d];
+    }
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < cnt * 3 * nk; q += 256) Gt[e0 * 3 * nk + q] = sm[q / (3 * nk) * ld + q % (3 * nk)];
+}
+
+// Per atom: the forces of the edges it receives minus those it sends (through
+// the transposed graph).  A wave per atom, its lanes over the edges, summed in
+// a fixed order.
+__global__ __launch_bounds__(256) void k_force_gather(const int64_t* __restrict__ row_ptr,
+                                                      const int64_t* __restrict__ rowT,
+                                                      const int32_t* __restrict__ perm,
+                                                      const float* __restrict__ gedge, int n,
+                                                      float* __restrict__ gpos) {
+  const int a = blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (a >= n) return;  // uniform over the wave
+  float s[3] = {0.f, 0.f, 0.f};
+  for (int64_t e = row_ptr[a] + lane; e < row_ptr[a + 1]; e += 64)
+    for (int x = 0; x < 3; ++x) s[x] += gedge[e * 3 + x];
+  for (int64_t q = rowT[a] + lane; q < rowT[a + 1]; q += 64)
+    for (int x = 0; x < 3; ++x) s[x] -= gedge[(int64_t)perm[q] * 3 + x];
+  for (int o = 32; o > 0; o >>= 1)
+    for (int x = 0; x < 3; ++x) s[x] += __shfl_xor(s[x], o);
+  if (lane < 3) gpos[(int64_t)a * 3 + lane] = lane == 0 ? s[0] : lane == 1 ? s[1] : s[2];
+}
+
+}  // namespace
+
+hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* Re, const float* Gt, const float* feat,
+                            const float* gy, const int64_t* row_ptr, const int32_t* col, const float* alpha,
+                            const int32_t* order, int n, int C, int H, int64_t n_edges, const float* coef,
+                            float* galpha, float* gpart, float* gedge, hipStream_t s) {
+  if (n == 0 || n_edges == 0 || (!galpha && !gedge)) return hipSuccess;
+  const int P = 16 / agg_group(C, H), dh = C / H;
+  int lg = std::max(1, std::min(32 / dh, H));  // heads of one 128-byte line
+  while (H % lg) --lg;
+  float* out = gedge && H > 1 ? gpart : gedge;
+#define E2F_G(LL, PP, LT, TT)                                                                                     \
+  do {                                                                                                            \
+    constexpr AggMap M = agg_map(LL, 1);                                                                          \
+    /* receivers a wave: up to eight, as long as every CU has work (they share the table) */                      \
+    const int rpw = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)n * H / (256 * 16)));                 \
+    const int nset = (n + kGradWaves * rpw - 1) / (kGradWaves * rpw);                                             \
+    const int64_t per = ((int64_t)nset * H + 7) / 8;                                                              \
+    if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                        \
+    k_edge_grad<LL, PP, LT, TT><<<(unsigned)(8 * per), 64 * kGradWaves, LT ? M.nk * M.ng * 256 : 0, s>>>(         \
+        t, pos, Re, Gt, feat, gy, row_ptr, col, alpha, order, n, rpw, nset, lg, (int)per, C, H, n_edges, coef,    \
+        galpha, out);                                                                                             \
+  } while (0)
+#define E2F_GP(LL, LT, TT)                    \
+  do {                                        \
+    if (P == 1) E2F_G(LL, 1, LT, TT);         \
+    else if (P == 2) E2F_G(LL, 2, LT, TT);    \
+    else E2F_G(LL, 4, LT, TT);                \
+  } while (0)
+#define E2F_GL(LL, LT)                                         \
+  case LL:                                                     \
+    if (n_edges <= (int64_t)n * 24) E2F_GP(LL, LT, 2);         \
+    else E2F_GP(LL, LT, grad_tiles(LL));                       \
+    break;
+  switch (t.L) {
+    E2F_GL(0, false) E2F_GL(1, false) E2F_GL(2, true) E2F_GL(3, true) E2F_GL(4, true) E2F_GL(5, false)
+    E2F_GL(6, false)
+    default: return hipErrorInvalidValue;
+  }
+#undef E2F_GL
+#undef E2F_GP
+#undef E2F_G
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || out == gedge) return e;
+  const int64_t blocks = (n_edges * 3 + 255) / 256;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  k_edge_sum<<<(unsigned)blocks, 256, 0, s>>>(gpart, H, n_edges * 3, gedge);
+  return hipGetLastError();
+}
+
+hipError_t launch_edge_shgrad(const DevTables& t, const float* pos, const int32_t* rows, const int32_t* col, int n,
+                              int64_t n_edges, float* Gt, hipStream_t s) {
+  if (n_edges == 0) return hipSuccess;
+  const int64_t blocks = (n_edges + 63) / 64;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  k_edge_shgrad<<<(unsigned)blocks, 256, sizeof(float) * 64 * (3 * t.nk | 1), s>>>(t, pos, rows, col, n, n_edges, Gt);
+  return hipGetLastError();
+}
+
+hipError_t launch_force_gather(const int64_t* row_ptr, const int64_t* rowT, const int32_t* perm, const float* gedge,
+                               int n, float* gpos, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  k_force_gather<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(row_ptr, rowT, perm, gedge, n, gpos);
+  return hipGetLastError();
+}
+
+}  // namespace e2f

@@ -488,61 +488,6 @@ CoupleSchedule couple_schedule(const LayerTables& t, int groups) {
   return cs;
 }
 
-GeomSchedule geom_schedule(const LayerTables& t, int qc) {
-  GeomSchedule gs;
-  const int nk = t.nk, G = kGeomGroups;
-  gs.qc = qc;
-  gs.nchunk = (nk + qc - 1) / qc;
-  // entries (k, unit, path) of each key (be, q), in ascending k
-  struct Ent { int k, path; double unit; };
-  std::vector<std::vector<Ent>> ent((size_t)nk * nk);
-  for (int sidx = 0; sidx < nk * nk; ++sidx)
-    for (int e = t.k_ptr[sidx]; e < t.k_ptr[sidx + 1]; ++e)
-      ent[(size_t)t.k_ridx[e] * nk + sidx % nk].push_back({sidx / nk, t.k_path[e], t.k_unit[e]});
-  for (int ch = 0; ch < gs.nchunk; ++ch) {
-    const int q0 = ch * qc, nq = std::min(qc, nk - q0);
-    std::vector<int> keys;
-    for (int be = 0; be < nk; ++be)
-      for (int qq = 0; qq < nq; ++qq) keys.push_back(be * nk + q0 + qq);
-    auto len = [&](int key) { return std::max<int>(1, (int)ent[key].size()); };
-    std::stable_sort(keys.begin(), keys.end(), [&](int x, int y) { return len(x) > len(y); });
-    std::vector<std::vector<int>> per(G);
-    std::vector<int> load(G, 0);
-    for (int key : keys) {
-      int best = 0;
-      for (int g = 1; g < G; ++g)
-        if (load[g] < load[best]) best = g;
-      per[best].push_back(key);
-      load[best] += len(key);
-    }
-    const int K = *std::max_element(load.begin(), load.end());
-    const size_t base = gs.meta.size();
-    gs.off.push_back((int)base);
-    gs.ck.push_back(K);
-    gs.meta.resize(base + (size_t)K * G, 0);
-    gs.unit.resize(base + (size_t)K * G, 0.0f);
-    for (int g = 0; g < G; ++g) {
-      int k = 0;
-      for (int key : per[g]) {
-        const int be = key / nk, qq = key % nk - q0;
-        const int kb = (be << 6) | (qq << 12);
-        if (ent[key].empty()) {
-          gs.meta[base + (size_t)k * G + g] = kb | (int)0x80000000u;
-          ++k;
-          continue;
-        }
-        for (size_t e = 0; e < ent[key].size(); ++e, ++k) {
-          const bool last = e + 1 == ent[key].size();
-          gs.meta[base + (size_t)k * G + g] =
-              ent[key][e].k | kb | (ent[key][e].path << 18) | (last ? (int)0x80000000u : 0);
-          gs.unit[base + (size_t)k * G + g] = (float)ent[key][e].unit;
-        }
-      }
-    }
-  }
-  return gs;
-}
-
 FuseTable fuse_table(const LayerTables& t, const std::vector<double>& w, const int* degs, int nd, int nkr) {
   const int nk = t.nk;
   FuseTable ft;
@@ -607,12 +552,18 @@ FuseTable fuse_table(const LayerTables& t, const std::vector<double>& w, const i
   return ft;
 }
 
+// K[o][q][be] for the path weights w.
+static std::vector<double> coupling(const LayerTables& t, const std::vector<double>& w) {
+  std::vector<double> K((size_t)t.nk * t.nk * t.nk, 0.0);
+  for (size_t s = 0; s + 1 < t.k_ptr.size(); ++s)
+    for (int e = t.k_ptr[s]; e < t.k_ptr[s + 1]; ++e) K[s * t.nk + t.k_ridx[e]] += t.k_unit[e] * w[t.k_path[e]];
+  return K;
+}
+
 AggTables agg_tables(const LayerTables& t, const std::vector<double>& w, int P) {
   const AggMap a = agg_map(t.L, P);
   const int nk = t.nk, nq = (a.ng * a.rb + 3) / 4;
-  std::vector<double> K((size_t)nk * nk * nk, 0.0);  // [o][q][be]
-  for (size_t s = 0; s + 1 < t.k_ptr.size(); ++s)
-    for (int e = t.k_ptr[s]; e < t.k_ptr[s + 1]; ++e) K[s * nk + t.k_ridx[e]] += t.k_unit[e] * w[t.k_path[e]];
+  const std::vector<double> K = coupling(t, w);
   AggTables r;
   for (int be = 0; be < nk; ++be) r.index.push_back(a.pos[be]);
   for (int v = 0; v < a.nw; ++v)
@@ -634,6 +585,20 @@ AggTables agg_tables(const LayerTables& t, const std::vector<double>& w, int P) 
           r.coef[((size_t)((v * a.tw + i) * nq + m / 4) * 64 + lane) * 4 + m % 4] =
               (float)K[((size_t)o * nk + q) * nk + be];
         }
+  return r;
+}
+
+std::vector<float> grad_table(const LayerTables& t, const std::vector<double>& w) {
+  const AggMap a = agg_map(t.L, 1);
+  const int nk = t.nk;
+  const std::vector<double> K = coupling(t, w);
+  std::vector<float> r((size_t)nk * a.ng * 64, 0.0f);
+  for (int q = 0; q < nk; ++q)
+    for (int g = 0; g < a.ng; ++g)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int o = a.gbe[g][lane / 16], be = a.rows[a.gkey[g] ^ a.kkey[q]][lane % 16];
+        if (o >= 0 && be >= 0) r[((size_t)q * a.ng + g) * 64 + lane] = (float)K[((size_t)o * nk + q) * nk + be];
+      }
   return r;
 }
 

@@ -50,6 +50,25 @@ int main() {
             fdiff = std::max(fdiff, std::fabs((f & 1 ? -v : v) - K[((size_t)k * nk + q) * nk + be]));
           }
     }
+    // the backward's table holds every K[o][be][q] once, and nothing else
+    {
+      const AggMap a = agg_map(L, 1);
+      const std::vector<float> tab = grad_table(t, w);
+      std::vector<double> left(K);
+      bool fits = tab.size() == (size_t)nk * a.ng * 64;
+      for (int q = 0; q < nk && fits; ++q)
+        for (int e = 0; e < a.ng * 64; ++e) {
+          const int g = e / 64, o = a.gbe[g][e % 64 / 16], be = a.rows[a.gkey[g] ^ a.kkey[q]][e % 16];
+          const double v = tab[(size_t)q * a.ng * 64 + e];
+          if (o < 0 || be < 0) fits = fits && v == 0.0;
+          else left[((size_t)o * nk + q) * nk + be] -= v;
+        }
+      double most = 0.0;
+      for (double v : left) most = std::max(most, std::fabs(v));
+      for (int x = 0; x < a.keys; ++x) fits = fits && a.rows[x][16] < 0;  // a key fits the 16 columns
+      all = all && fits && most < 1e-6;
+      std::printf("L=%d backward table: %s (%.1e left)\n", L, fits && most < 1e-6 ? "ok" : "FAIL", most);
+    }
     for (int P = 1; P <= 4; P *= 2) {
       const AggMap a = agg_map(L, P);
       const AggTables tab = agg_tables(t, w, P);

@@ -22,4 +22,4 @@ def test_agg_tables(tmp_path):
     print(r.stdout)
     lines = [l for l in r.stdout.splitlines() if l.strip()]
     assert r.returncode == 0, r.stdout + r.stderr
-    assert len(lines) == 7 * 3 and all(": ok" in l for l in lines), r.stdout
+    assert len(lines) == 7 * 4 and all(": ok" in l for l in lines), r.stdout
