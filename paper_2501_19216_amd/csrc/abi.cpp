@@ -66,9 +66,8 @@ struct e2f_ctx {
     const double* rc_coef = nullptr;
     std::vector<const double*> rcf_coef;  // per filter degree f
     const float* w_f = nullptr;
-    // fused aggregation, per column group width 16, 8, 4 (P = 1, 2, 4)
-    const int* agg_index[3] = {};
-    const float* agg_coef[3] = {};
+    const int* agg_index = nullptr;  // fused aggregation
+    const float* agg_coef = nullptr;
     const float* grad_coef = nullptr;  // the backward's per-edge products
   };
   std::vector<std::vector<CoefSet>> coefs;
@@ -367,12 +366,10 @@ e2f_status coef_of(e2f_ctx* ctx, int L, const std::vector<double>& w, bool allow
   }
   std::vector<float> wf(w.begin(), w.end());  // o[4 + L]
   push_array(blob, o, wf);
-  for (int P = 1; P <= 4; P *= 2) {  // o[5 + L] .. o[10 + L]
-    const AggTables ag = agg_tables(t, w, P);
-    push_array(blob, o, ag.index);
-    push_array(blob, o, ag.coef);
-  }
-  push_array(blob, o, grad_table(t, w));  // o[11 + L]
+  const AggTables ag = agg_tables(t, w);  // o[5 + L], o[6 + L]
+  push_array(blob, o, ag.index);
+  push_array(blob, o, ag.coef);
+  push_array(blob, o, grad_table(t, w));  // o[7 + L]
   if (sets.size() >= kMaxCoefSets) {  // the oldest set may still be read by queued work
     E2F_HIP(hipDeviceSynchronize());
     E2F_HIP(hipFree(sets.front().mem));
@@ -392,11 +389,9 @@ e2f_status coef_of(e2f_ctx* ctx, int L, const std::vector<double>& w, bool allow
   c.rc_coef = (const double*)((char*)mem + o[2]);
   for (int f = 0; f <= L; ++f) c.rcf_coef.push_back((const double*)((char*)mem + o[3 + f]));
   c.w_f = (const float*)((char*)mem + o[4 + L]);
-  for (int q = 0; q < 3; ++q) {
-    c.agg_index[q] = (const int*)((char*)mem + o[5 + L + 2 * q]);
-    c.agg_coef[q] = (const float*)((char*)mem + o[6 + L + 2 * q]);
-  }
-  c.grad_coef = (const float*)((char*)mem + o[11 + L]);
+  c.agg_index = (const int*)((char*)mem + o[5 + L]);
+  c.agg_coef = (const float*)((char*)mem + o[6 + L]);
+  c.grad_coef = (const float*)((char*)mem + o[7 + L]);
   sets.push_back(std::move(c));
   out = &sets.back();
   return E2F_OK;
@@ -674,12 +669,11 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
                                                ws + f.sort_tmp, f.sort_b, s));
     }
     E2F_TIMED("sh", launch_edge_sh(t, pos, row_ptr, col_idx, n, n_edges, ynorm, Re, s));
-    const int dh = agg_group(C, H), which = dh == 16 ? 0 : dh == 8 ? 1 : 2;
     for (int64_t q0 = 0; q0 < n; q0 += slice, ++slices)
       E2F_TIMED("aggregate", launch_aggregate_fused(L, Re, row_ptr, col_idx, alpha, n_edges, feat,
                                                     n > kPlanSmallMax ? order : nullptr, (int)q0,
                                                     (int)std::min<int64_t>(slice, n - q0), C, H, n,
-                                                    cs->agg_index[which], cs->agg_coef[which], y, s));
+                                                    cs->agg_index, cs->agg_coef, y, s));
     if (p->mix_w) E2F_TIMED("mix", launch_mix(L, y, p->mix_w, p->mix_dtype == E2F_BF16, n, C, out, s));
     ctx->last_slices = slices;
     return E2F_OK;

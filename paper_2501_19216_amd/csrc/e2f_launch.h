@@ -166,8 +166,7 @@ hipError_t launch_outer_agg(const DevTables& t, const float* Re, const int64_t* 
 // The fused aggregation (fused.hip): y[i] whole for the n receivers i =
 // order[first + r], or first + r where order is NULL, from Re
 // (launch_edge_sh), alpha [E][H] or NULL (ones) and feat; index and coef:
-// agg_tables for P = 16 / agg_group(C, H)
-int agg_group(int C, int H);
+// agg_tables
 hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr, const int32_t* col,
                                   const float* alpha, int64_t n_edges, const float* feat, const int32_t* order,
                                   int first, int n, int C, int H, int n_nodes, const int* index, const float* coef,

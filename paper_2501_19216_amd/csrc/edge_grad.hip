@@ -86,7 +86,7 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
                  const float* __restrict__ alpha, const int32_t* __restrict__ order, int n, int rpw, int nset, int lg,
                  int per_xcd, int C, int H, int64_t n_edges, const float* __restrict__ coef,
                  float* __restrict__ galpha, float* __restrict__ gedge) {
-  constexpr AggMap M = agg_map(L, 1);
+  constexpr AggMap M = agg_map(L);
   constexpr int NK = M.nk, NG = M.ng, KEYS = M.keys, DH = 16 / P;
   extern __shared__ float sm[];
   const float* tab = LT ? sm : coef;
@@ -367,13 +367,13 @@ hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* R
                             const int32_t* order, int n, int C, int H, int64_t n_edges, const float* coef,
                             float* galpha, float* gpart, float* gedge, hipStream_t s) {
   if (n == 0 || n_edges == 0 || (!galpha && !gedge)) return hipSuccess;
-  const int P = 16 / agg_group(C, H), dh = C / H;
+  const int dh = C / H, P = dh % 16 == 0 ? 1 : dh % 8 == 0 ? 2 : 4;  // the widest group that divides a head
   int lg = std::max(1, std::min(32 / dh, H));  // heads of one 128-byte line
   while (H % lg) --lg;
   float* out = gedge && H > 1 ? gpart : gedge;
 #define E2F_G(LL, PP, LT, TT)                                                                                     \
   do {                                                                                                            \
-    constexpr AggMap M = agg_map(LL, 1);                                                                          \
+    constexpr AggMap M = agg_map(LL);                                                                          \
     /* receivers a wave: up to eight, as long as every CU has work (they share the table) */                      \
     const int rpw = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)n * H / (256 * 16)));                 \
     const int nset = (n + kGradWaves * rpw - 1) / (kGradWaves * rpw);                                             \

@@ -560,36 +560,31 @@ static std::vector<double> coupling(const LayerTables& t, const std::vector<doub
   return K;
 }
 
-AggTables agg_tables(const LayerTables& t, const std::vector<double>& w, int P) {
-  const AggMap a = agg_map(t.L, P);
-  const int nk = t.nk, nq = (a.ng * a.rb + 3) / 4;
+AggTables agg_tables(const LayerTables& t, const std::vector<double>& w) {
+  const AggMap a = agg_map(t.L);
+  const int nk = t.nk, nq = (a.ng + 3) / 4;
   const std::vector<double> K = coupling(t, w);
   AggTables r;
   for (int be = 0; be < nk; ++be) r.index.push_back(a.pos[be]);
   for (int v = 0; v < a.nw; ++v)
-    for (int i = 0; i < a.tw; ++i)
-      for (int p = 0; p < P; ++p) {
-        const int q = a.slotq[v][i][p];
-        r.index.push_back(q >= 0 ? q : std::max(a.slotq[v][i][0], 0));
-      }
-  for (int k = 0; k < nk; ++k) r.index.push_back(a.kkey[k] * a.rb * a.dh + a.kidx[k]);
+    for (int i = 0; i < a.tw; ++i) r.index.push_back(a.slotq[v][i] >= 0 ? a.slotq[v][i] : a.slotq[v][0]);
+  for (int k = 0; k < nk; ++k) r.index.push_back(a.kkey[k] * 16 + a.kidx[k]);
   r.coef.assign((size_t)a.nw * a.tw * nq * 256, 0.0f);
   for (int v = 0; v < a.nw; ++v)
     for (int i = 0; i < a.tw; ++i)
-      for (int m = 0; m < a.ng * a.rb; ++m)
+      for (int g = 0; g < a.ng; ++g)
         for (int lane = 0; lane < 64; ++lane) {
-          const int g = m / a.rb, row = lane % 16, p = row / a.dh;
-          const int be = a.gbe[g][lane / 16], q = a.slotq[v][i][p];
-          const int o = a.rows[a.gkey[g] ^ a.skey[i] ^ a.wkey[v]][(m % a.rb) * a.dh + row % a.dh];
+          const int be = a.gbe[g][lane / 16], q = a.slotq[v][i];
+          const int o = a.rows[a.gkey[g] ^ a.skey[i] ^ a.wkey[v]][lane % 16];
           if (be < 0 || q < 0 || o < 0) continue;
-          r.coef[((size_t)((v * a.tw + i) * nq + m / 4) * 64 + lane) * 4 + m % 4] =
+          r.coef[((size_t)((v * a.tw + i) * nq + g / 4) * 64 + lane) * 4 + g % 4] =
               (float)K[((size_t)o * nk + q) * nk + be];
         }
   return r;
 }
 
 std::vector<float> grad_table(const LayerTables& t, const std::vector<double>& w) {
-  const AggMap a = agg_map(t.L, 1);
+  const AggMap a = agg_map(t.L);
   const int nk = t.nk;
   const std::vector<double> K = coupling(t, w);
   std::vector<float> r((size_t)nk * a.ng * 64, 0.0f);

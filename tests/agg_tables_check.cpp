@@ -1,11 +1,10 @@
 // Host check of the fused aggregation's layout and tables (built with g++
 // against the library's tables.cpp by test_agg_tables.py; no GPU).  For every
-// L and column group (P components x 16 / P channels a tile) it walks the
-// index and coupling tables as the kernel does, on random G, and compares y
+// L it walks the index and coupling tables as the kernel does, on random G, and compares y
 // with the sum over the real Clebsch-Gordan tensors; every index is checked
 // against its range.  For L <= 4 the coupling is also the composed recouple of
 // the local expansion at p_i = 0 (the x = 0 entries of fuse_table).
-// Prints one line per (L, P), "ok" or "FAIL", and exits 1 on a failure.
+// Prints two lines per L, "ok" or "FAIL", and exits 1 on a failure.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -52,7 +51,7 @@ int main() {
     }
     // the backward's table holds every K[o][be][q] once, and nothing else
     {
-      const AggMap a = agg_map(L, 1);
+      const AggMap a = agg_map(L);
       const std::vector<float> tab = grad_table(t, w);
       std::vector<double> left(K);
       bool fits = tab.size() == (size_t)nk * a.ng * 64;
@@ -69,63 +68,52 @@ int main() {
       all = all && fits && most < 1e-6;
       std::printf("L=%d backward table: %s (%.1e left)\n", L, fits && most < 1e-6 ? "ok" : "FAIL", most);
     }
-    for (int P = 1; P <= 4; P *= 2) {
-      const AggMap a = agg_map(L, P);
-      const AggTables tab = agg_tables(t, w, P);
-      const int dh = 16 / P, nq = (a.ng * a.rb + 3) / 4, nacc = a.keys * a.rb;
-      bool ok = (int)tab.index.size() == agg_index_ints(L, P) && (int)tab.coef.size() == agg_table_floats(L, P) &&
-                nq == agg_quads(L, P) && a.tw <= 32 && a.ng <= 4 * a.mt;
-      std::vector<double> G((size_t)nk * nk * dh), rowG((size_t)16 * a.mt * nk * dh, 0.0);  // [be][q][t], by row
-      for (double& v : G) v = S(g);
-      std::vector<int> used(16 * a.mt, 0), seen(nk, 0);
-      for (int be = 0; be < nk && ok; ++be) {
-        const int pos = tab.index[be];
-        ok = pos >= 0 && pos < 16 * a.mt && used[pos]++ == 0;
-        for (int e = 0; ok && e < nk * dh; ++e) rowG[(size_t)pos * nk * dh + e] = G[(size_t)be * nk * dh + e];
-      }
-      std::vector<double> D((size_t)a.nw * nacc * 256, 0.0);  // [wave][acc][row][column]
-      for (int v = 0; v < a.nw && ok; ++v)
-        for (int i = 0; i < a.tw; ++i) {
-          int q[4];
-          for (int p = 0; p < P; ++p) {
-            q[p] = tab.index[nk + (v * a.tw + i) * P + p];
-            ok = ok && q[p] >= 0 && q[p] < nk;
-            if (a.slotq[v][i][p] >= 0) ok = ok && q[p] == a.slotq[v][i][p] && seen[q[p]]++ == 0;
-          }
-          for (int m = 0; m < a.ng * a.rb && ok; ++m) {
-            const int gr = m / a.rb, acc = (a.gkey[gr] ^ a.skey[i]) * a.rb + m % a.rb;
-            ok = acc >= 0 && acc < nacc;
-            for (int row = 0; row < 16; ++row)
-              for (int col = 0; col < 16; ++col)
-                for (int k = 0; k < 4; ++k)
-                  D[(((size_t)v * nacc + acc) * 16 + row) * 16 + col] +=
-                      (double)tab.coef[((size_t)((v * a.tw + i) * nq + m / 4) * 64 + k * 16 + row) * 4 + m % 4] *
-                      rowG[((size_t)(16 * (gr / 4) + 4 * k + gr % 4) * nk + q[col / dh]) * dh + col % dh];
-          }
-        }
-      for (int k = 0; k < nk; ++k) ok = ok && seen[k] == 1;
-      double err = 0.0, top = 0.0;
-      for (int o = 0; o < nk && ok; ++o) {
-        const int kk = tab.index[nk + a.nw * a.tw * P + o], key = kk / (a.rb * dh), idx = kk % (a.rb * dh);
-        ok = kk >= 0 && key < a.keys && a.rows[key][idx] == o;
-        for (int ch = 0; ch < dh && ok; ++ch) {
-          double got = 0.0, want = 0.0;
-          for (int v = 0; v < a.nw; ++v)
-            for (int p = 0; p < P; ++p)
-              got += D[(((size_t)v * nacc + (key ^ a.wkey[v]) * a.rb + idx / dh) * 16 + p * dh + idx % dh) * 16 +
-                       p * dh + ch];
-          for (int be = 0; be < nk; ++be)
-            for (int q = 0; q < nk; ++q) want += K[((size_t)o * nk + q) * nk + be] * G[((size_t)be * nk + q) * dh + ch];
-          err = std::max(err, std::fabs(got - want));
-          top = std::max(top, std::fabs(want));
-        }
-      }
-      // the table rounds K to float: 2^-24 a term
-      ok = ok && top > 0.0 && err <= 1e-6 * top && fdiff <= 1e-12;
-      std::printf("L=%d P=%d: %s (err %.2e of %.2e, %d slots, %d groups, composed %.1e)\n", L, P, ok ? "ok" : "FAIL",
-                  err, top, a.tw, a.ng, fdiff);
-      all = all && ok;
+    const AggMap a = agg_map(L);
+    const AggTables tab = agg_tables(t, w);
+    const int nq = (a.ng + 3) / 4;
+    bool ok = (int)tab.index.size() == agg_index_ints(L) && (int)tab.coef.size() == agg_table_floats(L) &&
+              nq == agg_quads(L) && a.tw <= 32 && a.ng <= 4 * a.mt;
+    std::vector<double> G((size_t)nk * nk), rowG((size_t)16 * a.mt * nk, 0.0);  // [be][q], by row
+    for (double& v : G) v = S(g);
+    std::vector<int> used(16 * a.mt, 0), seen(nk, 0);
+    for (int be = 0; be < nk && ok; ++be) {
+      const int pos = tab.index[be];
+      ok = pos >= 0 && pos < 16 * a.mt && used[pos]++ == 0;
+      for (int q = 0; ok && q < nk; ++q) rowG[(size_t)pos * nk + q] = G[(size_t)be * nk + q];
     }
+    std::vector<double> D((size_t)a.nw * a.keys * 16, 0.0);  // [wave][key][row]
+    for (int v = 0; v < a.nw && ok; ++v)
+      for (int i = 0; i < a.tw; ++i) {
+        const int q = tab.index[nk + v * a.tw + i];
+        ok = ok && q >= 0 && q < nk;
+        if (a.slotq[v][i] >= 0) ok = ok && q == a.slotq[v][i] && seen[q]++ == 0;
+        for (int gr = 0; gr < a.ng && ok; ++gr) {
+          const int acc = a.gkey[gr] ^ a.skey[i];
+          ok = acc >= 0 && acc < a.keys;
+          for (int row = 0; row < 16; ++row)
+            for (int k = 0; k < 4; ++k)
+              D[((size_t)v * a.keys + acc) * 16 + row] +=
+                  (double)tab.coef[((size_t)((v * a.tw + i) * nq + gr / 4) * 64 + k * 16 + row) * 4 + gr % 4] *
+                  rowG[(size_t)(16 * (gr / 4) + 4 * k + gr % 4) * nk + q];
+        }
+      }
+    for (int k = 0; k < nk; ++k) ok = ok && seen[k] == 1;
+    double err = 0.0, top = 0.0;
+    for (int o = 0; o < nk && ok; ++o) {
+      const int kk = tab.index[nk + a.nw * a.tw + o], key = kk / 16, idx = kk % 16;
+      ok = kk >= 0 && key < a.keys && a.rows[key][idx] == o;
+      double got = 0.0, want = 0.0;
+      for (int v = 0; v < a.nw; ++v) got += D[((size_t)v * a.keys + (key ^ a.wkey[v])) * 16 + idx];
+      for (int be = 0; be < nk; ++be)
+        for (int q = 0; q < nk; ++q) want += K[((size_t)o * nk + q) * nk + be] * G[(size_t)be * nk + q];
+      err = std::max(err, std::fabs(got - want));
+      top = std::max(top, std::fabs(want));
+    }
+    // the table rounds K to float: 2^-24 a term
+    ok = ok && top > 0.0 && err <= 1e-6 * top && fdiff <= 1e-12;
+    std::printf("L=%d: %s (err %.2e of %.2e, %d slots, %d groups, composed %.1e)\n", L, ok ? "ok" : "FAIL", err, top,
+                a.tw, a.ng, fdiff);
+    all = all && ok;
   }
   return all ? 0 : 1;
 }
