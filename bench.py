@@ -86,8 +86,8 @@ def alg_counts(e2f, L, C, H, n, E, fused=False):
     factorised layer's a3 (dimT multiply-adds per edge and channel) plus the
     j-side coupling of every receiver (a2); the recouple (a4); the mixing
     (a5); and the compulsory bytes each kernel moves.  fused: the aggregation
-    applies the recouple itself (a2 + a3 + a4 in one kernel, y written
-    instead of S, and the per-receiver matrix F_i read)."""
+    couples to the output itself (a2 + a3 + a4 in one kernel, y written
+    instead of S)."""
     cnt = layer_counts(L)
     dimT, nk = cnt["dimT"], (L + 1) ** 2
     cpl = coupling_entries(e2f, L)
@@ -95,19 +95,18 @@ def alg_counts(e2f, L, C, H, n, E, fused=False):
     mp = 16 * mt  # components of R per MFMA tile column, padded to 16
     inputs = 4.0 * n * nk * C + 4.0 * E * nk + 4.0 * E * H + 4.0 * E + 8.0 * (n + 1)
     if fused:
-        # issued: the products as split bf16 (one v_mfma_f32_16x16x32_bf16 of
-        # 16384 flops per 4 edges, 16 rows and 16 columns: 8 bf16 products, six
-        # of them used, per fp32 multiply-add), then per receiver and head of
-        # 16 channels one fp32 16x16x4 MFMA per (component q, row tile, K tile,
-        # K step), a K tile of r components taking ceil(r / ceil(r / 4)) steps
-        ksteps = 0
-        for t in range(mt):
-            r = min(16, nk - 16 * t)
-            ksteps += -(-r // -(-r // 4))
+        # issued: from L = 4 on the products as split bf16 (three
+        # v_mfma_f32_16x16x32_bf16 of 16384 flops per 16 edges, 16 rows and 16
+        # columns: six bf16 products per fp32 multiply-add), below as fp32;
+        # then per receiver and 16 channels one fp32 16x16x4 MFMA per component
+        # q and group of four rows (7 groups at L = 4, 12 and 13 at L = 5, 6)
+        groups = {4: 7, 5: 12, 6: 13}.get(L, (nk + 3) // 4)
+        cols = 16 * -(-C // 16)
         agg = dict(flops=2.0 * E * dimT * C + 2.0 * n * (cpl + cnt["q_slots"]) * C,
-                   bytes=inputs + 4.0 * n * nk * nk * nk + 4.0 * n * nk * C,
-                   issued_flops=2.0 * n * (C // 16) * nk * mt * ksteps * 1024,
-                   issued_bf16_flops=16.0 * E * mp * nk * C)
+                   bytes=inputs + 4.0 * n * nk * C,
+                   issued_flops=2.0 * n * cols * nk * groups * 64 + (0.0 if L >= 4 else 2.0 * E * mp * nk * cols))
+        if L >= 4:
+            agg["issued_bf16_flops"] = 12.0 * E * mp * nk * cols
     else:
         agg = dict(flops=2.0 * E * dimT * C + 2.0 * n * cpl * C, bytes=inputs + 4.0 * n * dimT * C,
                    issued_flops=2.0 * E * mp * nk * C + 2.0 * n * cpl * C)
@@ -539,7 +538,7 @@ def main():
           file=sys.stderr, flush=True)
 
     kernels = {k: dict(launches=v[0] // args.steps, ms=v[1] / args.steps) for k, v in prof.items()}
-    fused = "fuse_build" in prof  # the aggregation applied the recouple itself
+    fused = "recouple" not in prof  # the aggregation coupled to the output itself
     counts = alg_counts(e2f, L, C, H, n, E, fused)
     peaks = {"aggregate": FP32_MFMA_PEAK_TFS, "recouple": FP32_MFMA_PEAK_TFS, "mix": FP32_MFMA_PEAK_TFS}
     for k, v in kernels.items():
@@ -570,8 +569,8 @@ def main():
     tr_path = os.path.join(ROOT, "profiles", "traffic_%s_%s.json" % (dom, wl.name))
     if os.path.exists(tr_path):
         tr = json.load(open(tr_path))
-        src = os.path.join(ROOT, "paper_2501_19216_amd", "csrc", "conv.hip")
-        if tr.get("conv_sha256") == file_sha(src):
+        src = "fused.hip" if dom == "aggregate" and fused else "conv.hip"
+        if tr.get("source_sha256") == file_sha(os.path.join(ROOT, "paper_2501_19216_amd", "csrc", src)):
             roof["traffic"] = tr["bytes_per_launch"]
             # measured HBM rate: counter bytes over the same launch time
             roof["traffic_GBps"] = tr["bytes_per_launch"] / (t_dom * 1e-3) / 1e9
