@@ -122,7 +122,7 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
     return Step{r, __builtin_amdgcn_readlane(va, r), __builtin_amdgcn_readlane(vb, r)};
   };
   auto next = [&](Step s) {  // past the last step: the last step again
-    if (s.e + 16 < s.end) return Step{s.r, s.e + 16, s.end};
+    if (s.end - s.e > 16) return Step{s.r, s.e + 16, s.end};  // (s.e + 16 may pass 2^31 - 1)
     const unsigned long long m = live & ~((2ull << s.r) - 1);
     return m ? row(m) : s;
   };
@@ -308,7 +308,7 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
         }
       }
     }
-    if (s0.e + 16 >= s0.end) {  // the receiver's last step: couple
+    if (s0.end - s0.e <= 16) {  // the receiver's last step: couple
       const int i0 = __builtin_amdgcn_readlane(vi, s0.r);
       // (PARTS sums an accumulator, so that consecutive steps do not wait for
       // each other)
