@@ -1342,8 +1342,7 @@ e2f_status e2f_wigner6j_conv_forward_dense(e2f_ctx* ctx, const e2f_conv_params* 
   E2F_TIMED("bbox", launch_plan_centre(stats, org, s));
   E2F_TIMED("sh", launch_sh(t, pos, nullptr, org, nullptr, nullptr, 1, n, R, nullptr, s));
   E2F_TIMED("node_tp", launch_node_tp(t, R, nullptr, feat, n, C, dh, T, s));
-  E2F_TIMED("tile_plan", launch_dense_alpha(alpha, n, H, A, s));
-  E2F_TIMED("tile_plan", launch_iota(n, order, s));
+  E2F_TIMED("tile_plan", launch_dense_alpha(alpha, n, H, A, order, s));
   E2F_TIMED("aggregate", launch_dense_aggregate(A, n, T, t.dimT, C, H, S, s));
   E2F_TIMED("recouple", launch_recouple(t, R, S, false, order, n, C, dh, y, s));
   if (mixing) E2F_TIMED("mix", launch_mix(L, y, p->mix_w, p->mix_dtype == E2F_BF16, n, C, out, s));

@@ -218,9 +218,9 @@ hipError_t launch_transpose_graph(const int64_t* row_ptr, const int32_t* col_idx
 hipError_t launch_transpose_mix(const void* W, bool bf16, int L, int C, void* WT, hipStream_t s);
 
 // ---- dense graphs (dense.hip): A[h][i][j] = alpha[i][j][h] (1 if alpha is
-// NULL), 0 for i == j, rows of dense_lda(n) floats (zero padding)
+// NULL), 0 for i == j, rows of dense_lda(n) floats (zero padding); order[i] = i
 int dense_lda(int n);
-hipError_t launch_dense_alpha(const float* alpha, int n, int H, float* A, hipStream_t s);
+hipError_t launch_dense_alpha(const float* alpha, int n, int H, float* A, int32_t* order, hipStream_t s);
 // S_h = A_h T_h per head on MFMA: T and S head-major [n][H][dimT][C/H]
 hipError_t launch_dense_aggregate(const float* A, int n, const float* T, int dimT, int C, int H, float* S,
                                   hipStream_t s);

@@ -136,6 +136,28 @@ def test_dense_graph_layer(e2f, ctx, n, L, C, H, rows, mix):
     assert o.max_rel_err(got1[r1], ref1, L) <= TOL_F32
 
 
+# The edges of the product's tiles (256 x 128, K slabs of 16, rows of A padded to
+# 32, column chunks of 256 and groups of 8 heads).  Float products (split exactly
+# into three bf16 parts) and sums of n terms: the layer's bar leaves more than a
+# digit over the 1e-6 seen.
+@pytest.mark.parametrize("n,L,C,H", [(2, 0, 4, 1), (15, 1, 36, 9), (16, 2, 16, 4), (17, 2, 64, 16), (33, 4, 8, 2),
+                                     (64, 3, 12, 3), (255, 1, 8, 1), (257, 2, 40, 10), (289, 3, 32, 8)])
+def test_dense_tile_edges(e2f, ctx, n, L, C, H):
+    rng = np.random.default_rng(31 * n + L)
+    pos = syn.quantize(rng.uniform(0, (n / 0.1) ** (1.0 / 3.0), size=(n, 3)))
+    feat = rng.standard_normal((n, (L + 1) ** 2, C)).astype(np.float32)
+    A = rng.uniform(0.0, 1.0 / n, size=(n, n, H)).astype(np.float32)
+    rp, ci = complete_graph(n)
+    r = np.unique(np.linspace(0, n - 1, 24).astype(np.int32))
+    al = A[np.repeat(np.arange(n), n - 1), ci]
+    print("dense n %d L %d C %d H %d" % (n, L, C, H), flush=True)
+    for weights, ref_al in ((gpu(A), al), (None, np.ones_like(al))):
+        got = e2f.e2f_wigner6j_conv_forward_dense(ctx, gpu(pos), gpu(feat), weights, L, H, 10.0).cpu().numpy()
+        err = o.max_rel_err(got[r], o.layer(L, H, pos, feat, rp, ci, ref_al, default_w(L, 10.0), rows=r), L)
+        print("  err %.3e" % err)
+        assert err <= TOL_F32
+
+
 def test_dense_graph_single_atom(e2f, ctx):
     feat = np.ones((1, 9, 8), dtype=np.float32)
     got = e2f.e2f_wigner6j_conv_forward_dense(ctx, gpu(np.zeros((1, 3), np.float32)), gpu(feat),
