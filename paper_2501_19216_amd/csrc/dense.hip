@@ -2,20 +2,27 @@
 // tensor alpha in R^{N x N x H}): per head h the einsum "ijh,jhds->ihds" is a
 // dense product S_h = A_h T_h, with A_h [N x N] the attention weights of head
 // h (zero diagonal) and T_h [N x W] the head's columns of the j-side node
-// products (W = dimT * C/H).  fp32 on v_mfma_f32_16x16x4f32.
+// products (W = dimT * C/H).
+//
+// The product is bound by the matrix cores.  Every float is split into three
+// bf16 parts on its way into LDS (x = hi + mid + lo exactly) and the six cross
+// products that reach 2^-24 of the product are summed in float: three
+// v_mfma_f32_16x16x32_bf16 (16 cycles each) per 16 k of a 16 x 16 tile, whose
+// 32 K slots are two parts of a lane's four k, against four
+// v_mfma_f32_16x16x4f32 (32 cycles each).  Dense forward at L = 3, C = 128,
+// H = 8: 522 -> 353 us at 1,000 atoms and 7.1 -> 4.4 ms at 4,000; error against
+// 64 bits 6.3e-7 -> 5.5e-7.  (A scheme with one k a lane and two of eight K
+// slots idle took 64 instructions where this one takes 48, and did not pay.)
 //
 // Tiling: a workgroup of eight waves owns a 256 x 128 tile of S_h (4 x 2
 // waves of 64 x 64, each 4 x 4 MFMA tiles of 16 x 16); K advances 16 at a
 // time through double-buffered LDS, the next K slab loaded into registers
-// while the current one is multiplied.  A is stored by the alpha kernel with
-// rows padded to a multiple of 32 (zeros), so K needs no tail handling.
-// Workgroups of one XCD take a contiguous range of (head, row block) tiles
-// with every column block, so A's row slabs and T's column slabs in flight
-// on an XCD are shared through its L2.  Measured at L = 3, C = 128, H = 8
-// (N = 250 .. 4000, whole dense forward): 256 x 128 tiles 0.098 / 0.210 /
-// 0.550 / 1.897 / 7.066 ms, against 128 x 128: 0.104 / 0.195 / 0.615 /
-// 2.097 / 7.899, 128 x 256: .. / 7.690, 256 x 256: 0.128 / .. / 6.979, and
-// 128 x 128 with K slabs of 32: .. / 8.154.
+// while the current one is multiplied.  128 VGPRs and 75 KB of LDS: two
+// workgroups share a CU, one's splits beside the other's products.  A is stored
+// by the alpha kernel with rows padded to a multiple of 32 (zeros), so K needs
+// no tail handling.  Workgroups of one XCD take a contiguous range of (head,
+// row block) tiles with every column block, so A's row slabs and T's column
+// slabs in flight on an XCD are shared through its L2.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -27,6 +34,33 @@ namespace e2f {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+
+// Two floats as three words of bfloat16 pairs, x = hi + mid + lo exactly: hi
+// and mid rounded to nearest, lo the rest (8 + 8 + 8 bits hold the 24).
+__device__ __forceinline__ void split_pair(float x, float y, unsigned& hi, unsigned& mid, unsigned& lo) {
+  hi = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){x, y}, v2b));
+  const float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xffff0000u);
+  mid = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){rx, ry}, v2b));
+  const float sx = rx - __uint_as_float(mid << 16), sy = ry - __uint_as_float(mid & 0xffff0000u);
+  lo = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){sx, sy}, v2b));
+}
+
+__device__ __forceinline__ void split4(float x, float y, float z, float w, v2u& hi, v2u& mid, v2u& lo) {
+  unsigned h, m, l;
+  split_pair(x, y, h, m, l);
+  hi.x = h, mid.x = m, lo.x = l;
+  split_pair(z, w, h, m, l);
+  hi.y = h, mid.y = m, lo.y = l;
+}
+
+__device__ __forceinline__ v4f mfma_bf16(v4u a, v4u b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
+}
 
 // A[h][i][j] = alpha[i][j][h] (1 if alpha is NULL), 0 for i == j and for the
 // padding columns j >= n of rows of lda floats; order[i] = i (the recouple's
@@ -69,20 +103,24 @@ __global__ __launch_bounds__(kPadCols) void k_dense_alpha_pad(const float* __res
 // past n; T rows past n are never read with a nonzero weight, their index is
 // clamped).  T_h[k][c] = T[k * ldt + h * W + c], S likewise.  WGM x WGN waves
 // of 64 x 64 outputs each; K slabs of BK.
-template <int WGM, int WGN, int BK>
+template <int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_dense_gemm(const float* __restrict__ A, int lda, int n,
                                                                const float* __restrict__ T, int64_t ldt, int W,
                                                                float* __restrict__ S, int n_ib, int n_cb, int H,
                                                                int per_xcd) {
-  constexpr int BM = 64 * WGM, BN = 64 * WGN, NT = 64 * WGM * WGN;
-  // LDS row strides (floats): A [BM][AS] with k contiguous (the MFMA reads of
-  // 16 rows x 2 k fall in distinct banks), B [BK][BS] with columns contiguous
-  // (16 mod 32: the two k rows of a read fall in different bank halves)
-  constexpr int AS = BK + 2, BS = BN + 16;
-  constexpr int FA = BM * BK / 4 / NT, FB = BK * BN / 4 / NT;  // float4 loads per thread
-  static_assert(FA * NT * 4 == BM * BK && FB * NT * 4 == BK * BN, "tile loads must divide evenly");
-  __shared__ __attribute__((aligned(16))) float As[2][BM * AS];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BK * BS];
+  constexpr int BM = 64 * WGM, BN = 64 * WGN, NT = 64 * WGM * WGN, BK = 16;
+  // K group q of a slab is its k = 4 q .. 4 q + 3; an entry (q, row or column)
+  // holds the parts of its four values, A's {lo01, lo23, hi01, hi23} and
+  // {mid01, mid23}, B's {hi01, hi23, mid01, mid23} and {lo01, lo23}.  (Groups
+  // start 16 banks apart, so the four entries of a row that neighbouring
+  // threads store fall in different banks.)
+  constexpr int AQ = BM + 4, AP = BM + 8;
+  constexpr int FA = BM * 4 / NT, FB = BN * 4 / NT;  // entries per thread
+  static_assert(FA * NT == BM * 4 && FB * NT == BN * 4, "tile loads must divide evenly");
+  __shared__ v4u Aw[2][4 * AQ];
+  __shared__ v2u Am[2][4 * AP];
+  __shared__ v4u Bw[2][4 * BN];
+  __shared__ v2u Bl[2][4 * BN];
   const int tile = (blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if (tile >= H * n_ib * n_cb) return;  // uniform over the workgroup
   const int cb = tile % n_cb, ib = (tile / n_cb) % n_ib, h = tile / (n_cb * n_ib);
@@ -92,36 +130,48 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_dense_gemm(const float* __re
   const float* Ah = A + (int64_t)h * n * lda;
   const float* Th = T + (int64_t)h * W;
   const int nk = lda / BK;
-  // float4 f of a slab: A row f / (BK/4) (clamped to n - 1), k 4 (f % (BK/4));
-  // B row f / (BN/4) (clamped to n - 1; A is zero there), columns clamped to
-  // W - 4 (never stored)
-  float4 ra[FA], rb[FB];
+  // entry f of a slab: A row f / 4 (clamped to n - 1), group f % 4; B column f %
+  // BN (clamped to W - 1, never stored), group f / BN, its rows clamped to n - 1
+  // (A is zero there)
+  const float* pa[FA];
+  unsigned pb[FB];
+  int qb[FB];  // (uniform over a wave: BN is a multiple of 64)
+#pragma unroll
+  for (int u = 0; u < FA; ++u) {
+    const int f = tid + u * NT;
+    pa[u] = Ah + (int64_t)min(ib * BM + f / 4, n - 1) * lda + 4 * (f % 4);
+  }
+#pragma unroll
+  for (int u = 0; u < FB; ++u) {
+    const int f = tid + u * NT;
+    pb[u] = (unsigned)min(cb * BN + f % BN, W - 1);
+    qb[u] = __builtin_amdgcn_readfirstlane(f / BN);
+  }
+  float4 ra[FA];
+  float rb[FB][4];
   auto load = [&](int kt) {
-    const int k0 = kt * BK;
 #pragma unroll
-    for (int u = 0; u < FA; ++u) {
-      const int f = tid + u * NT, r = min(ib * BM + f / (BK / 4), n - 1);
-      ra[u] = *(const float4*)(Ah + (int64_t)r * lda + k0 + 4 * (f % (BK / 4)));
-    }
+    for (int u = 0; u < FA; ++u) ra[u] = *(const float4*)(pa[u] + kt * BK);
 #pragma unroll
-    for (int u = 0; u < FB; ++u) {
-      const int f = tid + u * NT, r = min(k0 + f / (BN / 4), n - 1);
-      const int c = min(cb * BN + 4 * (f % (BN / 4)), W - 4);
-      rb[u] = *(const float4*)(Th + (int64_t)r * ldt + c);
-    }
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) rb[u][x] = (Th + (int64_t)min(kt * BK + 4 * qb[u] + x, n - 1) * ldt)[pb[u]];
   };
   auto store = [&](int buf) {
+    v2u hi, mid, lo;
 #pragma unroll
     for (int u = 0; u < FA; ++u) {
       const int f = tid + u * NT;
-      float* d = As[buf] + (f / (BK / 4)) * AS + 4 * (f % (BK / 4));
-      *(float2*)d = make_float2(ra[u].x, ra[u].y);
-      *(float2*)(d + 2) = make_float2(ra[u].z, ra[u].w);
+      split4(ra[u].x, ra[u].y, ra[u].z, ra[u].w, hi, mid, lo);
+      Aw[buf][(f % 4) * AQ + f / 4] = (v4u){lo.x, lo.y, hi.x, hi.y};
+      Am[buf][(f % 4) * AP + f / 4] = mid;
     }
 #pragma unroll
     for (int u = 0; u < FB; ++u) {
       const int f = tid + u * NT;
-      *(float4*)(Bs[buf] + (f / (BN / 4)) * BS + 4 * (f % (BN / 4))) = rb[u];
+      split4(rb[u][0], rb[u][1], rb[u][2], rb[u][3], hi, mid, lo);
+      Bw[buf][f] = (v4u){hi.x, hi.y, mid.x, mid.y};
+      Bl[buf][f] = lo;
     }
   };
   v4f acc[4][4];
@@ -134,23 +184,30 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_dense_gemm(const float* __re
   __syncthreads();
   for (int kt = 0; kt < nk; ++kt) {
     const int buf = kt & 1;
-    if (kt + 1 < nk) load(kt + 1);  // in flight while this slab is multiplied
-    const float* as = As[buf];
-    const float* bs = Bs[buf];
+    load(min(kt + 1, nk - 1));  // in flight while this slab is multiplied
+    v4u aw[4];
+    v2u am[4];
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      float a[4], b[4];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) a[mt] = as[(wm + mt * 16 + l16) * AS + kk + k4];
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) b[nt] = bs[(kk + k4) * BS + wn + nt * 16 + l16];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+    for (int mt = 0; mt < 4; ++mt) {
+      aw[mt] = Aw[buf][k4 * AQ + wm + mt * 16 + l16];
+      am[mt] = Am[buf][k4 * AP + wm + mt * 16 + l16];
     }
-    if (kt + 1 < nk) store(buf ^ 1);  // the other buffer was last read before the previous barrier
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      const v4u bw = Bw[buf][k4 * BN + wn + nt * 16 + l16];
+      const v2u bl = Bl[buf][k4 * BN + wn + nt * 16 + l16];
+      const v4u bmh = {bw.z, bw.w, bw.x, bw.y}, bhl = {bw.x, bw.y, bl.x, bl.y};
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)  // lo hi + hi lo
+        acc[mt][nt] = mfma_bf16(aw[mt], bhl, acc[mt][nt]);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)  // hi mid + mid hi
+        acc[mt][nt] = mfma_bf16((v4u){aw[mt].z, aw[mt].w, am[mt].x, am[mt].y}, bmh, acc[mt][nt]);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)  // hi hi + mid mid
+        acc[mt][nt] = mfma_bf16((v4u){aw[mt].z, aw[mt].w, am[mt].x, am[mt].y}, bw, acc[mt][nt]);
+    }
+    store(buf ^ 1);  // the other buffer was last read before the previous barrier
     __syncthreads();
   }
   // acc[mt][nt][v] = S[row wm + 16 mt + 4 k4 + v][col wn + 16 nt + l16]
@@ -187,27 +244,27 @@ hipError_t launch_dense_aggregate(const float* A, int n, const float* T, int dim
   if (n == 0) return hipSuccess;
   const int dh = C / H, W = dimT * dh;
   if (W < 4 || W % 4) return hipErrorInvalidValue;
-  // tile shape (waves in M, waves in N, K slab); E2F_DENSE_TILE = "WGM,WGN,BK"
-  // selects another of the compiled shapes (tuning)
+  // tile shape (waves in M, waves in N); E2F_DENSE_TILE = "WGM,WGN" selects
+  // another of the compiled shapes (tuning)
   static const int shape = [] {
     const char* v = getenv("E2F_DENSE_TILE");
-    int a = 4, b = 2, k = 16;
-    if (v) sscanf(v, "%d,%d,%d", &a, &b, &k);
-    return a * 100 + b * 10 + k / 16;
+    int a = 4, b = 2;
+    if (v) sscanf(v, "%d,%d", &a, &b);
+    return a * 10 + b;
   }();
-  const int wgm = shape / 100, wgn = (shape / 10) % 10;
+  const int wgm = shape / 10, wgn = shape % 10;
   const int n_ib = (n + 64 * wgm - 1) / (64 * wgm), n_cb = (W + 64 * wgn - 1) / (64 * wgn);
   const int64_t tiles = (int64_t)H * n_ib * n_cb;
   const int64_t per_xcd = (tiles + 7) / 8;
   if (8 * per_xcd > 0x7fffffff) return hipErrorInvalidValue;
   const int64_t ldt = (int64_t)dimT * C;
   switch (shape) {
-#define E2F_DG(M_, N_, K_)                                                                                    \
-  case M_ * 100 + N_ * 10 + K_ / 16:                                                                          \
-    k_dense_gemm<M_, N_, K_><<<(unsigned)(8 * per_xcd), 64 * M_ * N_, 0, s>>>(A, dense_lda(n), n, T, ldt, W, S, \
-                                                                              n_ib, n_cb, H, (int)per_xcd);   \
+#define E2F_DG(M_, N_)                                                                                             \
+  case M_ * 10 + N_:                                                                                               \
+    k_dense_gemm<M_, N_><<<(unsigned)(8 * per_xcd), 64 * M_ * N_, 0, s>>>(A, dense_lda(n), n, T, ldt, W, S, n_ib,   \
+                                                                          n_cb, H, (int)per_xcd);                  \
     break;
-    E2F_DG(2, 2, 16) E2F_DG(4, 2, 16) E2F_DG(4, 4, 16)
+    E2F_DG(2, 2) E2F_DG(4, 2) E2F_DG(4, 4)
 #undef E2F_DG
     default: return hipErrorInvalidValue;
   }
