@@ -16,6 +16,33 @@ namespace e2f {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+// Four floats as bfloat16 pairs, x = hi + mid + lo exactly: hi and mid rounded
+// to nearest, lo the rest (8 + 8 + 8 bits hold the 24).
+struct Parts {
+  unsigned h0, h1, m0, m1, l0, l1;
+};
+__device__ __forceinline__ void split_pair(float x, float y, unsigned& hi, unsigned& mid, unsigned& lo) {
+  hi = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){x, y}, v2b));
+  const float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xffff0000u);
+  mid = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){rx, ry}, v2b));
+  const float sx = rx - __uint_as_float(mid << 16), sy = ry - __uint_as_float(mid & 0xffff0000u);
+  lo = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){sx, sy}, v2b));
+}
+__device__ __forceinline__ Parts split4(float x, float y, float z, float w) {
+  Parts p;
+  split_pair(x, y, p.h0, p.m0, p.l0);
+  split_pair(z, w, p.h1, p.m1, p.l1);
+  return p;
+}
+
+__device__ __forceinline__ v4f mfma_bf16(v4u a, v4u b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
+}
 
 // Gradient of one solid harmonic from its monomials: d/dx of c x^a y^b z^e
 // is c a x^(a-1) y^b z^e (no term when a = 0).
@@ -58,10 +85,22 @@ __device__ __forceinline__ float sum16(float v) {
 // and key, the features of two steps eight per tile.
 constexpr int grad_tiles(int L) { return L <= 4 ? 6 : 3; }
 constexpr int kGradWaves = 4;
+// Where X += h Z^T runs as split bf16 products: a lane's four slots fill the K
+// of three v_mfma_f32_16x16x32_bf16 (16 cycles each) a tile and key with the six
+// cross products that reach 2^-24 of the product, against four
+// v_mfma_f32_16x16x4f32 (32 cycles each); the features' split is shared by the
+// keys, that of Z by the tiles.  Below L = 4 one key does not pay for the
+// split.  Feature and weight gradients (one component a step, P = 1): 2,000
+// atoms, L = 4 1.02 -> 0.87 ms, 9,001 atoms, L = 5 3.79 -> 3.02, 2,000 atoms, L =
+// 6 1.58 -> 1.34.  At L = 5, 6 with narrow heads (P = 2, 4) the coupling is the
+// larger part and the registers of the split slow it: 2,500 atoms, L = 5, P = 2
+// 1.12 float, 1.24 split; L = 6, P = 2 2.38 and 2.43, P = 4 4.41 and 4.44.  At L = 4
+// P = 2 0.74 -> 0.67, P = 4 0.90 -> 0.89.
+constexpr bool grad_split(int L, int P) { return L == 4 || (L > 4 && P == 1); }
 
 // A wave takes one head of one receiver at a time.  Both products run on
-// v_mfma_f32_16x16x4f32 and the first feeds the second from its accumulators:
-// for a component q
+// v_mfma_f32_16x16x4f32 (the second split where grad_split says so) and the
+// first feeds the second from its accumulators: for a component q
 //   Z^T[(p, c)][be] = sum_o gy^T[(p, c)][o] K_q[o][be]
 // comes out with column be = l16 and rows 4 k4 + v, which is the B operand of
 // step v of X[e][be] += sum_{(p, c)} h[e][(p, c)] Z^T[(p, c)][be] when step v
@@ -203,16 +242,39 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
               }
             }
             // (z[x] holds the columns of key x ^ y)
+            if constexpr (grad_split(L, P)) {
+              v4u hm[KEYS], mh[KEYS], hl[KEYS];  // the parts of z: {hi, mid}, {mid, hi}, {hi, lo}
 #pragma unroll
-            for (int u = 0; u < T; ++u)
-              if (u < nt) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                  for (int x = 0; x < KEYS; ++x)
-                    X[u][x ^ y] =
-                        __builtin_amdgcn_mfma_f32_16x16x4f32((&f[u].x)[v], z[x][v], X[u][x ^ y], 0, 0, 0);
+              for (int x = 0; x < KEYS; ++x) {
+                const Parts b = split4(z[x][0], z[x][1], z[x][2], z[x][3]);
+                hm[x] = (v4u){b.h0, b.h1, b.m0, b.m1};
+                mh[x] = (v4u){b.m0, b.m1, b.h0, b.h1};
+                hl[x] = (v4u){b.h0, b.h1, b.l0, b.l1};
               }
+#pragma unroll
+              for (int u = 0; u < T; ++u)
+                if (u < nt) {
+                  const Parts a = split4(f[u].x, f[u].y, f[u].z, f[u].w);
+                  const v4u lh = {a.l0, a.l1, a.h0, a.h1}, ha = {a.h0, a.h1, a.m0, a.m1};
+#pragma unroll
+                  for (int x = 0; x < KEYS; ++x) X[u][x ^ y] = mfma_bf16(lh, hl[x], X[u][x ^ y]);
+#pragma unroll
+                  for (int x = 0; x < KEYS; ++x) X[u][x ^ y] = mfma_bf16(ha, mh[x], X[u][x ^ y]);
+#pragma unroll
+                  for (int x = 0; x < KEYS; ++x) X[u][x ^ y] = mfma_bf16(ha, hm[x], X[u][x ^ y]);
+                }
+            } else {
+#pragma unroll
+              for (int u = 0; u < T; ++u)
+                if (u < nt) {
+#pragma unroll
+                  for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int x = 0; x < KEYS; ++x)
+                      X[u][x ^ y] =
+                          __builtin_amdgcn_mfma_f32_16x16x4f32((&f[u].x)[v], z[x][v], X[u][x ^ y], 0, 0, 0);
+                }
+            }
           };
           load(0, fa);
 #pragma unroll 1

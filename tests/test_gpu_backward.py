@@ -107,6 +107,18 @@ def test_backward_knn_graph_is_transposed(e2f, ctx):
     check(e2f, ctx, pos, rp, ci, 3, 32, 4, float(d.max()) * 1.001, 5)
 
 
+# the per-edge products at L >= 4, float and split, one, two and four components a
+# step, long rows and rows that average fewer than 24 edges
+@pytest.mark.parametrize("L,C,H", [(4, 12, 3), (4, 48, 3), (5, 16, 1), (5, 24, 3), (5, 24, 2), (6, 48, 3)])
+@pytest.mark.parametrize("rc", [3.0, 5.0])
+def test_backward_per_edge_products(e2f, ctx, L, C, H, rc):
+    rng = np.random.default_rng(70 + L + C)
+    pos = syn.quantize(rng.uniform(0, 9, size=(110, 3)))
+    rp, ci = o.neighbor_list(pos, rc)
+    print("L %d C %d H %d rc %.1f" % (L, C, H, rc), flush=True)
+    check(e2f, ctx, pos, rp, ci, L, C, H, rc, 70 + L)
+
+
 @pytest.mark.parametrize("H", [8, 2])
 def test_backward_graphs_and_single_outputs(e2f, ctx, H):
     inp = syn.make_inputs(syn.WORKLOADS["molecules256x30_L3"], n_atoms=40 * 30)
