@@ -518,6 +518,11 @@ e2f_status transpose_factors(e2f_ctx* ctx, int L, const std::vector<double>*& ou
 // Smallest slice of receivers a workspace must hold S for.
 constexpr int64_t kMinSlice = 256;
 
+// The backward's per-edge tables of one pass: at most this many bytes, but
+// always this many edges.
+constexpr size_t kEdgePassBytes = (size_t)4 << 30;
+constexpr int64_t kEdgePassMin = 16384;
+
 // Byte layout of the forward's workspace: the plan and per-edge arrays (a
 // fixed part), then S for a slice of receivers.
 struct FwdLayout {
@@ -668,7 +673,7 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
                                                (uint64_t*)(ws + f.keys_out), (int32_t*)(ws + f.vals), order,
                                                ws + f.sort_tmp, f.sort_b, s));
     }
-    E2F_TIMED("sh", launch_edge_sh(t, pos, row_ptr, col_idx, n, n_edges, ynorm, Re, s));
+    E2F_TIMED("sh", launch_edge_sh(t, pos, row_ptr, col_idx, n, 0, n_edges, ynorm, Re, s));
     for (int64_t q0 = 0; q0 < n; q0 += slice, ++slices)
       E2F_TIMED("aggregate", launch_aggregate_fused(L, Re, row_ptr, col_idx, alpha, n_edges, feat,
                                                     n > kPlanSmallMax ? order : nullptr, (int)q0,
@@ -1214,20 +1219,21 @@ e2f_status e2f_wigner6j_conv_backward(e2f_ctx* ctx, const e2f_conv_params* p, co
   const size_t wt_bytes = (size_t)L1 * C * C * (p->mix_dtype == E2F_BF16 ? 2 : 4);
   const size_t tmp_b = transpose_tmp_bytes(n, n_edges);
   const bool want_t = (grad_feat != nullptr || grad_pos != nullptr) && n_edges > 0;
-  // the forces read the harmonic gradients of every edge from a table when it
-  // stays under 4 GiB (else the per-edge kernel evaluates them itself)
-  const size_t gt_bytes_full = sizeof(float) * 3 * (size_t)n_edges * nk;
-  const char* gt_env = getenv("E2F_GEOM_GT");  // "0": always evaluate in the per-edge kernel (read per call)
-  const size_t gt_bytes = grad_pos && n_edges > 0 && gt_bytes_full <= ((size_t)4 << 30) && !(gt_env && atoi(gt_env) == 0)
-                              ? gt_bytes_full
-                              : 0;
+  // the per-edge products go in passes of edges whose tables (the harmonics,
+  // their gradients, the heads' parts of the forces) fit kEdgePassBytes
+  const size_t edge_b = (grad_pos ? sizeof(float) * 3 * (size_t)(nk + (H > 1 ? H : 0)) : 0) +
+                        (grad_alpha ? sizeof(float) * (size_t)nk : 0);
+  const char* pass_env = getenv("E2F_GEOM_GT");  // another limit in bytes (read per call; 0: the smallest passes)
+  const size_t pass_b = pass_env ? (size_t)std::max(0ll, atoll(pass_env)) : kEdgePassBytes;
+  const int64_t pass =
+      edge_b ? std::min<int64_t>(n_edges, std::max<int64_t>(kEdgePassMin, (int64_t)(pass_b / edge_b))) : 0;
+  const int passes = pass ? (int)((n_edges + pass - 1) / pass) : 0;
   const size_t need = (mixing ? al256(sizeof(float) * (size_t)n * nk * C) + al256(wt_bytes) : 0) +
                       (want_t ? 5 * al256(sizeof(int32_t) * (size_t)n_edges) + 2 * al256(sizeof(int64_t) * (n + 1)) +
                                     al256(sizeof(float) * (size_t)n_edges * H) + al256(tmp_b)
                               : 0) +
-                      (grad_pos ? al256(sizeof(float) * (size_t)n_edges * 3) : 0) + al256(gt_bytes) +
-                      (grad_pos && H > 1 ? al256(sizeof(float) * (size_t)n_edges * 3 * H) : 0) +
-                      (grad_alpha ? al256(sizeof(float) * (size_t)n_edges * nk) : 0) + 256;
+                      (grad_pos ? al256(sizeof(float) * (size_t)n_edges * 3) : 0) + edge_b * (size_t)pass +
+                      sizeof(int) * 2 * (size_t)passes + 5 * 256;
   rs = ensure(ctx, ctx->d, need, s);
   if (rs != E2F_OK) return rs;
   Carver cd{(char*)ctx->d.p};
@@ -1267,14 +1273,18 @@ e2f_status e2f_wigner6j_conv_backward(e2f_ctx* ctx, const e2f_conv_params* p, co
   // ---- attention weights and positions: per edge, both from one product per
   // (receiver, head); then per atom the forces received minus those sent
   float* gedge = grad_pos ? cd.take<float>((size_t)n_edges * 3) : nullptr;
-  float* Gt = gt_bytes ? cd.take<float>(gt_bytes / sizeof(float)) : nullptr;
-  if (Gt) E2F_TIMED("edge_geom", launch_edge_shgrad(tw, pos, rows, col_idx, n, n_edges, Gt, s));
-  if (grad_alpha || gedge) {
-    float* Re = grad_alpha ? cd.take<float>((size_t)n_edges * nk) : nullptr;
-    if (Re) E2F_TIMED("sh", launch_edge_sh(tw, pos, row_ptr, col_idx, n, n_edges, false, Re, s));
-    float* gpart = gedge && H > 1 ? cd.take<float>((size_t)n_edges * 3 * H) : nullptr;
-    E2F_TIMED("edge_geom", launch_edge_grad(tw, pos, Re, Gt, feat, gy, row_ptr, col_idx, alpha, nullptr, n, C, H,
-                                            n_edges, cs->grad_coef, grad_alpha, gpart, gedge, s));
+  float* Gt = grad_pos ? cd.take<float>((size_t)pass * 3 * nk) : nullptr;
+  float* gpart = grad_pos && H > 1 ? cd.take<float>((size_t)pass * 3 * H) : nullptr;
+  float* Re = grad_alpha ? cd.take<float>((size_t)pass * nk) : nullptr;
+  int* range = passes > 1 ? cd.take<int>((size_t)passes * 2) : nullptr;
+  if (range) E2F_TIMED("edge_geom", launch_edge_ranges(row_ptr, n, n_edges, pass, passes, range, s));
+  for (int q = 0; q < passes; ++q) {
+    const int64_t lo = q * pass, hi = std::min(lo + pass, n_edges);
+    if (Gt) E2F_TIMED("edge_geom", launch_edge_shgrad(tw, pos, rows + lo, col_idx + lo, n, hi - lo, Gt, s));
+    if (Re) E2F_TIMED("sh", launch_edge_sh(tw, pos, row_ptr, col_idx, n, lo, hi - lo, false, Re, s));
+    E2F_TIMED("edge_geom", launch_edge_grad(L, Re, Gt, feat, gy, row_ptr, col_idx, alpha, nullptr, n, C, H, n_edges, lo,
+                                            hi, range ? range + 2 * q : nullptr, cs->grad_coef, grad_alpha, gpart,
+                                            gedge ? gedge + 3 * lo : nullptr, s));
   }
   if (gedge) E2F_TIMED("force_gather", launch_force_gather(row_ptr, rowT, perm, gedge, n, grad_pos, s));
   // ---- features: the same layer on the transposed graph, input degree o,

@@ -61,10 +61,11 @@ hipError_t launch_plan_order(const float* pos, const int32_t* graph_id, int n, c
 hipError_t launch_plan_sh(const DevTables& t, const float* pos, const int32_t* rows, const int32_t* col, int n,
                           int64_t n_edges, const int32_t* tile_of, const TileGridDev* grid, double* Rr, float* Re,
                           hipStream_t s);
-// Re [E][nk] float32: the harmonics of r_i - r_j of every edge (unit: of the
-// unit vector, the zero vector's where the atoms coincide)
+// Re [count][nk] float32: the harmonics of r_i - r_j of the edges first ..
+// first + count - 1 (unit: of the unit vector, the zero vector's where the
+// atoms coincide)
 hipError_t launch_edge_sh(const DevTables& t, const float* pos, const int64_t* row_ptr, const int32_t* col, int n,
-                          int64_t n_edges, bool unit, float* Re, hipStream_t s);
+                          int64_t first, int64_t count, bool unit, float* Re, hipStream_t s);
 // rows [E] = the receiver of every edge; with alpha (and alpha_hm), the same
 // launch copies the weights [E][H] head-major into alpha_hm [H][E]
 hipError_t launch_plan_edge_rows(const int64_t* row_ptr, int n, int64_t n_edges, int32_t* rows, const float* alpha,
@@ -190,19 +191,25 @@ hipError_t launch_attention(const float* pos, const float* q, const float* k, in
                             float* alpha, hipStream_t s);
 
 // ---- backward
-// Both per-edge backward products in one pass (either output may be NULL):
-// galpha[e][h] = sum_{c of h} <gy_i[.][c], (K_e h_j)[.][c]> [E][H] and the
-// position gradient per edge gedge [E][3]; coef: grad_table, Re [E][nk]:
-// launch_edge_sh (read for galpha); gpart [H][E][3]: scratch of gedge when H >
-// 1; order: the receivers, or NULL (by index).  launch_force_gather then sums per atom
-// the edges it receives minus those it sends (rowT, perm: the transposed
-// graph).
-hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* Re, const float* Gt, const float* feat,
-                            const float* gy, const int64_t* row_ptr, const int32_t* col, const float* alpha,
-                            const int32_t* order, int n, int C, int H, int64_t n_edges, const float* coef,
-                            float* galpha, float* gpart, float* gedge, hipStream_t s);
-// Gt [E][3][nk]: the harmonic gradients of every edge (rows: the receiver of
-// each edge); launch_edge_grad evaluates them itself when given NULL
+// Both per-edge backward products of the edges lo .. hi - 1 (either output may
+// be NULL): galpha[e][h] = sum_{c of h} <gy_i[.][c], (K_e h_j)[.][c]> [E][H] and
+// the position gradient per edge gedge [hi - lo][3] (from the edge lo on);
+// coef: grad_table, Re [hi - lo][nk]: launch_edge_sh (read for galpha), Gt [hi
+// - lo][3][nk]: launch_edge_shgrad (read for gedge); gpart [H][hi - lo][3]:
+// scratch of gedge when H > 1; order: the receivers, or NULL (by index); range:
+// the pass's entry of launch_edge_ranges, or NULL where the pass has every edge.
+// launch_force_gather then sums per atom the edges it receives minus those it
+// sends (rowT, perm: the transposed graph).
+hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float* feat, const float* gy,
+                            const int64_t* row_ptr, const int32_t* col, const float* alpha, const int32_t* order,
+                            int n, int C, int H, int64_t n_edges, int64_t lo, int64_t hi, const int* range,
+                            const float* coef, float* galpha, float* gpart, float* gedge, hipStream_t s);
+// range [passes][2]: of each pass of `pass` edges the first receiver with one of
+// them and one past the last
+hipError_t launch_edge_ranges(const int64_t* row_ptr, int n, int64_t n_edges, int64_t pass, int passes, int* range,
+                              hipStream_t s);
+// Gt [n_edges][3][nk]: the harmonic gradients of edges given by their receivers
+// (rows) and senders (col)
 hipError_t launch_edge_shgrad(const DevTables& t, const float* pos, const int32_t* rows, const int32_t* col, int n,
                               int64_t n_edges, float* Gt, hipStream_t s);
 hipError_t launch_force_gather(const int64_t* row_ptr, const int64_t* rowT, const int32_t* perm, const float* gedge,

@@ -85,6 +85,12 @@ __device__ __forceinline__ float sum16(float v) {
 // and key, the features of two steps eight per tile.
 constexpr int grad_tiles(int L) { return L <= 4 ? 6 : 3; }
 constexpr int kGradWaves = 4;
+// Receivers a wave takes one after another: up to eight, as long as every CU
+// has work (they share the table).
+__host__ __device__ inline int grad_rpw(int n, int H) {
+  const int64_t r = (int64_t)n * H / (256 * 16);
+  return r < 1 ? 1 : r > 8 ? 8 : (int)r;
+}
 // Where X += h Z^T runs as split bf16 products: a lane's four slots fill the K
 // of three v_mfma_f32_16x16x32_bf16 (16 cycles each) a tile and key with the six
 // cross products that reach 2^-24 of the product, against four
@@ -115,15 +121,23 @@ constexpr bool grad_split(int L, int P) { return L == 4 || (L > 4 && P == 1); }
 // As in the fused aggregation an XCD takes a contiguous range of items (a set
 // of receivers and a head, the heads of one 128-byte line first), so that the
 // lines its waves gather stay in its L2; gedge is therefore written per head
-// ([H][E][3]) and summed over the heads by k_edge_sum.
+// ([H][edges][3]) and summed over the heads by k_edge_sum.
 // T: grad_tiles, or 2 for graphs of short rows (more waves share a SIMD).
+//
+// A launch covers the edges lo .. hi - 1 (a row that crosses the range gives
+// its part: every edge's products are its own).  Re, Gt and gedge hold these
+// edges only, galpha every edge.  range: the receivers with an edge of the
+// range (first, end), over which the workgroups are dealt out anew; NULL: all
+// n.  (Workgroups dealt out over all n, those without an edge leaving at once:
+// the edges of a pass then fall to a few XCDs only, 512,000 edges in four
+// passes 4.1 ms against 1.3 in one.)
 template <int L, int P, bool LT, int T>
 __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu(T > 2 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
-void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __restrict__ Re,
-                 const float* __restrict__ Gt, const float* __restrict__ feat, const float* __restrict__ gy,
-                 const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, const float* __restrict__ feat,
+                 const float* __restrict__ gy, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                  const float* __restrict__ alpha, const int32_t* __restrict__ order, int n, int rpw, int nset, int lg,
-                 int per_xcd, int C, int H, int64_t n_edges, const float* __restrict__ coef,
+                 int per_xcd, int C, int H, int64_t lo, int64_t hi, const int* __restrict__ range,
+                 const float* __restrict__ coef,
                  float* __restrict__ galpha, float* __restrict__ gedge) {
   constexpr AggMap M = agg_map(L);
   constexpr int NK = M.nk, NG = M.ng, KEYS = M.keys, DH = 16 / P;
@@ -131,6 +145,14 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
   const float* tab = LT ? sm : coef;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, k4 = lane >> 4;
+  int first = 0, nrec = n;
+  if (range) {  // (as launch_edge_grad has it for all n)
+    first = range[0], nrec = range[1] - first;
+    rpw = grad_rpw(nrec, H);
+    nset = (nrec + kGradWaves * rpw - 1) / (kGradWaves * rpw);
+    per_xcd = (int)(((int64_t)nset * H + 7) / 8);
+    if ((int)(blockIdx.x / 8) >= per_xcd) return;
+  }
   const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   const int h = item / (nset * lg) * lg + item % lg, set = item / lg % nset;
   if (h >= H) return;
@@ -161,10 +183,10 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
   }
   const int dh = C / H, uph = dh / DH;
   const int pl = 4 * k4 / DH, cl = 4 * k4 % DH;  // the lane's slots 4 k4 .. + 3: component pl, channels cl ..
-  // bounds of a receiver (clamped to [0, E]; E < 2^31), loaded while the one
-  // before is worked on
+  // bounds of a receiver (clamped to the range; hi < 2^31), loaded while the
+  // one before is worked on
   auto receiver = [&](int k, int& i, int64_t& b0, int64_t& b1) {
-    const int at = min((set * rpw + min(k, rpw - 1)) * kGradWaves + wave, n - 1);
+    const int at = first + min((set * rpw + min(k, rpw - 1)) * kGradWaves + wave, nrec - 1);
     i = order ? order[at] : at;
     b0 = row_ptr[i], b1 = row_ptr[i + 1];
   };
@@ -172,10 +194,10 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
   int64_t b0, b1;
   receiver(0, in, b0, b1);
   for (int k = 0; k < rpw; ++k) {
-    if ((set * rpw + k) * kGradWaves + wave >= n) return;
+    if ((set * rpw + k) * kGradWaves + wave >= nrec) return;
     const int i = __builtin_amdgcn_readfirstlane(in);
-    const int e0 = __builtin_amdgcn_readfirstlane((int)max((int64_t)0, min(b0, n_edges)));
-    const int e1 = __builtin_amdgcn_readfirstlane((int)max((int64_t)e0, min(b1, n_edges)));
+    const int e0 = __builtin_amdgcn_readfirstlane((int)max(lo, min(b0, hi)));
+    const int e1 = __builtin_amdgcn_readfirstlane((int)max((int64_t)e0, min(b1, hi)));
     receiver(k + 1, in, b0, b1);
     const float* gyi = gy + (size_t)i * NK * C;
     const int all = (e1 - e0 + 15) / 16;
@@ -288,10 +310,10 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
       }
       // lane (l16, k4) holds X of the columns be = cb[x], edges 16 u + 4 k4 + v:
       // the sums over be for galpha (with R) and gedge (with its gradients)
-      const float* Rc = Re + c0 * NK;
-      const float* Gc = Gt + c0 * 3 * NK;
+      const float* Rc = Re + (c0 - lo) * NK;
+      const float* Gc = Gt + (c0 - lo) * 3 * NK;
       const float* ac = alpha + c0 * H + h;
-      float* gc = gedge + ((size_t)h * n_edges + c0) * 3;
+      float* gc = gedge + (h * (hi - lo) + c0 - lo) * 3;
       // (a pass over the tiles per output: its loads are in flight together)
       auto edge = [&](int u, int v) { return (unsigned)min(16 * u + 4 * k4 + v, cnt - 1); };
       if (galpha) {
@@ -336,19 +358,7 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
-              for (int x = 0; x < KEYS; ++x) {
-                const unsigned e = edge(u, v);
-                const int be = max(cb[x], 0);
-                if (Gt) {
-                  g[u][v][x] = Gc[(e * 3 + d) * NK + be];
-                } else {
-                  const int j = (col + c0)[e], jc = (unsigned)j < (unsigned)n ? j : 0;
-                  float dx, dy, dz;
-                  sh_poly_grad<float>(t, be, pos[3 * i] - pos[3 * jc], pos[3 * i + 1] - pos[3 * jc + 1],
-                                      pos[3 * i + 2] - pos[3 * jc + 2], dx, dy, dz);
-                  g[u][v][x] = d == 0 ? dx : d == 1 ? dy : dz;
-                }
-              }
+              for (int x = 0; x < KEYS; ++x) g[u][v][x] = Gc[(edge(u, v) * 3 + d) * NK + max(cb[x], 0)];
 #pragma unroll
           for (int u = 0; u < T; ++u) {
             float p[4];
@@ -367,6 +377,23 @@ void k_edge_grad(DevTables t, const float* __restrict__ pos, const float* __rest
       }
     }
   }
+}
+
+// The receivers of each pass of `pass` edges: the first that has one of its
+// edges, and one past the last (the last row that starts at or before an edge
+// holds it).
+__global__ __launch_bounds__(256) void k_edge_ranges(const int64_t* __restrict__ row_ptr, int n, int64_t n_edges,
+                                                     int64_t pass, int passes, int* __restrict__ range) {
+  const int p = (blockIdx.x * 256 + threadIdx.x) / 2, last = threadIdx.x & 1;
+  if (p >= passes) return;
+  const int64_t e = last ? min((p + 1) * pass, n_edges) - 1 : p * pass;
+  int i = 0;
+  for (int hi = n; hi - i > 1;) {
+    const int mid = i + (hi - i) / 2;
+    if (row_ptr[mid] <= e) i = mid;
+    else hi = mid;
+  }
+  range[2 * p + last] = i + last;
 }
 
 // gedge = the sum of the heads' parts, in order.
@@ -424,11 +451,11 @@ __global__ __launch_bounds__(256) void k_force_gather(const int64_t* __restrict_
 
 }  // namespace
 
-hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* Re, const float* Gt, const float* feat,
-                            const float* gy, const int64_t* row_ptr, const int32_t* col, const float* alpha,
-                            const int32_t* order, int n, int C, int H, int64_t n_edges, const float* coef,
-                            float* galpha, float* gpart, float* gedge, hipStream_t s) {
-  if (n == 0 || n_edges == 0 || (!galpha && !gedge)) return hipSuccess;
+hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float* feat, const float* gy,
+                            const int64_t* row_ptr, const int32_t* col, const float* alpha, const int32_t* order,
+                            int n, int C, int H, int64_t n_edges, int64_t lo, int64_t hi, const int* range,
+                            const float* coef, float* galpha, float* gpart, float* gedge, hipStream_t s) {
+  if (n == 0 || hi <= lo || (!galpha && !gedge)) return hipSuccess;
   const int dh = C / H, P = dh % 16 == 0 ? 1 : dh % 8 == 0 ? 2 : 4;  // the widest group that divides a head
   int lg = std::max(1, std::min(32 / dh, H));  // heads of one 128-byte line
   while (H % lg) --lg;
@@ -436,14 +463,13 @@ hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* R
 #define E2F_G(LL, PP, LT, TT)                                                                                     \
   do {                                                                                                            \
     constexpr AggMap M = agg_map(LL);                                                                          \
-    /* receivers a wave: up to eight, as long as every CU has work (they share the table) */                      \
-    const int rpw = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)n * H / (256 * 16)));                 \
+    const int rpw = grad_rpw(n, H);                                                                               \
     const int nset = (n + kGradWaves * rpw - 1) / (kGradWaves * rpw);                                             \
     const int64_t per = ((int64_t)nset * H + 7) / 8;                                                              \
     if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                        \
     k_edge_grad<LL, PP, LT, TT><<<(unsigned)(8 * per), 64 * kGradWaves, LT ? M.nk * M.ng * 256 : 0, s>>>(         \
-        t, pos, Re, Gt, feat, gy, row_ptr, col, alpha, order, n, rpw, nset, lg, (int)per, C, H, n_edges, coef,    \
-        galpha, out);                                                                                             \
+        Re, Gt, feat, gy, row_ptr, col, alpha, order, n, rpw, nset, lg, (int)per, C, H, lo, hi,                   \
+        range, coef, galpha, out);                                                                                \
   } while (0)
 #define E2F_GP(LL, LT, TT)                    \
   do {                                        \
@@ -456,7 +482,7 @@ hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* R
     if (n_edges <= (int64_t)n * 24) E2F_GP(LL, LT, 2);         \
     else E2F_GP(LL, LT, grad_tiles(LL));                       \
     break;
-  switch (t.L) {
+  switch (L) {
     E2F_GL(0, false) E2F_GL(1, false) E2F_GL(2, true) E2F_GL(3, true) E2F_GL(4, true) E2F_GL(5, false)
     E2F_GL(6, false)
     default: return hipErrorInvalidValue;
@@ -465,9 +491,16 @@ hipError_t launch_edge_grad(const DevTables& t, const float* pos, const float* R
 #undef E2F_GP
 #undef E2F_G
   if (hipError_t e = hipGetLastError(); e != hipSuccess || out == gedge) return e;
-  const int64_t blocks = (n_edges * 3 + 255) / 256;
+  const int64_t blocks = ((hi - lo) * 3 + 255) / 256;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  k_edge_sum<<<(unsigned)blocks, 256, 0, s>>>(gpart, H, n_edges * 3, gedge);
+  k_edge_sum<<<(unsigned)blocks, 256, 0, s>>>(gpart, H, (hi - lo) * 3, gedge);
+  return hipGetLastError();
+}
+
+hipError_t launch_edge_ranges(const int64_t* row_ptr, int n, int64_t n_edges, int64_t pass, int passes, int* range,
+                              hipStream_t s) {
+  if (n == 0 || passes <= 0) return hipSuccess;
+  k_edge_ranges<<<(unsigned)((2 * (int64_t)passes + 255) / 256), 256, 0, s>>>(row_ptr, n, n_edges, pass, passes, range);
   return hipGetLastError();
 }
 

@@ -506,7 +506,8 @@ __global__ __launch_bounds__(256) void k_plan_sh(DevTables t, const float* __res
   for (int q = threadIdx.x; q < cnt * NK; q += 256) dst[q] = buf[(q / NK) * NKP + q % NK];
 }
 
-// Harmonics of every edge's vector r_i - r_j, Re [E][NK] float32 (evaluated in
+// Harmonics of every edge's vector r_i - r_j, Re [E][NK] float32, for the edges
+// from first on (evaluated in
 // float64 from the positions, whose difference is exact there; with UNIT those
 // of the unit vector, the zero vector's at r = 0).  A thread per edge; its
 // receiver is the last row that starts at or before it, found by bisection
@@ -516,13 +517,13 @@ __global__ __launch_bounds__(256) void k_plan_sh(DevTables t, const float* __res
 template <int L, bool UNIT>
 __global__ __launch_bounds__(256) void k_edge_sh(DevTables t, const float* __restrict__ pos,
                                                  const int64_t* __restrict__ row_ptr,
-                                                 const int32_t* __restrict__ col, int n, int64_t n_edges,
-                                                 float* __restrict__ Re) {
+                                                 const int32_t* __restrict__ col, int n, int64_t first,
+                                                 int64_t count, float* __restrict__ Re) {
   constexpr int NK = (L + 1) * (L + 1), NKP = NK | 1;  // odd row stride: conflict-free LDS stores
   __shared__ float buf[256 * NKP];
-  const int64_t e0 = (int64_t)blockIdx.x * 256, e = e0 + threadIdx.x;
-  const int cnt = (int)min((int64_t)256, n_edges - e0);
-  if (e < n_edges) {
+  const int64_t e0 = (int64_t)blockIdx.x * 256, e = first + e0 + threadIdx.x;
+  const int cnt = (int)min((int64_t)256, count - e0);
+  if ((int)threadIdx.x < cnt) {
     int i = 0;
     for (int hi = n; hi - i > 1;) {
       const int mid = (i + hi) >> 1;
@@ -685,15 +686,15 @@ hipError_t launch_plan_sh(const DevTables& t, const float* pos, const int32_t* r
 }
 
 hipError_t launch_edge_sh(const DevTables& t, const float* pos, const int64_t* row_ptr, const int32_t* col, int n,
-                          int64_t n_edges, bool unit, float* Re, hipStream_t s) {
-  const int64_t blocks = (n_edges + 255) / 256;
+                          int64_t first, int64_t count, bool unit, float* Re, hipStream_t s) {
+  const int64_t blocks = (count + 255) / 256;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
   switch (t.L) {
 #define E2F_SH(LL)                                                                                              \
   case LL:                                                                                                      \
-    if (unit) k_edge_sh<LL, true><<<(unsigned)blocks, 256, 0, s>>>(t, pos, row_ptr, col, n, n_edges, Re);        \
-    else k_edge_sh<LL, false><<<(unsigned)blocks, 256, 0, s>>>(t, pos, row_ptr, col, n, n_edges, Re);            \
+    if (unit) k_edge_sh<LL, true><<<(unsigned)blocks, 256, 0, s>>>(t, pos, row_ptr, col, n, first, count, Re);   \
+    else k_edge_sh<LL, false><<<(unsigned)blocks, 256, 0, s>>>(t, pos, row_ptr, col, n, first, count, Re);       \
     break;
     E2F_SH(0) E2F_SH(1) E2F_SH(2) E2F_SH(3) E2F_SH(4) E2F_SH(5) E2F_SH(6)
 #undef E2F_SH

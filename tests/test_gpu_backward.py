@@ -199,11 +199,88 @@ def test_backward_without_edges(e2f, ctx):
 
 
 def test_backward_forces_without_gradient_table(e2f, ctx, monkeypatch):
-    # the per-edge kernel evaluates the harmonic gradients itself when the
-    # per-edge table would exceed its memory cap; force that path here
+    # the per-edge products run in passes of edges whose tables fit a memory
+    # cap; force the smallest passes here
     monkeypatch.setenv("E2F_GEOM_GT", "0")
     rng = np.random.default_rng(41)
     pos = syn.quantize(rng.uniform(0, 14, size=(400, 3)))
     rp, ci = o.neighbor_list(pos, 5.0)
     check(e2f, ctx, pos, rp, ci, 4, 32, 2, 5.0, 42)
     check(e2f, ctx, pos, rp, ci, 6, 16, 4, 5.0, 43)
+
+
+def knn_inputs(e2f, ctx, n, k, L, C, H, seed):
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    pos = torch.rand(n, 3, device="cuda:0", generator=g) * (n / 0.1) ** (1.0 / 3.0)
+    rp, ci = e2f.e2f_knn_graph(ctx, pos, k)
+    feat, gout = (torch.randn(n, (L + 1) ** 2, C, device="cuda:0", generator=g) for _ in range(2))
+    alpha = torch.rand(ci.numel(), H, device="cuda:0", generator=g)
+    return pos, feat, gout, rp, ci, alpha
+
+
+@pytest.mark.parametrize("L,C,H", [(1, 16, 1), (4, 24, 3), (5, 8, 2), (6, 16, 1)])
+def test_backward_passes_are_bitwise(e2f, ctx, monkeypatch, L, C, H):
+    # every edge's products are its own, so where a pass ends (inside a row of
+    # 50 edges: 16,384 is no multiple of 50) does not matter
+    args = knn_inputs(e2f, ctx, 1200, 50, L, C, H, 90 + L)
+    print("passes: L %d C %d H %d" % (L, C, H), flush=True)
+    one = e2f.e2f_wigner6j_conv_backward(ctx, *args, L, H, 8.0, want_pos=True)
+    monkeypatch.setenv("E2F_GEOM_GT", "0")
+    for kw in (dict(), dict(want_alpha=False), dict(want_feat=False)):
+        got = e2f.e2f_wigner6j_conv_backward(ctx, *args, L, H, 8.0, want_pos=True, **kw)
+        for a, b in zip(one, got):
+            assert b is None or torch.equal(a, b)
+
+
+def test_backward_passes_keep_time_and_memory(e2f, monkeypatch):
+    # position gradients beyond the cap: a table per pass, evaluated once per
+    # edge.  (Evaluated in the per-edge kernel, 3 H times per edge, they took
+    # 13 times as long as with a table.)
+    L, C, H = 4, 32, 8
+    c = e2f.e2f_create(L, 0)
+    try:
+        args = knn_inputs(e2f, c, 8000, 64, L, C, H, 95)
+        e2f.e2f_wigner6j_prepare(c, L, C, H, 8.0)
+        E = args[4].numel()
+
+        def call():
+            return e2f.e2f_wigner6j_conv_backward(c, *args, L, H, 8.0, want_feat=False, want_pos=True)
+
+        def ms():
+            best = 1e9
+            for _ in range(4):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                call()
+                b.record()
+                b.synchronize()
+                best = min(best, a.elapsed_time(b))
+            return best
+
+        # memory of the capped call: the cap, and what an edge needs whole (six
+        # ints, a force vector, the weights of the transposed graph, the sort)
+        cap = 64 << 20
+        monkeypatch.setenv("E2F_GEOM_GT", str(cap))
+        out = call()
+        del out
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        f = e2f.e2f_create(L, 0)
+        e2f.e2f_wigner6j_prepare(f, L, C, H, 8.0)
+        free = torch.cuda.mem_get_info()[0]
+        e2f.e2f_wigner6j_conv_backward(f, *args, L, H, 8.0, want_feat=False, want_pos=True)
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        used = free - torch.cuda.mem_get_info()[0]
+        f.close()
+        capped = ms()
+        monkeypatch.setenv("E2F_GEOM_GT", "0")
+        small = ms()
+        monkeypatch.delenv("E2F_GEOM_GT")
+        whole = ms()
+        print("%d edges: one pass %.3f ms, passes of 64 MiB %.3f, smallest passes %.3f; %.0f MiB capped"
+              % (E, whole, capped, small, used / 2 ** 20))
+        assert used <= cap + E * (64 + 4 * H) + (16 << 20)
+        assert capped <= 1.5 * whole and small <= 3.0 * whole
+    finally:
+        c.close()
