@@ -524,7 +524,9 @@ constexpr size_t kEdgePassBytes = (size_t)4 << 30;
 constexpr int64_t kEdgePassMin = 16384;
 
 // Byte layout of the forward's workspace: the plan and per-edge arrays (a
-// fixed part), then S for a slice of receivers.
+// fixed part), then S for a slice of receivers.  lean: only what the fused form
+// reads and writes (the order, Re, y), for every receiver at once; callers'
+// workspaces keep the layout whose sizes the size queries give.
 struct FwdLayout {
   size_t stats = 0, dmin = 0, grid = 0, tile_of = 0, keys = 0, keys_out = 0, vals = 0, order = 0, sort_tmp = 0;
   size_t sort_b = 0, Re = 0, Rr = 0, alpha_hm = 0, erows = 0, y = 0, S = 0;
@@ -557,7 +559,7 @@ int fused_row_floats(const e2f_conv_params* p) {
   return fl;
 }
 
-FwdLayout fwd_layout(const e2f_conv_params* p, int n, int64_t E, bool have_alpha) {
+FwdLayout fwd_layout(const e2f_conv_params* p, int n, int64_t E, bool have_alpha, bool lean = false) {
   const int L = p->lmax, nk = nk_of(L), C = p->channels, H = p->heads;
   const bool ynorm = p->y_norm != 0;
   FwdLayout f;
@@ -578,14 +580,15 @@ FwdLayout fwd_layout(const e2f_conv_params* p, int n, int64_t E, bool have_alpha
   f.sort_b = plan_sort_tmp_bytes(std::max(n, 1));
   f.sort_tmp = take(f.sort_b);
   f.Re = take(sizeof(float) * (size_t)(E + kEdgePad) * nk);
-  f.Rr = take(sizeof(double) * (size_t)n * nk);
+  f.Rr = take(lean ? 0 : sizeof(double) * (size_t)n * nk);
   const size_t na = ynorm ? (size_t)(L + 1) : (have_alpha ? 1 : 0);
-  f.alpha_hm = take(sizeof(float) * ((size_t)E * H * na + kEdgePad));
-  f.erows = take(sizeof(int32_t) * (size_t)E);
+  f.alpha_hm = take(lean ? 0 : sizeof(float) * ((size_t)E * H * na + kEdgePad));
+  f.erows = take(lean ? 0 : sizeof(int32_t) * (size_t)E);
   f.y = take(p->mix_w ? sizeof(float) * (size_t)n * nk * C : 0);
-  if (fused_sizes(p, n)) take(sizeof(float) * (size_t)n * C * 6 * ((nk + 3) / 4));
+  if (!lean && fused_sizes(p, n)) take(sizeof(float) * (size_t)n * C * 6 * ((nk + 3) / 4));
   f.S = off;
   f.fixed = off;
+  if (lean) return f;  // (s_row = 0)
   // per receiver of a slice (fused_sizes)
   f.s_row = fused_sizes(p, n) ? sizeof(float) * (size_t)fused_row_floats(p)
                               : al256(sizeof(float) * (size_t)node_tp_dim(L) * C);
@@ -612,7 +615,7 @@ constexpr double kYnormTileScale = 2.31;
 e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos, const int32_t* graph_id,
                         const float* feat, int32_t n, const int64_t* row_ptr, const int32_t* col_idx, int64_t n_edges,
                         const float* alpha, float* out, void* workspace, size_t workspace_bytes, void* stream,
-                        bool allow_upload) {
+                        bool allow_upload, bool lean = false) {
   e2f_status rs = check_conv(ctx, p, pos, feat, n, row_ptr, col_idx, n_edges, out);
   if (rs != E2F_OK) return rs;
   hipStream_t s = (hipStream_t)stream;
@@ -635,7 +638,7 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
   }
   if (n == 0) return E2F_OK;
   const bool ynorm = p->y_norm != 0;
-  const FwdLayout f = fwd_layout(p, n, n_edges, alpha != nullptr);
+  const FwdLayout f = fwd_layout(p, n, n_edges, alpha != nullptr, lean);
   if (n_edges > 0) {
     if (!workspace) return fail(E2F_EINVAL, "workspace is NULL");
     if ((uintptr_t)workspace % 256) return fail(E2F_EINVAL, "workspace must be 256-byte aligned");
@@ -660,7 +663,7 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
   float* alpha_hm = (alpha || ynorm) ? (float*)(ws + f.alpha_hm) : nullptr;
   float* y = p->mix_w ? (float*)(ws + f.y) : out;
   float* S = (float*)(ws + f.S);
-  const int64_t slice = std::min<int64_t>(n, (int64_t)((workspace_bytes - f.fixed) / f.s_row));
+  const int64_t slice = lean ? n : std::min<int64_t>(n, (int64_t)((workspace_bytes - f.fixed) / f.s_row));
   int64_t slices = 0;
   const double side = (p->tile_side > 0.0f ? (double)p->tile_side : kTileCutoffs[L] * (double)p->cutoff) * kGrid;
   if (fused) {
@@ -1305,10 +1308,11 @@ e2f_status e2f_wigner6j_conv_backward(e2f_ctx* ctx, const e2f_conv_params* p, co
     pt.mix_w = nullptr;
     // the forward on the transposed graph, in a workspace of the context's
     // own (the backward's buffers, which it reads, stay where they are)
-    const size_t fb = fwd_layout(&pt, n, n_edges, alpha != nullptr).total(n);
+    const bool lean = p->form != E2F_FORM_SPLIT;
+    const size_t fb = fwd_layout(&pt, n, n_edges, alpha != nullptr, lean).total(n);
     if ((rs = ensure(ctx, ctx->c, fb, s)) != E2F_OK) return rs;
     return forward_impl(ctx, &pt, pos, graph_id, gy, n, rowT, colT, n_edges, alpha ? alphaT : nullptr, grad_feat,
-                        ctx->c.p, ctx->c.n, stream, true);
+                        ctx->c.p, ctx->c.n, stream, true, lean);
   }
   return E2F_OK;
 }
