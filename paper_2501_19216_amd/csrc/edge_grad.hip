@@ -123,6 +123,10 @@ constexpr bool grad_split(int L, int P) { return L == 4 || (L > 4 && P == 1); }
 // lines its waves gather stay in its L2; gedge is therefore written per head
 // ([H][edges][3]) and summed over the heads by k_edge_sum.
 // T: grad_tiles, or 2 for graphs of short rows (more waves share a SIMD).
+// W: groups of DH channels taken together, the same component of both in turn:
+// 2 for heads of 32 channels and more, whose 128-byte lines hold two groups (a
+// pass per group fetched each line twice: attention gradient at 20,000 atoms,
+// 80 neighbours, L = 3, four heads of 32, 3.65 -> 2.04 ms).
 //
 // A launch covers the edges lo .. hi - 1 (a row that crosses the range gives
 // its part: every edge's products are its own).  Re, Gt and gedge hold these
@@ -131,8 +135,8 @@ constexpr bool grad_split(int L, int P) { return L == 4 || (L > 4 && P == 1); }
 // n.  (Workgroups dealt out over all n, those without an edge leaving at once:
 // the edges of a pass then fall to a few XCDs only, 512,000 edges in four
 // passes 4.1 ms against 1.3 in one.)
-template <int L, int P, bool LT, int T>
-__global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu(T > 2 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
+template <int L, int P, int W, int NWV, int T>
+__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(T > 2 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
 void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, const float* __restrict__ feat,
                  const float* __restrict__ gy, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                  const float* __restrict__ alpha, const int32_t* __restrict__ order, int n, int rpw, int nset, int lg,
@@ -141,6 +145,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
                  float* __restrict__ galpha, float* __restrict__ gedge) {
   constexpr AggMap M = agg_map(L);
   constexpr int NK = M.nk, NG = M.ng, KEYS = M.keys, DH = 16 / P;
+  constexpr bool LT = L >= 2 && L <= 4;
   extern __shared__ float sm[];
   const float* tab = LT ? sm : coef;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -149,7 +154,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
   if (range) {  // (as launch_edge_grad has it for all n)
     first = range[0], nrec = range[1] - first;
     rpw = grad_rpw(nrec, H);
-    nset = (nrec + kGradWaves * rpw - 1) / (kGradWaves * rpw);
+    nset = (nrec + NWV * rpw - 1) / (NWV * rpw);
     per_xcd = (int)(((int64_t)nset * H + 7) / 8);
     if ((int)(blockIdx.x / 8) >= per_xcd) return;
   }
@@ -157,13 +162,16 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
   const int h = item / (nset * lg) * lg + item % lg, set = item / lg % nset;
   if (h >= H) return;
   if constexpr (LT) {
-    constexpr int NV = NK * NG * 16, IT = (NV + 64 * kGradWaves - 1) / (64 * kGradWaves);
-    float4 v[IT];  // every load in flight before the first store
+    constexpr int NV = NK * NG * 16, NT = 64 * NWV, IT = (NV + NT - 1) / NT, B = IT < 20 ? IT : 20;
+#pragma unroll 1
+    for (int e0 = threadIdx.x; e0 < NV; e0 += B * NT) {
+      float4 v[B];  // every load in flight before the first store
 #pragma unroll
-    for (int x = 0; x < IT; ++x) v[x] = ((const float4*)coef)[min((int)threadIdx.x + x * 64 * kGradWaves, NV - 1)];
+      for (int x = 0; x < B; ++x) v[x] = ((const float4*)coef)[min(e0 + x * NT, NV - 1)];
 #pragma unroll
-    for (int x = 0; x < IT; ++x)
-      if ((int)threadIdx.x + x * 64 * kGradWaves < NV) ((float4*)sm)[threadIdx.x + x * 64 * kGradWaves] = v[x];
+      for (int x = 0; x < B; ++x)
+        if (e0 + x * NT < NV) ((float4*)sm)[e0 + x * NT] = v[x];
+    }
     __syncthreads();
   }
   // the lane's component o of every group, its column be of every key (-1: none)
@@ -186,7 +194,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
   // bounds of a receiver (clamped to the range; hi < 2^31), loaded while the
   // one before is worked on
   auto receiver = [&](int k, int& i, int64_t& b0, int64_t& b1) {
-    const int at = first + min((set * rpw + min(k, rpw - 1)) * kGradWaves + wave, nrec - 1);
+    const int at = first + min((set * rpw + min(k, rpw - 1)) * NWV + wave, nrec - 1);
     i = order ? order[at] : at;
     b0 = row_ptr[i], b1 = row_ptr[i + 1];
   };
@@ -194,7 +202,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
   int64_t b0, b1;
   receiver(0, in, b0, b1);
   for (int k = 0; k < rpw; ++k) {
-    if ((set * rpw + k) * kGradWaves + wave >= nrec) return;
+    if ((set * rpw + k) * NWV + wave >= nrec) return;
     const int i = __builtin_amdgcn_readfirstlane(in);
     const int e0 = __builtin_amdgcn_readfirstlane((int)max(lo, min(b0, hi)));
     const int e1 = __builtin_amdgcn_readfirstlane((int)max((int64_t)e0, min(b1, hi)));
@@ -217,15 +225,22 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
       for (int u = 0; u < T; ++u)
 #pragma unroll
         for (int x = 0; x < KEYS; ++x) X[u][x] = (v4f){0.f, 0.f, 0.f, 0.f};
-      for (int un = 0; un < uph; ++un) {
-        const int hc = h * dh + un * DH;
-        float ga[NG];
+      for (int un = 0; un < uph; un += W) {
+        const bool pair = W == 2 && un + 1 < uph;
+        int hc[W];
+        float ga[W][NG];
 #pragma unroll
-        for (int g = 0; g < NG; ++g) ga[g] = gyi[(size_t)go[g] * C + hc + l16 % DH];
+        for (int w = 0; w < W; ++w) {
+          hc[w] = h * dh + (un + (pair ? w : 0)) * DH;
+#pragma unroll
+          for (int g = 0; g < NG; ++g) ga[w][g] = gyi[(size_t)go[g] * C + hc[w] + l16 % DH];
+        }
         // (waited for here: loads return in order, and a wait inside the loop
         // would be one for the features of its next step)
 #pragma unroll
-        for (int g = 0; g < NG; ++g) asm volatile("" : "+v"(ga[g]));
+        for (int w = 0; w < W; ++w)
+#pragma unroll
+          for (int g = 0; g < NG; ++g) asm volatile("" : "+v"(ga[w][g]));
 #pragma unroll
         for (int y = 0; y < KEYS; ++y) {
           // members of key y, P at a time
@@ -234,6 +249,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
           for (int z = 0; z < 16; ++z) ny += M.rows[y][z] >= 0 ? 1 : 0;
           const int steps = (ny + P - 1) / P;
           auto member = [&](int z) {  // component z of key y (uniform or per lane)
+            if constexpr (KEYS == 1 && W == 2) return z;  // (without it the wide form spills scalars at L = 3)
             int q = M.rows[y][0];
 #pragma unroll
             for (int m = 1; m < 16; ++m)
@@ -243,13 +259,13 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
           // unconditional loads (a tile past nt repeats the row's last sender),
           // two register sets in turn: the waits then count exactly
           float4 fa[T], fb[T];
-          auto load = [&](int s, float4* d) {
+          auto load = [&](int s, int w, float4* d) {
             const int q = member(min(s * P + pl, ny - 1));
-            const unsigned off = (unsigned)(q * C + hc);
+            const unsigned off = (unsigned)(q * C + hc[w]);
 #pragma unroll
             for (int u = 0; u < T; ++u) d[u] = *(const float4*)(fj[u] + off);
           };
-          auto step = [&](int s, const float4* f) {
+          auto step = [&](int s, int w, const float4* f) {
             v4f z[KEYS];
 #pragma unroll
             for (int x = 0; x < KEYS; ++x) z[x] = (v4f){0.f, 0.f, 0.f, 0.f};
@@ -259,7 +275,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
               const float* kq = tab + (size_t)member(s * P + p) * NG * 64 + lane;
 #pragma unroll
               for (int g = 0; g < NG; ++g) {
-                const float a = P == 1 || l16 / DH == p ? ga[g] : 0.0f;
+                const float a = P == 1 || l16 / DH == p ? ga[w][g] : 0.0f;
                 z[M.gkey[g]] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, kq[g * 64], z[M.gkey[g]], 0, 0, 0);
               }
             }
@@ -298,13 +314,14 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
                 }
             }
           };
-          load(0, fa);
+          load(0, 0, fa);
+          const int odd = pair ? 0 : 1;  // fb: the other group's, or the next component
 #pragma unroll 1
-          for (int s = 0; s < steps; s += 2) {
-            load(s + 1, fb);  // (past the end: the last component again)
-            step(s, fa);
-            load(s + 2, fa);
-            if (s + 1 < steps) step(s + 1, fb);
+          for (int s = 0; s < steps; s += 1 + odd) {
+            load(s + odd, W - 1, fb);  // (past the end: the last component again)
+            step(s, 0, fa);
+            load(s + 1 + odd, 0, fa);
+            if (s + odd < steps) step(s + odd, W - 1, fb);
           }
         }
       }
@@ -460,35 +477,37 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
   int lg = std::max(1, std::min(32 / dh, H));  // heads of one 128-byte line
   while (H % lg) --lg;
   float* out = gedge && H > 1 ? gpart : gedge;
-#define E2F_G(LL, PP, LT, TT)                                                                                     \
+  const bool few = n_edges <= (int64_t)n * 24;
+#define E2F_G(LL, PP, WW, NN, TT)                                                                                 \
   do {                                                                                                            \
-    constexpr AggMap M = agg_map(LL);                                                                          \
+    constexpr AggMap M = agg_map(LL);                                                                             \
+    constexpr int nw = NN;                                                                                        \
     const int rpw = grad_rpw(n, H);                                                                               \
-    const int nset = (n + kGradWaves * rpw - 1) / (kGradWaves * rpw);                                             \
+    const int nset = (n + nw * rpw - 1) / (nw * rpw);                                                             \
     const int64_t per = ((int64_t)nset * H + 7) / 8;                                                              \
     if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                        \
-    k_edge_grad<LL, PP, LT, TT><<<(unsigned)(8 * per), 64 * kGradWaves, LT ? M.nk * M.ng * 256 : 0, s>>>(         \
-        Re, Gt, feat, gy, row_ptr, col, alpha, order, n, rpw, nset, lg, (int)per, C, H, lo, hi,                   \
-        range, coef, galpha, out);                                                                                \
+    k_edge_grad<LL, PP, WW, nw, TT><<<(unsigned)(8 * per), 64 * nw, LL >= 2 && LL <= 4 ? M.nk * M.ng * 256 : 0, s>>>(        \
+        Re, Gt, feat, gy, row_ptr, col, alpha, order, n, rpw, nset, lg, (int)per, C, H, lo, hi, range, coef,      \
+        galpha, out);                                                                                             \
   } while (0)
-#define E2F_GP(LL, LT, TT)                    \
-  do {                                        \
-    if (P == 1) E2F_G(LL, 1, LT, TT);         \
-    else if (P == 2) E2F_G(LL, 2, LT, TT);    \
-    else E2F_G(LL, 4, LT, TT);                \
+#define E2F_GT(LL, PP, WW, NN)                                 \
+  do {                                                         \
+    if (few) E2F_G(LL, PP, WW, NN, 2);                         \
+    else E2F_G(LL, PP, WW, NN, grad_tiles(LL));            \
   } while (0)
-#define E2F_GL(LL, LT)                                         \
+#define E2F_GL(LL)                                             \
   case LL:                                                     \
-    if (n_edges <= (int64_t)n * 24) E2F_GP(LL, LT, 2);         \
-    else E2F_GP(LL, LT, grad_tiles(LL));                       \
+    if (P == 1 && dh >= 32) E2F_GT(LL, 1, 2, kGradWaves);                  \
+    else if (P == 1) E2F_GT(LL, 1, 1, kGradWaves);                         \
+    else if (P == 2) E2F_GT(LL, 2, 1, kGradWaves);                         \
+    else E2F_GT(LL, 4, 1, kGradWaves);                                     \
     break;
   switch (L) {
-    E2F_GL(0, false) E2F_GL(1, false) E2F_GL(2, true) E2F_GL(3, true) E2F_GL(4, true) E2F_GL(5, false)
-    E2F_GL(6, false)
+    E2F_GL(0) E2F_GL(1) E2F_GL(2) E2F_GL(3) E2F_GL(4) E2F_GL(5) E2F_GL(6)
     default: return hipErrorInvalidValue;
   }
 #undef E2F_GL
-#undef E2F_GP
+#undef E2F_GT
 #undef E2F_G
   if (hipError_t e = hipGetLastError(); e != hipSuccess || out == gedge) return e;
   const int64_t blocks = ((hi - lo) * 3 + 255) / 256;

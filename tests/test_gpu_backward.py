@@ -119,6 +119,20 @@ def test_backward_per_edge_products(e2f, ctx, L, C, H, rc):
     check(e2f, ctx, pos, rp, ci, L, C, H, rc, 70 + L)
 
 
+# heads of 32 channels and more (two groups of 16 channels in turn, an odd number
+# of groups among them), and enough heads and receivers for workgroups of eight
+# waves at L = 5, 6
+@pytest.mark.parametrize("L,C,H,n", [(1, 96, 2, 110), (2, 64, 1, 110), (3, 96, 3, 110), (4, 96, 3, 110),
+                                     (5, 80, 1, 110), (6, 48, 1, 110), (5, 32, 8, 160), (5, 64, 8, 160),
+                                     (6, 192, 6, 180)])
+@pytest.mark.parametrize("rc", [3.0, 5.0])
+def test_backward_per_edge_groups(e2f, ctx, L, C, H, n, rc):
+    rng = np.random.default_rng(170 + L + C)
+    pos = syn.quantize(rng.uniform(0, 9, size=(n, 3)))
+    rp, ci = o.neighbor_list(pos, rc)
+    check(e2f, ctx, pos, rp, ci, L, C, H, rc, 170 + L)
+
+
 @pytest.mark.parametrize("H", [8, 2])
 def test_backward_graphs_and_single_outputs(e2f, ctx, H):
     inp = syn.make_inputs(syn.WORKLOADS["molecules256x30_L3"], n_atoms=40 * 30)
