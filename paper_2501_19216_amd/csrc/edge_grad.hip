@@ -84,6 +84,12 @@ __device__ __forceinline__ float sum16(float v) {
 // Row tiles of 16 edges a wave holds at a time: X takes 4 registers per tile
 // and key, the features of two steps eight per tile.
 constexpr int grad_tiles(int L) { return L <= 4 ? 6 : 3; }
+// Waves a workgroup, which share the coupling table in LDS: 45 KB at L = 4, 108
+// and 159 KB at L = 5, 6, where one workgroup has the CU to itself; it has four
+// waves there too where eight would leave half of the CUs without one.  (Read
+// from L2 at L = 5, 6, each read of the table waited for the features' loads
+// before it, which return in order: 20,000 atoms, 80 neighbours,
+// L = 5, 8 heads, C = 64 16.1 -> 7.2 ms, C = 32 19.2 -> 6.2.)
 constexpr int kGradWaves = 4;
 // Receivers a wave takes one after another: up to eight, as long as every CU
 // has work (they share the table).
@@ -145,7 +151,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
                  float* __restrict__ galpha, float* __restrict__ gedge) {
   constexpr AggMap M = agg_map(L);
   constexpr int NK = M.nk, NG = M.ng, KEYS = M.keys, DH = 16 / P;
-  constexpr bool LT = L >= 2 && L <= 4;
+  constexpr bool LT = L >= 2;  // (a table of up to 1 KB stays in L1)
   extern __shared__ float sm[];
   const float* tab = LT ? sm : coef;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -477,6 +483,7 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
   int lg = std::max(1, std::min(32 / dh, H));  // heads of one 128-byte line
   while (H % lg) --lg;
   float* out = gedge && H > 1 ? gpart : gedge;
+  const int64_t n_waves = (int64_t)n * H;
   const bool few = n_edges <= (int64_t)n * 24;
 #define E2F_G(LL, PP, WW, NN, TT)                                                                                 \
   do {                                                                                                            \
@@ -486,7 +493,7 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
     const int nset = (n + nw * rpw - 1) / (nw * rpw);                                                             \
     const int64_t per = ((int64_t)nset * H + 7) / 8;                                                              \
     if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                        \
-    k_edge_grad<LL, PP, WW, nw, TT><<<(unsigned)(8 * per), 64 * nw, LL >= 2 && LL <= 4 ? M.nk * M.ng * 256 : 0, s>>>(        \
+    k_edge_grad<LL, PP, WW, nw, TT><<<(unsigned)(8 * per), 64 * nw, LL >= 2 ? M.nk * M.ng * 256 : 0, s>>>(        \
         Re, Gt, feat, gy, row_ptr, col, alpha, order, n, rpw, nset, lg, (int)per, C, H, lo, hi, range, coef,      \
         galpha, out);                                                                                             \
   } while (0)
@@ -495,18 +502,24 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
     if (few) E2F_G(LL, PP, WW, NN, 2);                         \
     else E2F_G(LL, PP, WW, NN, grad_tiles(LL));            \
   } while (0)
+#define E2F_GN(LL, PP, WW)                                     \
+  do {                                                         \
+    if (LL <= 4 || n_waves <= 1024) E2F_GT(LL, PP, WW, kGradWaves);           \
+    else E2F_GT(LL, PP, WW, (LL <= 4 ? kGradWaves : 2 * kGradWaves));         \
+  } while (0)
 #define E2F_GL(LL)                                             \
   case LL:                                                     \
-    if (P == 1 && dh >= 32) E2F_GT(LL, 1, 2, kGradWaves);                  \
-    else if (P == 1) E2F_GT(LL, 1, 1, kGradWaves);                         \
-    else if (P == 2) E2F_GT(LL, 2, 1, kGradWaves);                         \
-    else E2F_GT(LL, 4, 1, kGradWaves);                                     \
+    if (P == 1 && dh >= 32) E2F_GN(LL, 1, 2);                  \
+    else if (P == 1) E2F_GN(LL, 1, 1);                         \
+    else if (P == 2) E2F_GN(LL, 2, 1);                         \
+    else E2F_GN(LL, 4, 1);                                     \
     break;
   switch (L) {
     E2F_GL(0) E2F_GL(1) E2F_GL(2) E2F_GL(3) E2F_GL(4) E2F_GL(5) E2F_GL(6)
     default: return hipErrorInvalidValue;
   }
 #undef E2F_GL
+#undef E2F_GN
 #undef E2F_GT
 #undef E2F_G
   if (hipError_t e = hipGetLastError(); e != hipSuccess || out == gedge) return e;
