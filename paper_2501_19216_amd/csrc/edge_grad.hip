@@ -81,9 +81,14 @@ __device__ __forceinline__ float sum16(float v) {
   return v;
 }
 
-// Row tiles of 16 edges a wave holds at a time: X takes 4 registers per tile
-// and key, the features of two steps eight per tile.
-constexpr int grad_tiles(int L) { return L <= 4 ? 6 : 3; }
+// Row tiles of 16 edges a wave holds at a time where rows are long: X takes 4
+// registers per tile and key, the features of two steps eight per tile.  A tile
+// past the chunk's end is loaded all the same (one line), so more is not better.
+// Attention gradient, 20,000 atoms, 8 heads, C = 64, with 2, 3, 4, 5 and 6 tiles:
+// 100 neighbours, L = 2 1.49, 1.37, 1.29, 1.37, 1.44 ms; L = 3 3.22, 3.23, 3.23,
+// 2.67, 2.39; L = 4 4.09, 5.39, 3.83, 3.54, 3.61; L = 5 10.8, 10.2, 9.3 (2, 3, 4);
+// 72 neighbours, L = 2 1.02, 0.93, 0.99, 0.93, 0.93.
+constexpr int grad_tiles(int L, int W) { return L <= 2 || L == 4 ? 5 : L == 3 ? 6 : L == 5 || W == 1 ? 4 : 3; }
 // Waves a workgroup, which share the coupling table in LDS: 45 KB at L = 4, 108
 // and 159 KB at L = 5, 6, where one workgroup has the CU to itself; it has four
 // waves there too where eight would leave half of the CUs without one.  (Read
@@ -219,7 +224,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
     for (int ch = 0; ch < chunks; ++ch) {
       const int64_t c0 = e0 + ch * per * 16;
       const int nt = min(per, all - ch * per);
-      const int cnt = (int)(e1 - c0);  // edges from here to the row's end
+      const int cnt = min((int)(e1 - c0), 16 * nt);  // edges of the chunk
       const float* fj[T];
 #pragma unroll
       for (int u = 0; u < T; ++u) {
@@ -262,7 +267,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
               if (M.rows[y][m] >= 0) q = z == m ? M.rows[y][m] : q;
             return q;
           };
-          // unconditional loads (a tile past nt repeats the row's last sender),
+          // unconditional loads (a tile past nt repeats the chunk's last sender, one line),
           // two register sets in turn: the waits then count exactly
           float4 fa[T], fb[T];
           auto load = [&](int s, int w, float4* d) {
@@ -484,7 +489,13 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
   while (H % lg) --lg;
   float* out = gedge && H > 1 ? gpart : gedge;
   const int64_t n_waves = (int64_t)n * H;
-  const bool few = n_edges <= (int64_t)n * 24;
+  // two tiles a wave where rows average at most two (20,000 atoms, C = 64, L =
+  // 4: 28 neighbours 1.07 ms with two tiles, 1.32 with five; 40 neighbours 1.95
+  // and 1.50), or, at L = 3 with heads of 8 and 4 channels, one and a half: more
+  // waves then evict the lines that the heads share (32 neighbours 796 us with two
+  // tiles, 727 with six); and at L <= 1 wherever the waves fill the chip (L = 1,
+  // 80 neighbours 441 us with two, 482 with six)
+  const bool few = n_edges <= (int64_t)n * (L == 3 && P > 1 ? 24 : 32) || (L <= 1 && n_waves > 16384);
 #define E2F_G(LL, PP, WW, NN, TT)                                                                                 \
   do {                                                                                                            \
     constexpr AggMap M = agg_map(LL);                                                                             \
@@ -500,7 +511,7 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
 #define E2F_GT(LL, PP, WW, NN)                                 \
   do {                                                         \
     if (few) E2F_G(LL, PP, WW, NN, 2);                         \
-    else E2F_G(LL, PP, WW, NN, grad_tiles(LL));            \
+    else E2F_G(LL, PP, WW, NN, grad_tiles(LL, WW));            \
   } while (0)
 #define E2F_GN(LL, PP, WW)                                     \
   do {                                                         \
