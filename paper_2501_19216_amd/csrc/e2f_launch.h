@@ -194,7 +194,7 @@ hipError_t launch_attention(const float* pos, const float* q, const float* k, in
 // Both per-edge backward products of the edges lo .. hi - 1 (either output may
 // be NULL): galpha[e][h] = sum_{c of h} <gy_i[.][c], (K_e h_j)[.][c]> [E][H] and
 // the position gradient per edge gedge [hi - lo][3] (from the edge lo on);
-// coef: grad_table, Re [hi - lo][nk]: launch_edge_sh (read for galpha), Gt [hi
+// coef: grad_table, Re [hi - lo][nk]: launch_edge_sh (read for galpha at L > 0), Gt [hi
 // - lo][3][nk]: launch_edge_shgrad (read for gedge); gpart [H][hi - lo][3]:
 // scratch of gedge when H > 1; order: the receivers, or NULL (by index); range:
 // the pass's entry of launch_edge_ranges, or NULL where the pass has every edge.

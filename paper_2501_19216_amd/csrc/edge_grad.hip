@@ -351,7 +351,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
 #pragma unroll
           for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int x = 0; x < KEYS; ++x) r[u][v][x] = Rc[edge(u, v) * NK + max(cb[x], 0)];
+            for (int x = 0; x < KEYS; ++x) r[u][v][x] = L == 0 ? 1.0f : Rc[edge(u, v) * NK + max(cb[x], 0)];
 #pragma unroll
         for (int u = 0; u < T; ++u) {
           float p[4];

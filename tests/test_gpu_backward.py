@@ -133,6 +133,23 @@ def test_backward_per_edge_groups(e2f, ctx, L, C, H, n, rc):
     check(e2f, ctx, pos, rp, ci, L, C, H, rc, 170 + L)
 
 
+@pytest.mark.parametrize("C,H", [(4, 1), (24, 3), (96, 2)])
+def test_backward_degree_zero(e2f, ctx, C, H):
+    # L = 0: the filter is 1, so grad_alpha is <gy_i, h_j> per head and no force is left
+    rng = np.random.default_rng(12)
+    pos = syn.quantize(rng.uniform(0, 9, size=(110, 3)))
+    rp, ci = o.neighbor_list(pos, 4.0)
+    feat, gout = (rng.standard_normal((110, 1, C)).astype(np.float32) for _ in range(2))
+    alpha = rng.uniform(0.05, 1.0, size=(len(ci), H)).astype(np.float32)
+    print("L 0 C %d H %d" % (C, H), flush=True)
+    _, ga, gp = e2f.e2f_wigner6j_conv_backward(ctx, gpu(pos), gpu(feat), gpu(gout), gpu(rp), gpu(ci), gpu(alpha), 0, H,
+                                               4.0, want_pos=True)
+    i = np.repeat(np.arange(110), np.diff(rp))
+    ref = (gout[i, 0].astype(np.float64) * feat[ci, 0]).reshape(len(ci), H, C // H).sum(2)
+    assert head_err(ga.cpu().numpy(), ref) <= TOL_F32
+    assert (gp.cpu().numpy() == 0).all()
+
+
 @pytest.mark.parametrize("H", [8, 2])
 def test_backward_graphs_and_single_outputs(e2f, ctx, H):
     inp = syn.make_inputs(syn.WORKLOADS["molecules256x30_L3"], n_atoms=40 * 30)
