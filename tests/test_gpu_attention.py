@@ -76,3 +76,21 @@ def test_attention_beyond_cutoff_and_empty_rows(e2f, ctx):
     got = got.cpu().numpy()
     assert np.any(ref == 0) and np.all(got[ref == 0] == 0)
     assert att_err(got, ref) <= TOL_ATT
+
+
+# one head (radial functions in registers) and several (in LDS, padded to a
+# multiple of 8), rows at the edges of an iteration, of the 64 edges evaluated
+# together and of the rows whose logits stay in registers
+@pytest.mark.parametrize("H,dk,R", [(1, 4, 3), (1, 5, 8), (1, 0, 32), (2, 4, 9), (4, 8, 2), (8, 0, 16), (13, 2, 31),
+                                    (64, 1, 7)])
+def test_attention_ragged_rows(e2f, ctx, H, dk, R):
+    rng = np.random.default_rng(40 + H + R)
+    n = 620
+    pos = syn.quantize(rng.uniform(0, 9, size=(n, 3)))
+    deg = [(0, 1, 2, 16, 17, 63, 64, 65, 128, 129, 511, 512, 513, 619)[i % 14] for i in range(n)]
+    rows = [np.sort(rng.choice(np.delete(np.arange(n), i), size=d, replace=False)) for i, d in enumerate(deg)]
+    rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    got, ref = run(e2f, ctx, pos, rp, np.concatenate(rows).astype(np.int32), 12.0, H, dk, R, 50 + H)
+    err = att_err(got.cpu().numpy(), ref)
+    print("ragged rows: H %d dk %d R %d: err %.3e" % (H, dk, R, err))
+    assert err <= TOL_ATT
