@@ -22,6 +22,14 @@ namespace e2f {
 namespace {
 
 
+// Orders the LDS accesses of a wave's lanes among each other: a fence over the
+// wavefront (the wave barrier alone orders scheduling, not memory).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int HP>
 __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos, const float* __restrict__ q,
                                                    const float* __restrict__ kf, int n, int H, int dk,
@@ -70,7 +78,7 @@ __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos
   // neighbours, 8 heads, d_k = 8, R = 8 149 -> 104 us, 300 atoms, 16 neighbours, R =
   // 32 11.0 -> 9.4)
   auto fill = [&](int64_t c) {
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();  // (the rows before have been read)
     const int64_t e = c + lane;
     if (e < e1) {
       const int j = col[e];
@@ -89,7 +97,7 @@ __global__ __launch_bounds__(256) void k_attention(const float* __restrict__ pos
       o[Rp] = envelope(d);
       o[Rp + 1] = __int_as_float(j);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   };
   auto dot = [&](int j) {
     const float* kj = kf + ((size_t)j * H + hc) * dk;
