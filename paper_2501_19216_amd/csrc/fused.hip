@@ -38,7 +38,7 @@ __device__ __forceinline__ v4f mfma_bf16(v4u a, v4u b, v4f c) {
 
 constexpr int kAggStride = 64;
 
-// One workgroup: rpw receivers of one group of 16 V channels (V = agg_vec),
+// One workgroup: rpw receivers of one group of 16 V channels (V = agg_vec or 1),
 // of any heads: the weight alpha_ij of a lane's head multiplies its features,
 // and the harmonics R of an edge serve every channel.  Edges are taken 16 a
 // step; edge 4 r + k4 of a step belongs to lane group k4 (r < 4).  A slot is a
@@ -61,7 +61,7 @@ constexpr int kAggStride = 64;
 // Edges past the row's end repeat its last sender with a weight of zero.
 //
 // OFF: unsigned where byte offsets into the features fit 32 bits.
-template <int L, bool SPLIT, typename OFF>
+template <int L, bool SPLIT, typename OFF, int V>
 __global__ __launch_bounds__(64 * agg_waves(L)) __attribute__((amdgpu_waves_per_eu(L >= 2 ? 2 : 3)))
 void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__ row_ptr,
                        const int32_t* __restrict__ col, const float* __restrict__ alpha, int n_edges,
@@ -69,7 +69,7 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
                        int nblk, int lg, int per_xcd, int C, int H, int n_nodes, const int* __restrict__ index,
                        const float4* __restrict__ coef, float* __restrict__ y) {
   constexpr AggMap M = agg_map(L);
-  constexpr int NK = M.nk, MT = M.mt, NW = M.nw, TW = M.tw, NG = M.ng, KEYS = M.keys, V = agg_vec(L);
+  constexpr int NK = M.nk, MT = M.mt, NW = M.nw, TW = M.tw, NG = M.ng, KEYS = M.keys;
   constexpr int NT = 64 * NW, NQ = (NG + 3) / 4, W = 16 * V;
   constexpr bool PIPE = MT == 2;
   constexpr int NST = (4 * NK + NT - 1) / NT;  // staging passes: a thread per (component, k4)
@@ -408,9 +408,22 @@ hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr
                                   float* y, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const bool wide = (double)n_nodes * nk_of(L) * C * 4.0 > 4.0e9;
+  // One channel a lane where two would leave half of the last column group
+  // empty, as long as that is dearer than the smaller groups (a group of 16 costs
+  // 0.55 of one of 32: even at nine).  20,000 atoms, 80 neighbours, L = 2: C = 4
+  // and 16 295 us with two channels a lane, 202 with one, C = 48 498 and 442, but
+  // C = 20 296 and 315, C = 32 297 and 316, C = 128 906 and 996; L = 5, C = 16 1.64
+  // and 1.00 ms, C = 48 3.12 and 2.78; 3,000 atoms, L = 5, C = 80 781 and 756 us.
+  const int groups = (C + 15) / 16;
+  const bool narrow = groups % 2 == 1 && groups <= 7;
 #define E2F_AGG(LL, SP)                                                                                           \
-  case LL: {                                                                                                      \
-    constexpr int nw = agg_waves(LL), W = 16 * agg_vec(LL);                                                       \
+  case LL:                                                                                                        \
+    if (agg_vec(LL) > 1 && narrow) E2F_AGG_V(LL, SP, 1);                                                          \
+    else E2F_AGG_V(LL, SP, agg_vec(LL));                                                                          \
+    break;
+#define E2F_AGG_V(LL, SP, VV)                                                                                     \
+  do {                                                                                                            \
+    constexpr int nw = agg_waves(LL), V = VV, W = 16 * V;                                                         \
     const int units = (C + W - 1) / W;                                                                            \
     int lg = std::min(32 / W, units); /* column groups of one line */                                             \
     while (units % lg) --lg;                                                                                      \
@@ -421,15 +434,15 @@ hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr
     const int64_t per = ((int64_t)nblk * units + 7) / 8;                                                          \
     if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                        \
     if (wide)                                                                                                     \
-      k_aggregate_fused<LL, SP, uint64_t><<<(unsigned)(8 * per), 64 * nw, 0, s>>>(                                \
+      k_aggregate_fused<LL, SP, uint64_t, V><<<(unsigned)(8 * per), 64 * nw, 0, s>>>(                                \
           Re, row_ptr, col, alpha, (int)n_edges, feat, order, first, n, rpw, nblk, lg, (int)per, C, H, n_nodes,   \
           index, (const float4*)coef, y);                                                                         \
     else                                                                                                          \
-      k_aggregate_fused<LL, SP, uint32_t><<<(unsigned)(8 * per), 64 * nw, 0, s>>>(                                \
+      k_aggregate_fused<LL, SP, uint32_t, V><<<(unsigned)(8 * per), 64 * nw, 0, s>>>(                                \
           Re, row_ptr, col, alpha, (int)n_edges, feat, order, first, n, rpw, nblk, lg, (int)per, C, H, n_nodes,   \
           index, (const float4*)coef, y);                                                                         \
     return hipGetLastError();                                                                                     \
-  }
+  } while (0)
   switch (L) {
     E2F_AGG(0, false)
     E2F_AGG(1, false)
@@ -440,6 +453,7 @@ hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr
     E2F_AGG(6, true)
     default: return hipErrorInvalidValue;
   }
+#undef E2F_AGG_V
 #undef E2F_AGG
 }
 

@@ -23,7 +23,8 @@ def gpu(a):
 # parity bar 1e-4 of the layer leaves two digits over the 1e-6 seen
 @pytest.mark.parametrize("L,C,H", [(0, 4, 1), (1, 12, 3), (2, 36, 3), (2, 16, 4), (3, 32, 8), (3, 100, 5), (4, 4, 1),
                                    (4, 48, 4), (4, 64, 1), (5, 4, 1), (5, 40, 2), (5, 64, 8), (6, 4, 1), (6, 48, 4),
-                                   (6, 32, 1)])
+                                   (6, 32, 1), (0, 20, 1), (1, 24, 2), (2, 20, 5), (2, 64, 4), (1, 144, 9), (5, 20, 1),
+                                   (5, 144, 3)])
 @pytest.mark.parametrize("y_norm", [False, True])
 def test_tile_edges(L, C, H, y_norm):
     import paper_2501_19216_amd as e2f
