@@ -53,3 +53,114 @@ def test_tile_edges(L, C, H, y_norm):
             assert np.all(got[np.array(deg) == 0] == 0)
     finally:
         ctx.close()
+
+
+# Several receivers a workgroup, one after another (2 to 8, 64 apart in the
+# order): the steps loaded ahead across rows, runs of empty rows between live
+# ones, a last set that is not full, the partial sums of one receiver over those
+# of the one before; below and above the 8,192 atoms from which the receivers are
+# sorted.  Sampled rows against the oracle, every row against the two-kernel form,
+# which shares neither kernel nor work split, every empty row zero.
+@pytest.mark.parametrize("L,C,H,n", [(0, 128, 8, 20011), (1, 64, 4, 17003), (2, 128, 8, 5003), (2, 128, 4, 16403),
+                                     (2, 48, 4, 7001), (3, 128, 8, 2501), (3, 64, 8, 9001), (4, 64, 4, 4099),
+                                     (5, 64, 8, 1501), (5, 64, 4, 5003), (5, 48, 12, 1801), (6, 64, 8, 1301)])
+def test_receivers_in_turn(L, C, H, n):
+    import paper_2501_19216_amd as e2f
+    ctx = e2f.e2f_create(L, 0)
+    try:
+        rng = np.random.default_rng(11 * L + C)
+        pos = syn.quantize(rng.uniform(0, 6.0, size=(n, 3)))
+        deg = np.array([(0, 0, 1, 16, 17, 0, 4, 33, 5, 15, 32, 0, 0, 40, 64)[i % 15] for i in range(n)])
+        deg[n // 3:n // 3 + 400] = 0  # a run over several sets
+        deg[-3:] = (0, 17, 0)
+        rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+        ci = np.concatenate([np.sort(rng.choice(n - 1, size=d, replace=False)) for d in deg if d]).astype(np.int32)
+        ci += ci >= np.repeat(np.arange(n), deg)  # (no atom is its own neighbour)
+        feat = rng.standard_normal((n, (L + 1) ** 2, C)).astype(np.float32)
+        alpha = rng.uniform(0.1, 1.0, size=(len(ci), H)).astype(np.float32)
+        w = rng.uniform(0.5, 1.5, size=(L + 1) ** 3)
+        print("L %d C %d H %d n %d" % (L, C, H, n), flush=True)
+        args = (ctx, gpu(pos), gpu(feat), gpu(rp), gpu(ci), gpu(alpha), L, H, 6.0)
+        got = e2f.e2f_wigner6j_conv_forward(*args, path_w=w).cpu().numpy()
+        assert np.all(got[deg == 0] == 0)
+        live = np.flatnonzero(deg)
+        r = np.unique(np.concatenate([live[:16], live[-16:], rng.choice(live, size=32)])).astype(np.int32)
+        ref = o.layer(L, H, pos, feat, rp, ci, alpha, w, rows=r)
+        err = o.max_rel_err(got[r], ref, L)
+        two = e2f.e2f_wigner6j_conv_forward(*args, path_w=w, form="split").cpu().numpy()
+        every = o.max_rel_err(got, two, L)
+        print("  err %.3e, against the two-kernel form %.3e" % (err, every))
+        assert err <= TOL_F32 and every <= TOL_F32
+    finally:
+        ctx.close()
+
+
+# Features of more than 2^32 bytes (64-bit offsets): senders on both sides of it.
+@pytest.mark.parametrize("L,C,H", [(2, 1024, 8), (3, 1024, 16), (5, 1024, 4), (6, 1024, 8)])
+def test_features_beyond_4_gib(L, C, H):
+    import paper_2501_19216_amd as e2f
+    nk = (L + 1) ** 2
+    n = int(4.5e9 / (4 * nk * C))
+    ctx = e2f.e2f_create(L, 0)
+    try:
+        rng = np.random.default_rng(5 + L)
+        far = int(2 ** 32 / (4 * nk * C)) + 1  # the first atom past 2^32 bytes
+        recv = np.sort(np.concatenate([[0, 1, far - 1, far, n - 1], rng.choice(np.arange(2, far - 1), 40, replace=False)]))
+        deg = np.zeros(n, dtype=np.int64)
+        deg[recv] = rng.integers(1, 40, size=len(recv))
+        rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+        cols = [np.sort(np.concatenate([rng.choice(np.arange(far, n - 1), (d + 1) // 2, replace=False),
+                                        rng.choice(np.arange(2, far - 1), d // 2, replace=False)])) for d in deg[recv]]
+        ci = np.concatenate(cols).astype(np.int32)
+        pos = syn.quantize(rng.uniform(0, 6.0, size=(n, 3)))
+        g = torch.Generator(device=DEV).manual_seed(L)
+        feat = torch.randn(n, nk, C, device=DEV, generator=g)
+        alpha = rng.uniform(0.1, 1.0, size=(len(ci), H)).astype(np.float32)
+        w = rng.uniform(0.5, 1.5, size=(L + 1) ** 3)
+        print("L %d C %d H %d n %d: %.2f GB of features" % (L, C, H, n, feat.numel() * 4e-9), flush=True)
+        size = e2f.e2f_wigner6j_workspace_size(ctx, n, len(ci), L, C, H, 6.0, path_w=w, minimum=True)
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        got = e2f.e2f_wigner6j_conv_forward(ctx, gpu(pos), feat, gpu(rp), gpu(ci), gpu(alpha), L, H, 6.0, path_w=w,
+                                            workspace=ws)
+        empty = torch.from_numpy(deg == 0).to(DEV)
+        assert not bool((got.abs().amax(dim=(1, 2))[empty] != 0).any())
+        # the graph of the atoms that take part, for the oracle
+        used = np.unique(np.concatenate([recv, ci]))
+        at = np.searchsorted(used, recv).astype(np.int32)
+        ld = np.zeros(len(used), dtype=np.int64)
+        ld[at] = deg[recv]
+        lrp = np.concatenate([[0], np.cumsum(ld)]).astype(np.int64)
+        sub = feat[torch.from_numpy(used).to(DEV)].cpu().numpy()
+        ref = o.layer(L, H, pos[used], sub, lrp, np.searchsorted(used, ci).astype(np.int32), alpha, w, rows=at)
+        err = o.max_rel_err(got[torch.from_numpy(recv).to(DEV)].cpu().numpy(), ref, L)
+        print("  err %.3e" % err)
+        assert err <= TOL_F32
+    finally:
+        ctx.close()
+        torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("L,C,H,n", [(2, 64, 4, 900), (5, 128, 8, 300)])
+def test_bf16_mixing_is_of_the_rounded_sums(L, C, H, n):
+    # bf16 mixing rounds y to bf16 once: the mixed output equals the product of the
+    # rounded unmixed output (float sums of C products: 1e-6 a product), so that two
+    # correct y differ in it only where one lies near a tie
+    import paper_2501_19216_amd as e2f
+    ctx = e2f.e2f_create(L, 0)
+    try:
+        g = torch.Generator(device=DEV).manual_seed(3)
+        pos = gpu(syn.quantize(np.random.default_rng(3).uniform(0, 14.0, size=(n, 3))))
+        rp, ci = e2f.e2f_neighbor_list(ctx, pos, 6.0)
+        feat = torch.randn(n, (L + 1) ** 2, C, device=DEV, generator=g)
+        alpha = torch.rand(ci.numel(), H, device=DEV, generator=g)
+        W = (torch.randn(L + 1, C, C, device=DEV, generator=g) / C ** 0.5).bfloat16()
+        y = e2f.e2f_wigner6j_conv_forward(ctx, pos, feat, rp, ci, alpha, L, H, 6.0)
+        got = e2f.e2f_wigner6j_conv_forward(ctx, pos, feat, rp, ci, alpha, L, H, 6.0, mix_w=W)
+        for l in range(L + 1):
+            a = y[:, l * l:(l + 1) ** 2].bfloat16().double().reshape(-1, C)
+            ref = a @ W[l].double().t().contiguous()
+            err = float((got[:, l * l:(l + 1) ** 2].double().reshape(-1, C) - ref).abs().max() / ref.abs().max())
+            print("bf16 mixing L %d degree %d: %.3e" % (L, l, err), flush=True)
+            assert err <= 4e-6
+    finally:
+        ctx.close()
