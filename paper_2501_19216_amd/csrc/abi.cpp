@@ -612,6 +612,21 @@ constexpr double kTileCutoffs[kMaxL + 1] = {8.0, 8.0, 8.0, 6.0, 4.0, 3.0, 2.0};
 // ratio (|p_i| + |p_j|) / |r_ij| stays below about 1 + 2.31 sqrt(3) = 5.
 constexpr double kYnormTileScale = 2.31;
 
+// Whether a graph of at most kPlanSmallMax atoms is sorted for the fused form
+// (launch_plan_small, one workgroup: 16 us at 1,000 atoms, 45 at 8,000).  It pays
+// where the features no longer fit the L2s together (32 MB) and are read often
+// enough.  Measured on atoms in random order, own order and sorted: L = 3, 8,000
+// atoms, C = 256 (131 MB), 32 neighbours 0.90 of the time, 200 0.81; C = 1024, 200
+// neighbours 22.8 and 11.5 ms; L = 4, 8,000 atoms, C = 128 (102 MB), 200 0.62;
+// 4,000 atoms (51 MB), 80 0.93, 32 1.01; 2,000 atoms (26 MB), 80 1.00; L = 3, 1,000
+// atoms, C = 1024 (66 MB), 32 1.02.  Up to L = 2 a column group reads whole lines
+// and bears more: 8,000 atoms, L = 2, C = 1024 (295 MB), 12 neighbours 1.04, 32
+// 0.98, 80 0.91; C = 256 (74 MB), 200 1.01.
+bool small_sorted(const e2f_conv_params* p, int n, int64_t n_edges) {
+  const double atom = 4.0 * nk_of(p->lmax) * p->channels;  // bytes of features
+  return p->lmax <= 2 ? n * atom >= 256e6 && n_edges * atom >= 8e9 : n * atom >= 48e6 && n_edges * atom >= 3e9;
+}
+
 e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos, const int32_t* graph_id,
                         const float* feat, int32_t n, const int64_t* row_ptr, const int32_t* col_idx, int64_t n_edges,
                         const float* alpha, float* out, void* workspace, size_t workspace_bytes, void* stream,
@@ -667,19 +682,23 @@ e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos
   int64_t slices = 0;
   const double side = (p->tile_side > 0.0f ? (double)p->tile_side : kTileCutoffs[L] * (double)p->cutoff) * kGrid;
   if (fused) {
-    // ---- the receiver order (their own, up to kPlanSmallMax atoms), the
+    // ---- the receiver order (their own where sorting does not pay), the
     // harmonics of the edges, then per slice of receivers the aggregation
+    const bool sorted = n > kPlanSmallMax || small_sorted(p, n, n_edges);
     if (n > kPlanSmallMax) {
       E2F_TIMED("bbox", launch_plan_bbox(pos, graph_id, n, stats, nullptr, s));
       E2F_TIMED("tile_plan", launch_plan_grid(stats, nullptr, side, kYnormTileScale, grid, s));
       E2F_TIMED("tile_plan", launch_plan_order(pos, graph_id, n, grid, tile_of, (uint64_t*)(ws + f.keys),
                                                (uint64_t*)(ws + f.keys_out), (int32_t*)(ws + f.vals), order,
                                                ws + f.sort_tmp, f.sort_b, s));
+    } else if (sorted) {
+      E2F_TIMED("tile_plan", launch_plan_small(pos, graph_id, n, nullptr, side, kYnormTileScale, stats, grid, tile_of,
+                                               order, s));
     }
     E2F_TIMED("sh", launch_edge_sh(t, pos, row_ptr, col_idx, n, 0, n_edges, ynorm, Re, s));
     for (int64_t q0 = 0; q0 < n; q0 += slice, ++slices)
       E2F_TIMED("aggregate", launch_aggregate_fused(L, Re, row_ptr, col_idx, alpha, n_edges, feat,
-                                                    n > kPlanSmallMax ? order : nullptr, (int)q0,
+                                                    sorted ? order : nullptr, (int)q0,
                                                     (int)std::min<int64_t>(slice, n - q0), C, H, n,
                                                     cs->agg_index, cs->agg_coef, y, s));
     if (p->mix_w) E2F_TIMED("mix", launch_mix(L, y, p->mix_w, p->mix_dtype == E2F_BF16, n, C, out, s));

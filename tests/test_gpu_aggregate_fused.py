@@ -58,12 +58,14 @@ def test_tile_edges(L, C, H, y_norm):
 # Several receivers a workgroup, one after another (2 to 8, 64 apart in the
 # order): the steps loaded ahead across rows, runs of empty rows between live
 # ones, a last set that is not full, the partial sums of one receiver over those
-# of the one before; below and above the 8,192 atoms from which the receivers are
-# sorted.  Sampled rows against the oracle, every row against the two-kernel form,
-# which shares neither kernel nor work split, every empty row zero.
+# of the one before; receivers in their own order and sorted (above 8,192 atoms,
+# and below where 3 GB of features are gathered: the last case).  Sampled rows
+# against the oracle, every row against the two-kernel form, which shares neither
+# kernel nor work split, every empty row zero.
 @pytest.mark.parametrize("L,C,H,n", [(0, 128, 8, 20011), (1, 64, 4, 17003), (2, 128, 8, 5003), (2, 128, 4, 16403),
                                      (2, 48, 4, 7001), (3, 128, 8, 2501), (3, 64, 8, 9001), (4, 64, 4, 4099),
-                                     (5, 64, 8, 1501), (5, 64, 4, 5003), (5, 48, 12, 1801), (6, 64, 8, 1301)])
+                                     (5, 64, 8, 1501), (5, 64, 4, 5003), (5, 48, 12, 1801), (6, 64, 8, 1301),
+                                     (3, 1024, 8, 4003)])
 def test_receivers_in_turn(L, C, H, n):
     import paper_2501_19216_amd as e2f
     ctx = e2f.e2f_create(L, 0)
