@@ -539,6 +539,7 @@ struct FwdLayout {
 // (fused_row_floats) instead of S.  Callers allocate by these sizes and the
 // slices follow from them, so they stay what they are, although the fused
 // aggregation keeps neither in memory.
+constexpr int kFuseMaxL = 4;
 bool fused_sizes(const e2f_conv_params* p, int64_t n) {
   const int dh = p->channels / p->heads, groups = (nk_of(p->lmax) + 3) / 4;
   if (p->form == E2F_FORM_SPLIT || dh % 16 != 0 || p->lmax > kFuseMaxL) return false;
@@ -548,15 +549,14 @@ bool fused_sizes(const e2f_conv_params* p, int64_t n) {
   return p->lmax == kFuseMaxL && s_bytes > 256.0 * 1024 * 1024;
 }
 
-// Floats of one receiver's composed matrix, the largest layout among the
-// stacked alpha / D^f passes (ynorm_passes).
+// Floats of one receiver's composed matrix: (L+1)^2 output rows by (L+1)^2
+// components of the features by the components of the harmonics, padded to four
+// (with alpha / D^f every filter degree has its own (f+1)^2 of them, at L = 4
+// two sets of at most 30), padded to 256 bytes.
 int fused_row_floats(const e2f_conv_params* p) {
   const int L = p->lmax, nk = nk_of(L);
-  int fl = fuse_stride(nk, nk);
-  YnormPass yps[kYnormMaxPasses];
-  const int nyp = p->y_norm && L <= kFuseMaxL ? ynorm_passes(L, yps) : 0;
-  for (int q = 0; q < nyp; ++q) fl = std::max(fl, fuse_stride(nk, fuse_krows(nk, yps[q].degs, yps[q].nd)));
-  return fl;
+  const int k = !p->y_norm ? nk : L == 4 ? 30 : (L + 1) * (L + 2) * (2 * L + 3) / 6;
+  return (nk * nk * ((k + 3) / 4 * 4) + 63) / 64 * 64;
 }
 
 FwdLayout fwd_layout(const e2f_conv_params* p, int n, int64_t E, bool have_alpha, bool lean = false) {

@@ -11,6 +11,7 @@
 #include <random>
 
 #include "agg_layout.h"
+#include "fuse_table.h"
 
 using namespace e2f;
 

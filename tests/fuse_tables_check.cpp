@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <random>
 #include "e2f_internal.h"
+#include "fuse_table.h"
 
 using namespace e2f;
 
