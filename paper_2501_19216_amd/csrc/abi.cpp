@@ -1304,7 +1304,7 @@ e2f_status e2f_wigner6j_conv_backward(e2f_ctx* ctx, const e2f_conv_params* p, co
     const int64_t lo = q * pass, hi = std::min(lo + pass, n_edges);
     if (Gt) E2F_TIMED("edge_geom", launch_edge_shgrad(tw, pos, rows + lo, col_idx + lo, n, hi - lo, Gt, s));
     if (Re && L > 0) E2F_TIMED("sh", launch_edge_sh(tw, pos, row_ptr, col_idx, n, lo, hi - lo, false, Re, s));
-    E2F_TIMED("edge_geom", launch_edge_grad(L, Re, Gt, feat, gy, row_ptr, col_idx, alpha, nullptr, n, C, H, n_edges, lo,
+    E2F_TIMED("edge_geom", launch_edge_grad(L, Re, Gt, feat, gy, row_ptr, col_idx, alpha, n, C, H, n_edges, lo,
                                             hi, range ? range + 2 * q : nullptr, cs->grad_coef, grad_alpha, gpart,
                                             gedge ? gedge + 3 * lo : nullptr, s));
   }

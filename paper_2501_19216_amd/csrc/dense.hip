@@ -25,9 +25,6 @@
 // slabs in flight on an XCD are shared through its L2.
 #include <hip/hip_runtime.h>
 
-#include <cstdio>
-#include <cstdlib>
-
 #include "e2f_launch.h"
 
 namespace e2f {
@@ -244,30 +241,14 @@ hipError_t launch_dense_aggregate(const float* A, int n, const float* T, int dim
   if (n == 0) return hipSuccess;
   const int dh = C / H, W = dimT * dh;
   if (W < 4 || W % 4) return hipErrorInvalidValue;
-  // tile shape (waves in M, waves in N); E2F_DENSE_TILE = "WGM,WGN" selects
-  // another of the compiled shapes (tuning)
-  static const int shape = [] {
-    const char* v = getenv("E2F_DENSE_TILE");
-    int a = 4, b = 2;
-    if (v) sscanf(v, "%d,%d", &a, &b);
-    return a * 10 + b;
-  }();
-  const int wgm = shape / 10, wgn = shape % 10;
+  constexpr int wgm = 4, wgn = 2;  // waves in M and N
   const int n_ib = (n + 64 * wgm - 1) / (64 * wgm), n_cb = (W + 64 * wgn - 1) / (64 * wgn);
   const int64_t tiles = (int64_t)H * n_ib * n_cb;
   const int64_t per_xcd = (tiles + 7) / 8;
   if (8 * per_xcd > 0x7fffffff) return hipErrorInvalidValue;
   const int64_t ldt = (int64_t)dimT * C;
-  switch (shape) {
-#define E2F_DG(M_, N_)                                                                                             \
-  case M_ * 10 + N_:                                                                                               \
-    k_dense_gemm<M_, N_><<<(unsigned)(8 * per_xcd), 64 * M_ * N_, 0, s>>>(A, dense_lda(n), n, T, ldt, W, S, n_ib,   \
-                                                                          n_cb, H, (int)per_xcd);                  \
-    break;
-    E2F_DG(2, 2) E2F_DG(4, 2) E2F_DG(4, 4)
-#undef E2F_DG
-    default: return hipErrorInvalidValue;
-  }
+  k_dense_gemm<wgm, wgn><<<(unsigned)(8 * per_xcd), 64 * wgm * wgn, 0, s>>>(A, dense_lda(n), n, T, ldt, W, S, n_ib, n_cb,
+                                                                            H, (int)per_xcd);
   return hipGetLastError();
 }
 

@@ -196,14 +196,14 @@ hipError_t launch_attention(const float* pos, const float* q, const float* k, in
 // the position gradient per edge gedge [hi - lo][3] (from the edge lo on);
 // coef: grad_table, Re [hi - lo][nk]: launch_edge_sh (read for galpha at L > 0), Gt [hi
 // - lo][3][nk]: launch_edge_shgrad (read for gedge); gpart [H][hi - lo][3]:
-// scratch of gedge when H > 1; order: the receivers, or NULL (by index); range:
-// the pass's entry of launch_edge_ranges, or NULL where the pass has every edge.
+// scratch of gedge when H > 1; range: the pass's entry of launch_edge_ranges, or
+// NULL where the pass has every edge.
 // launch_force_gather then sums per atom the edges it receives minus those it
 // sends (rowT, perm: the transposed graph).
 hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float* feat, const float* gy,
-                            const int64_t* row_ptr, const int32_t* col, const float* alpha, const int32_t* order,
-                            int n, int C, int H, int64_t n_edges, int64_t lo, int64_t hi, const int* range,
-                            const float* coef, float* galpha, float* gpart, float* gedge, hipStream_t s);
+                            const int64_t* row_ptr, const int32_t* col, const float* alpha, int n, int C, int H,
+                            int64_t n_edges, int64_t lo, int64_t hi, const int* range, const float* coef,
+                            float* galpha, float* gpart, float* gedge, hipStream_t s);
 // range [passes][2]: of each pass of `pass` edges the first receiver with one of
 // them and one past the last
 hipError_t launch_edge_ranges(const int64_t* row_ptr, int n, int64_t n_edges, int64_t pass, int passes, int* range,

@@ -150,9 +150,8 @@ template <int L, int P, int W, int NWV, int T>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(T > 2 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
 void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, const float* __restrict__ feat,
                  const float* __restrict__ gy, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                 const float* __restrict__ alpha, const int32_t* __restrict__ order, int n, int rpw, int nset, int lg,
-                 int per_xcd, int C, int H, int64_t lo, int64_t hi, const int* __restrict__ range,
-                 const float* __restrict__ coef,
+                 const float* __restrict__ alpha, int n, int rpw, int nset, int lg, int per_xcd, int C, int H,
+                 int64_t lo, int64_t hi, const int* __restrict__ range, const float* __restrict__ coef,
                  float* __restrict__ galpha, float* __restrict__ gedge) {
   constexpr AggMap M = agg_map(L);
   constexpr int NK = M.nk, NG = M.ng, KEYS = M.keys, DH = 16 / P;
@@ -205,8 +204,7 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
   // bounds of a receiver (clamped to the range; hi < 2^31), loaded while the
   // one before is worked on
   auto receiver = [&](int k, int& i, int64_t& b0, int64_t& b1) {
-    const int at = first + min((set * rpw + min(k, rpw - 1)) * NWV + wave, nrec - 1);
-    i = order ? order[at] : at;
+    i = first + min((set * rpw + min(k, rpw - 1)) * NWV + wave, nrec - 1);
     b0 = row_ptr[i], b1 = row_ptr[i + 1];
   };
   int in;
@@ -480,9 +478,9 @@ __global__ __launch_bounds__(256) void k_force_gather(const int64_t* __restrict_
 }  // namespace
 
 hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float* feat, const float* gy,
-                            const int64_t* row_ptr, const int32_t* col, const float* alpha, const int32_t* order,
-                            int n, int C, int H, int64_t n_edges, int64_t lo, int64_t hi, const int* range,
-                            const float* coef, float* galpha, float* gpart, float* gedge, hipStream_t s) {
+                            const int64_t* row_ptr, const int32_t* col, const float* alpha, int n, int C, int H,
+                            int64_t n_edges, int64_t lo, int64_t hi, const int* range, const float* coef,
+                            float* galpha, float* gpart, float* gedge, hipStream_t s) {
   if (n == 0 || hi <= lo || (!galpha && !gedge)) return hipSuccess;
   const int dh = C / H, P = dh % 16 == 0 ? 1 : dh % 8 == 0 ? 2 : 4;  // the widest group that divides a head
   int lg = std::max(1, std::min(32 / dh, H));  // heads of one 128-byte line
@@ -505,7 +503,7 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
     const int64_t per = ((int64_t)nset * H + 7) / 8;                                                              \
     if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                        \
     k_edge_grad<LL, PP, WW, nw, TT><<<(unsigned)(8 * per), 64 * nw, LL >= 2 ? M.nk * M.ng * 256 : 0, s>>>(        \
-        Re, Gt, feat, gy, row_ptr, col, alpha, order, n, rpw, nset, lg, (int)per, C, H, lo, hi, range, coef,      \
+        Re, Gt, feat, gy, row_ptr, col, alpha, n, rpw, nset, lg, (int)per, C, H, lo, hi, range, coef,      \
         galpha, out);                                                                                             \
   } while (0)
 #define E2F_GT(LL, PP, WW, NN)                                 \
