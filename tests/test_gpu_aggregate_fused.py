@@ -166,3 +166,80 @@ def test_bf16_mixing_is_of_the_rounded_sums(L, C, H, n):
             assert err <= 4e-6
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("L,bad", [(2, np.inf), (4, np.inf), (4, np.nan), (6, -np.inf)])
+def test_bad_values_stay_where_they_belong(L, bad):
+    # a feature, weight or gradient that is not finite reaches the receivers (rows,
+    # edges) that read it and no other value, which stays what it was bit for bit
+    # (past a row's end its last sender is read with a weight of zero; receivers of
+    # one workgroup follow each other in the same registers)
+    import paper_2501_19216_amd as e2f
+    C, H, n, j0, c0 = 32, 4, 700, 123, 7
+    ctx = e2f.e2f_create(L, 0)
+    try:
+        g = torch.Generator(device=DEV).manual_seed(L)
+        pos = gpu(syn.quantize(np.random.default_rng(L).uniform(0, 19.0, size=(n, 3))))
+        rp, ci = e2f.e2f_neighbor_list(ctx, pos, 5.0)
+        feat, gout = (torch.randn(n, (L + 1) ** 2, C, device=DEV, generator=g) for _ in range(2))
+        alpha = torch.rand(ci.numel(), H, device=DEV, generator=g)
+        recv = torch.arange(n, device=DEV).repeat_interleave(rp[1:] - rp[:-1])
+        print("L %d %s" % (L, bad), flush=True)
+
+        def forward(f, a):
+            return e2f.e2f_wigner6j_conv_forward(ctx, pos, f, rp, ci, a, L, H, 5.0)
+
+        def backward(f, go):
+            return e2f.e2f_wigner6j_conv_backward(ctx, pos, f, go, rp, ci, alpha, L, H, 5.0, want_pos=True)
+
+        def same(got, want, hit):
+            assert not bool(torch.isfinite(got[hit]).all())
+            assert torch.equal(got[~hit], want[~hit]) and bool(torch.isfinite(want).all())
+
+        y = forward(feat, alpha)
+        f = feat.clone()
+        f[j0, 2, c0] = bad
+        hit = torch.zeros_like(y, dtype=torch.bool)
+        hit[recv[ci == j0], :, c0] = True
+        same(forward(f, alpha), y, hit)
+        e = int((ci == j0).nonzero()[0])
+        a = alpha.clone()
+        a[e, 2] = bad
+        hit = torch.zeros_like(y, dtype=torch.bool)
+        hit[recv[e], :, 2 * C // H:3 * C // H] = True
+        same(forward(feat, a), y, hit)
+        gf, ga, gp = backward(feat, gout)
+        go = gout.clone()
+        go[j0, 2, c0] = bad
+        bf, ba, bp = backward(feat, go)
+        hit = torch.zeros_like(ga, dtype=torch.bool)
+        hit[recv == j0, c0 * H // C] = True
+        same(ba, ga, hit)
+        hit = torch.zeros_like(gf, dtype=torch.bool)
+        hit[ci[recv == j0].long(), :, c0] = True
+        same(bf, gf, hit)
+        hit = torch.zeros_like(gp, dtype=torch.bool)
+        hit[j0] = hit[ci[recv == j0].long()] = True
+        same(bp, gp, hit)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("L", [2, 4, 6])
+def test_small_features(L):
+    # 2^-100 of the features is 2^-100 of the result, to float rounding: what the
+    # split operands lose lies below 2^-133
+    import paper_2501_19216_amd as e2f
+    ctx = e2f.e2f_create(L, 0)
+    try:
+        g = torch.Generator(device=DEV).manual_seed(L)
+        pos = gpu(syn.quantize(np.random.default_rng(L).uniform(0, 9.0, size=(150, 3))))
+        rp, ci = e2f.e2f_neighbor_list(ctx, pos, 5.0)
+        feat = torch.randn(150, (L + 1) ** 2, 16, device=DEV, generator=g)
+        alpha = torch.rand(ci.numel(), 2, device=DEV, generator=g)
+        y, z = (e2f.e2f_wigner6j_conv_forward(ctx, pos, feat * s, rp, ci, alpha, L, 2, 5.0).double() for s in (1.0, 2.0 ** -100))
+        err = float((z * 2.0 ** 100 - y).norm() / y.norm())
+        print("L %d features of 2^-100: %.2e" % (L, err), flush=True)
+        assert err <= 1e-6
+    finally:
+        ctx.close()
