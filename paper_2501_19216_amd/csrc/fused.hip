@@ -17,6 +17,9 @@
 namespace e2f {
 namespace {
 
+// How far apart in the order the receivers of a workgroup lie (see below).  Flat
+// around 64: 20,000 atoms, L = 4 3.12, 3.07, 3.09 and 3.14 ms with 1, 16, 64 and
+// 256, 5,001 atoms 772, 764, 758 and 886 us, 3,000 atoms, L = 5 503, 500, 507, 590.
 constexpr int kAggStride = 64;
 
 // One workgroup: rpw receivers of one group of 16 V channels (V = agg_vec or 1),
@@ -300,7 +303,9 @@ void k_aggregate_fused(const float* __restrict__ Re, const int64_t* __restrict__
       const char* cw = (const char*)(coef + (size_t)wave * TW * NQ * 64);
       unsigned lo = (unsigned)lane * 16;
       asm("" : "+v"(lo));  // keeps the table's addresses out of the registers that live through the steps
-      // the table is read AHEAD entries ahead (each is a read from L2)
+      // the table is read AHEAD entries ahead (each is a read from L2; 20,000 atoms,
+      // L = 4 3.11, 3.09 and 3.20 ms with 3, 6 and 12, 3,000 atoms, L = 5 505, 507 and
+      // 614 us)
       constexpr int ALL = TW * NQ, AHEAD = ALL < 6 ? ALL : 6;
       float4 kk[AHEAD];
       auto entry = [&](int m) { return *(const float4*)(cw + m * 1024 + lo); };
@@ -408,7 +413,10 @@ hipError_t launch_aggregate_fused(int L, const float* Re, const int64_t* row_ptr
     const int units = (C + W - 1) / W;                                                                            \
     int lg = std::min(32 / W, units); /* column groups of one line */                                             \
     while (units % lg) --lg;                                                                                      \
-    /* receivers a workgroup: the steps of consecutive ones overlap, as long as every CU has work */              \
+    /* receivers a workgroup: the steps of consecutive ones overlap, as long as every CU has work four times  */   \
+    /* over.  One, 4, 8 and 16 at most: 20,000 atoms, L = 4 3.30, 3.06, 3.09, 3.18 ms; 10,000 atoms, L = 3 495,  */ \
+    /* 446, 435, 440 us.  Work once, 4 and 16 times over: 7,680 atoms in rows of 6, L = 3 87, 91 and 110 us;    */  \
+    /* 3,000 atoms, L = 5 482, 507 and 550; 1,517 atoms, L = 2 34.6, 33.3 and 33.2                              */  \
     const int64_t slots = 256 * 8 / nw;                                                                           \
     const int rpw = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)n * units / (slots * 4)));            \
     const int nblk = (n + kAggStride * rpw - 1) / (kAggStride * rpw) * kAggStride;                                \
