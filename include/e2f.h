@@ -175,10 +175,11 @@ typedef struct {
   const double* path_w;  /* host [(L+1)^3] w[a][f][o]; NULL => cutoff^-f on triangle-valid paths */
   const void* mix_w;     /* device [(L+1)][C][C] W[o][c_out][c_in] of mix_dtype; NULL => no mixing */
   e2f_dtype mix_dtype;   /* E2F_F32, or E2F_BF16 (mixing inputs rounded to bf16, fp32 accumulate) */
-  float tile_side;       /* two-kernel form and dense/global defaults: side of the receiver tiles whose centres
-                            serve as local origins; 0 => cutoff * (8, 8, 8, 6, 4, 3, 2) for L = 0..6 (fp32
-                            precision of the binomial expansion; the cost does not depend on it).  The fused
-                            form expands about each receiver and needs no tiles */
+  float tile_side;       /* two-kernel form: side of the receiver tiles whose centres serve as local origins; 0 =>
+                            cutoff * (8, 8, 8, 6, 4, 3, 2) for L = 0..6 (fp32 precision of the binomial
+                            expansion; the cost does not depend on it).  No result of the other forms depends on
+                            it: the fused one expands about each receiver, the dense and global ones about the
+                            centre of the bounding box */
   int32_t y_norm;        /* 0: the layer above.  1: Alg. 1's per-degree attention weights
                             alpha_ij / D_ij^f on the paths of filter degree f, D_ij = |r_i - r_j|
                             (filters Y^(f) of the unit vector; the path f takes 0 at D = 0 for
@@ -198,7 +199,8 @@ typedef struct {
                             matrix cores with each float operand split into three bf16 parts
                             (x = hi + mid + lo exactly) and the six cross products that reach
                             2^-24 of the product accumulated in float, i.e. float products to
-                            within float rounding.  The workspace sizes do not depend on which kernel
+                            within float rounding (for operands up to the largest bfloat16; below about 2^-110
+                            their last bits are lost).  The workspace sizes do not depend on which kernel
                             runs: they hold S, or a composed coupling matrix, per receiver */
 } e2f_conv_params;
 
@@ -246,7 +248,10 @@ e2f_status e2f_wigner6j_prepare(e2f_ctx* ctx, const e2f_conv_params* params);
  * atom outside that range is placed in the nearest tile and its outputs are
  * not meaningful; nothing is reported).  The CSR is trusted for values but
  * read with clamped indices (a malformed graph gives wrong outputs, never an
- * access outside the buffers); e2f_validate_graph checks one.
+ * access outside the buffers); e2f_validate_graph checks one.  A feature or
+ * weight that is not finite makes the outputs of the receivers and channels
+ * that read it not finite (NaN also where the sum by its definition would be an
+ * infinity: couplings of zero meet it in the matrix products) and no others.
  * Deterministic: no floating-point atomics. */
 e2f_status e2f_wigner6j_conv_forward(e2f_ctx* ctx, const e2f_conv_params* params, const float* pos,
                                      const int32_t* graph_id, const float* feat, int32_t n, const int64_t* row_ptr,
@@ -286,8 +291,8 @@ e2f_status e2f_validate_graph(e2f_ctx* ctx, int32_t n, const int64_t* row_ptr, c
  * ignored; NULL => 1 for every pair.  One origin, the centre of the bounding
  * box (found on the device).  T_j is stored for every atom and the
  * aggregation S_h = A_h T_h is a dense product per head on the matrix cores
- * (fp32, a hand-written tiled kernel).  tile_side and cutoff serve only the
- * default path weights (cutoff^-f).  N^2 H must stay below 4e9.  Internal
+ * (float operands split into three bf16 parts as in the fused form).  cutoff
+ * serves only the default path weights (cutoff^-f).  N^2 H must stay below 4e9.  Internal
  * workspace: about N (2 dimT C + N H) floats.  Positions must be finite with
  * |x| < 16384 A (not reported). */
 e2f_status e2f_wigner6j_conv_forward_dense(e2f_ctx* ctx, const e2f_conv_params* params, const float* pos,
@@ -331,7 +336,9 @@ e2f_status e2f_wigner6j_conv_forward_global(e2f_ctx* ctx, const e2f_conv_params*
  * the receiver's output gradient is contracted with the filter coefficients
  * once per receiver, and one product with the senders' features per head
  * gives the contraction against R (grad_alpha) and against its gradient
- * weighted by alpha (grad_pos) for every edge of the receiver.
+ * weighted by alpha (grad_pos) for every edge of the receiver.  The edges go
+ * in passes whose tables (harmonics, their gradients, per-head parts) take at
+ * most 4 GiB of the context's memory.
  * Any of the outputs may be NULL (not all).  Not available with y_norm. */
 e2f_status e2f_wigner6j_conv_backward(e2f_ctx* ctx, const e2f_conv_params* params, const float* pos,
                                       const int32_t* graph_id, const float* feat, const float* grad_out, int32_t n,

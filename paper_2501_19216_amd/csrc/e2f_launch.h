@@ -13,8 +13,8 @@ namespace e2f {
 // graph id, stats[7] = error bits (1: bad position, 2: negative graph id).
 constexpr int kStatsInts = 8;
 // rows of padding after the forward's per-edge arrays (harmonics of the
-// edges, head-major attention weights): the fused aggregation's staging
-// loads whole chunks of edges without a bound check
+// edges, head-major attention weights), part of the workspace sizes callers
+// allocate by; every kernel clamps its reads to the row's end
 constexpr int kEdgePad = 128;
 hipError_t launch_bbox(const float* pos, const int32_t* graph_id, int n, int* stats, hipStream_t s);
 
