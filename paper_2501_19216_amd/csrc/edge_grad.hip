@@ -80,13 +80,6 @@ constexpr int grad_tiles(int L, int W) { return L <= 2 || L == 4 ? 5 : L == 3 ? 
 // before it, which return in order: 20,000 atoms, 80 neighbours,
 // L = 5, 8 heads, C = 64 16.1 -> 7.2 ms, C = 32 19.2 -> 6.2.)
 constexpr int kGradWaves = 4;
-// Receivers a wave takes one after another: up to `most`, as long as every CU
-// has work (they share the table).
-__host__ __device__ inline int grad_rpw(int n, int H, int most) {
-  const int64_t r = (int64_t)n * H / (256 * 16);
-  return r < 1 ? 1 : r > most ? most : (int)r;
-}
-
 // Where X += h Z^T runs as split bf16 products: a lane's four slots fill the K
 // of three v_mfma_f32_16x16x32_bf16 (16 cycles each) a tile and key with the six
 // cross products that reach 2^-24 of the product, against four
@@ -135,8 +128,8 @@ template <int L, int P, int W, int NWV, int T>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(T > 2 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
 void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, const float* __restrict__ feat,
                  const float* __restrict__ gy, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                 const float* __restrict__ alpha, int n, int rpw, int most, int nset, int lg, int per_xcd, int C,
-                 int H, int64_t lo, int64_t hi, const int* __restrict__ range, const float* __restrict__ coef,
+                 const float* __restrict__ alpha, int n, int rpw, int nset, int lg, int per_xcd, int C, int H,
+                 int64_t lo, int64_t hi, const int* __restrict__ range, const float* __restrict__ coef,
                  float* __restrict__ galpha, float* __restrict__ gedge) {
   constexpr AggMap M = agg_map(L);
   constexpr int NK = M.nk, NG = M.ng, KEYS = M.keys, DH = 16 / P;
@@ -146,9 +139,8 @@ void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, con
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, k4 = lane >> 4;
   int first = 0, nrec = n;
-  if (range) {  // (as launch_edge_grad has it for all n)
+  if (range) {  // (fewer sets than launch_edge_grad has for all n, of the same size)
     first = range[0], nrec = range[1] - first;
-    rpw = grad_rpw(nrec, H, most);
     nset = (nrec + NWV * rpw - 1) / (NWV * rpw);
     per_xcd = (int)(((int64_t)nset * H + 7) / 8);
     if ((int)(blockIdx.x / 8) >= per_xcd) return;
@@ -472,14 +464,15 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
   while (H % lg) --lg;
   float* out = gedge && H > 1 ? gpart : gedge;
   const int64_t n_waves = (int64_t)n * H;
-  // One receiver a wave where rows are long (up to L = 4): the heads of a line run
+  // Receivers a wave takes one after another (they share the table): up to eight,
+  // as long as every CU has work.  One where rows are long (up to L = 4): the heads of a line run
   // as workgroups side by side and share it only as long as they keep in step,
   // which they lose over several receivers.  20,000 atoms, 8 heads, C = 64, one
   // and up to eight: 200 neighbours, L = 3 0.54 of the time, L = 4 0.53; 80, L = 2
   // 0.85, L = 3 0.59, L = 4 0.55; 60, all L, heads of 4 to 32 channels 0.9 (the
   // worst, L = 2, C = 32, 1.07); 40, L = 2 0.97, L = 3 1.06, L = 4 1.04; 12, L = 1
   // 1.11, L = 3 1.09.  At L = 5, where the table takes longer to load, 80 1.02.
-  const int most = L <= 4 && n_edges > (int64_t)n * 56 ? 1 : 8;
+  const int64_t most = L <= 4 && n_edges > (int64_t)n * 56 ? 1 : 8;
   // two tiles a wave where rows average at most two (20,000 atoms, C = 64, L =
   // 4: 28 neighbours 1.07 ms with two tiles, 1.32 with five; 40 neighbours 1.95
   // and 1.50), or, at L = 3 with heads of 8 and 4 channels, one and a half: more
@@ -492,12 +485,12 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
   do {                                                                                                            \
     constexpr AggMap M = agg_map(LL);                                                                             \
     constexpr int nw = NN;                                                                                        \
-    const int rpw = grad_rpw(n, H, most);                                                                         \
+    const int rpw = (int)std::max<int64_t>(1, std::min(most, n_waves / (256 * 16)));                              \
     const int nset = (n + nw * rpw - 1) / (nw * rpw);                                                             \
     const int64_t per = ((int64_t)nset * H + 7) / 8;                                                              \
     if (per * 8 > 0x7fffffff) return hipErrorInvalidValue;                                                        \
     k_edge_grad<LL, PP, WW, nw, TT><<<(unsigned)(8 * per), 64 * nw, LL >= 2 ? M.nk * M.ng * 256 : 0, s>>>(        \
-        Re, Gt, feat, gy, row_ptr, col, alpha, n, rpw, most, nset, lg, (int)per, C, H, lo, hi, range, coef,      \
+        Re, Gt, feat, gy, row_ptr, col, alpha, n, rpw, nset, lg, (int)per, C, H, lo, hi, range, coef,      \
         galpha, out);                                                                                             \
   } while (0)
 #define E2F_GT(LL, PP, WW, NN)                                 \

@@ -249,15 +249,23 @@ def knn_inputs(e2f, ctx, n, k, L, C, H, seed):
     return pos, feat, gout, rp, ci, alpha
 
 
-@pytest.mark.parametrize("L,C,H", [(1, 16, 1), (4, 24, 3), (5, 8, 2), (6, 16, 1)])
-def test_backward_passes_are_bitwise(e2f, ctx, monkeypatch, L, C, H):
+# (the last two: several receivers a wave over the whole graph, fewer receivers in
+# a pass than would fill the chip)
+@pytest.mark.parametrize("L,C,H,n,k", [(1, 16, 1, 1200, 50), (4, 24, 3, 1200, 50), (5, 8, 2, 1200, 50),
+                                       (6, 16, 1, 1200, 50), (1, 32, 8, 6000, 20), (5, 32, 8, 6000, 20)])
+def test_backward_passes_are_bitwise(e2f, ctx, monkeypatch, L, C, H, n, k):
     # every edge's products are its own, so where a pass ends (inside a row of
     # 50 edges: 16,384 is no multiple of 50) does not matter
-    args = knn_inputs(e2f, ctx, 1200, 50, L, C, H, 90 + L)
-    print("passes: L %d C %d H %d" % (L, C, H), flush=True)
+    args = knn_inputs(e2f, ctx, n, k, L, C, H, 90 + L)
+    print("passes: L %d C %d H %d n %d" % (L, C, H, n), flush=True)
     one = e2f.e2f_wigner6j_conv_backward(ctx, *args, L, H, 8.0, want_pos=True)
+    assert all(bool(torch.isfinite(x).all()) for x in one)
     monkeypatch.setenv("E2F_GEOM_GT", "0")
     for kw in (dict(), dict(want_alpha=False), dict(want_feat=False)):
+        torch.cuda.empty_cache()
+        # outputs in memory that holds no earlier result
+        del_me = [torch.full_like(x, float("nan")) for x in one]
+        del del_me
         got = e2f.e2f_wigner6j_conv_backward(ctx, *args, L, H, 8.0, want_pos=True, **kw)
         for a, b in zip(one, got):
             assert b is None or torch.equal(a, b)
