@@ -465,10 +465,10 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
   float* out = gedge && H > 1 ? gpart : gedge;
   const int64_t n_waves = (int64_t)n * H;
   // Receivers a wave takes one after another (they share the table): up to eight,
-  // as long as every CU has work.  One where rows are long (up to L = 4): the heads of a line run
-  // as workgroups side by side and share it only as long as they keep in step,
-  // which they lose over several receivers.  20,000 atoms, 8 heads, C = 64, one
-  // and up to eight: 200 neighbours, L = 3 0.54 of the time, L = 4 0.53; 80, L = 2
+  // as long as every CU has work.  One where rows are long (up to L = 4): the heads
+  // of a line run as workgroups side by side and share it only as long as they
+  // keep in step, which they lose over several receivers.  20,000 atoms, 8 heads,
+  // C = 64, one and up to eight: 200 neighbours, L = 3 0.54 of the time, L = 4 0.53; 80, L = 2
   // 0.85, L = 3 0.59, L = 4 0.55; 60, all L, heads of 4 to 32 channels 0.9 (the
   // worst, L = 2, C = 32, 1.07); 40, L = 2 0.97, L = 3 1.06, L = 4 1.04; 12, L = 1
   // 1.11, L = 3 1.09.  At L = 5, where the table takes longer to load, 80 1.02.
