@@ -64,15 +64,22 @@ __device__ __forceinline__ float sum16(float v) {
   return v;
 }
 
-// Row tiles of 16 edges a wave holds at a time where rows are long: X takes 4
-// registers per tile and key, the features of two steps eight per tile.  A tile
-// past the chunk's end is loaded all the same (one line), so more is not better.
-// Attention gradient, 20,000 atoms, 8 heads, C = 64, with 2, 3, 4, 5 and 6 tiles:
-// 72 neighbours, L = 2 885, 858, 971, 831, 929 us; L = 3 1.33, 1.25, 1.37, 1.27,
-// 1.29 ms; L = 4 3.12, 2.49, 2.81, 2.13, 2.19; 200 neighbours, L = 2 2.43, 2.35,
-// 2.37, 2.44, 2.55; L = 3 5.19, 4.52, 4.24, 3.76, 3.72; L = 4 7.36, 6.67, 6.39, 6.17,
-// 6.21; 100 neighbours, L = 5 10.8, 10.2, 9.3 (2, 3, 4).
-constexpr int grad_tiles(int L, int W) { return L <= 2 || L == 4 ? 5 : L == 3 ? 6 : L == 5 || W == 1 ? 4 : 3; }
+// Row tiles of 16 edges a wave holds at a time where rows average more than 32
+// edges, more than 24 (medium) or fewer: X takes 4 registers per tile and key, the
+// features of two steps eight per tile.  A tile past the chunk's end is loaded all
+// the same (one line), so more is not better; fewer take a long row in more
+// chunks, each of which couples the receiver's gradient again.
+// Attention gradient, 20,000 atoms, 8 heads, C = 64, rows of half to one and a
+// half times the average (where no number of tiles fits every row), with 2, 3, 4,
+// 5 and 6 tiles: 28 edges on average L = 2 460, 399, 443, 488, 570 us; L = 3 901,
+// 639, 603, 682, 707; L = 4 1.66, 1.20, 1.36, 1.38, 1.43 ms; 60, L = 2 742, 728,
+// 806, 814, 833 us; L = 3 1.26, 1.12, 1.18, 1.28, 1.13 ms; L = 4 2.66, 2.27, 2.48,
+// 2.28, 1.98; 120, L = 3 4.09, 3.82, 3.26, 2.45, 2.58; L = 4 5.87, 6.52, 4.56, 4.96,
+// 5.26; one head of 16, 36, L = 5 980, 826, 736 us (2, 3, 4).  20 on average: two
+// tiles take 0.90 of the time of three at L = 2, 0.92 at L = 3, 0.98 at L = 4.
+constexpr int grad_tiles(int L, int W, bool medium) {
+  return L <= 2 ? 3 : L <= 4 ? (medium ? 3 : 6) : L == 5 || W == 1 ? 4 : 3;
+}
 // Waves a workgroup, which share the coupling table in LDS: 45 KB at L = 4, 108
 // and 159 KB at L = 5, 6, where one workgroup has the CU to itself; it has four
 // waves there too where eight would leave half of the CUs without one.  (Read
@@ -125,7 +132,7 @@ constexpr bool grad_split(int L, int P) { return L == 4 || (L > 4 && P == 1); }
 // the edges of a pass then fall to a few XCDs only, 512,000 edges in four
 // passes 4.1 ms against 1.3 in one.)
 template <int L, int P, int W, int NWV, int T>
-__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(T > 2 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
+__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(T > 3 ? 2 : L <= 3 ? 4 : L == 4 ? 3 : 2)))
 void k_edge_grad(const float* __restrict__ Re, const float* __restrict__ Gt, const float* __restrict__ feat,
                  const float* __restrict__ gy, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                  const float* __restrict__ alpha, int n, int rpw, int nset, int lg, int per_xcd, int C, int H,
@@ -473,14 +480,11 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
   // worst, L = 2, C = 32, 1.07); 40, L = 2 0.97, L = 3 1.06, L = 4 1.04; 12, L = 1
   // 1.11, L = 3 1.09.  At L = 5, where the table takes longer to load, 80 1.02.
   const int64_t most = L <= 4 && n_edges > (int64_t)n * 56 ? 1 : 8;
-  // two tiles a wave where rows average at most two (20,000 atoms, C = 64, L =
-  // 4: 28 neighbours 1.07 ms with two tiles, 1.32 with five; 40 neighbours 1.95
-  // and 1.50), or, at L = 3 with heads of 8 and 4 channels, one and a half: more
-  // waves then evict the lines that the heads share (32 neighbours 796 us with two
-  // tiles, 727 with six); and at L <= 1 wherever the waves fill the chip (L = 1,
-  // 80 neighbours, several receivers a wave 441 us with two, 482 with six; alike
-  // with one)
-  const bool few = n_edges <= (int64_t)n * (L == 3 && P > 1 ? 24 : 32) || (L <= 1 && n_waves > 16384);
+  const bool few = n_edges <= (int64_t)n * 24, medium = n_edges <= (int64_t)n * 32;
+  // waves that have a SIMD to themselves wait for their own chunks (up to L = 2,
+  // where the others take three tiles: 600 atoms, one head of 12, L = 2, 60
+  // neighbours, three tiles 1.14 of the time of six)
+  const bool alone = n_waves <= 1024;
 #define E2F_G(LL, PP, WW, NN, TT)                                                                                 \
   do {                                                                                                            \
     constexpr AggMap M = agg_map(LL);                                                                             \
@@ -493,10 +497,13 @@ hipError_t launch_edge_grad(int L, const float* Re, const float* Gt, const float
         Re, Gt, feat, gy, row_ptr, col, alpha, n, rpw, nset, lg, (int)per, C, H, lo, hi, range, coef,      \
         galpha, out);                                                                                             \
   } while (0)
-#define E2F_GT(LL, PP, WW, NN)                                 \
-  do {                                                         \
-    if (few) E2F_G(LL, PP, WW, NN, 2);                         \
-    else E2F_G(LL, PP, WW, NN, grad_tiles(LL, WW));            \
+#define E2F_GT(LL, PP, WW, NN)                                                             \
+  do {                                                                                     \
+    constexpr int tm = grad_tiles(LL, WW, true), tl = grad_tiles(LL, WW, false);           \
+    if (few) E2F_G(LL, PP, WW, NN, 2);                                                     \
+    else if (LL <= 2 && alone) E2F_G(LL, PP, WW, NN, (LL <= 2 ? 6 : tm));                  \
+    else if (medium) E2F_G(LL, PP, WW, NN, tm);                                            \
+    else E2F_G(LL, PP, WW, NN, tl);                                                        \
   } while (0)
 #define E2F_GN(LL, PP, WW)                                     \
   do {                                                         \
