@@ -619,12 +619,15 @@ constexpr double kYnormTileScale = 2.31;
 // atoms, C = 256 (131 MB), 32 neighbours 0.90 of the time, 200 0.81; C = 1024, 200
 // neighbours 22.8 and 11.5 ms; L = 4, 8,000 atoms, C = 128 (102 MB), 200 0.62;
 // 4,000 atoms (51 MB), 80 0.93, 32 1.01; 2,000 atoms (26 MB), 80 1.00; L = 3, 1,000
-// atoms, C = 1024 (66 MB), 32 1.02.  Up to L = 2 a column group reads whole lines
-// and bears more: 8,000 atoms, L = 2, C = 1024 (295 MB), 12 neighbours 1.04, 32
-// 0.98, 80 0.91; C = 256 (74 MB), 200 1.01.
+// atoms, C = 1024 (66 MB), 32 1.02.  Up to L = 2 and at L = 5 a column group reads
+// whole lines and bears more: 8,000 atoms, L = 2, C = 1024 (295 MB), 12 neighbours
+// 1.04, 32 0.98, 80 0.91; C = 256 (74 MB), 200 1.01; L = 5, 8,000 atoms, C = 256
+// (295 MB), 32 0.93, 80 0.90; 4,000 atoms (147 MB), 80 1.02; 6,700 atoms, C = 96 (92
+// MB), 195 1.03.
 bool small_sorted(const e2f_conv_params* p, int n, int64_t n_edges) {
   const double atom = 4.0 * nk_of(p->lmax) * p->channels;  // bytes of features
-  return p->lmax <= 2 ? n * atom >= 256e6 && n_edges * atom >= 8e9 : n * atom >= 48e6 && n_edges * atom >= 3e9;
+  if (p->lmax <= 2 || p->lmax == 5) return n * atom >= 192e6 && n_edges * atom >= 8e9;
+  return n * atom >= 48e6 && n_edges * atom >= 3e9;
 }
 
 e2f_status forward_impl(e2f_ctx* ctx, const e2f_conv_params* p, const float* pos, const int32_t* graph_id,
