@@ -243,3 +243,45 @@ def test_small_features(L):
         assert err <= 1e-6
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("L,C,H,n,y_norm", [(2, 16, 4, 300, False), (4, 64, 4, 1200, True), (3, 1024, 8, 4003, False)])
+def test_forward_under_capture(L, C, H, n, y_norm):
+    # a captured forward of a graph that one workgroup plans (receivers in their own
+    # order, and sorted: the last case), replayed on new features and positions with
+    # eager work in between
+    import paper_2501_19216_amd as e2f
+    ctx = e2f.e2f_create(L, 0)
+    try:
+        rng = np.random.default_rng(n)
+        pos = gpu(syn.quantize(rng.uniform(0, (n / 0.1) ** (1.0 / 3.0), size=(n, 3))))
+        rp, ci = e2f.e2f_knn_graph(ctx, pos, 16)
+        g = torch.Generator(device=DEV).manual_seed(n)
+        feat = torch.randn(n, (L + 1) ** 2, C, device=DEV, generator=g)
+        alpha = torch.rand(ci.numel(), H, device=DEV, generator=g)
+        mix = torch.randn(L + 1, C, C, device=DEV, generator=g) / C ** 0.5
+        kw = dict(mix_w=mix, y_norm=y_norm)
+        e2f.e2f_wigner6j_prepare(ctx, L, C, H, 8.0, **kw)
+        size = e2f.e2f_wigner6j_workspace_size(ctx, n, ci.numel(), L, C, H, 8.0, minimum=True, **kw)
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        out = torch.empty_like(feat)
+
+        def forward(o):
+            return e2f.e2f_wigner6j_conv_forward(ctx, pos, feat, rp, ci, alpha, L, H, 8.0, out=o, workspace=ws, **kw)
+
+        forward(out)
+        torch.cuda.synchronize()
+        print("capture: L %d C %d n %d" % (L, C, n), flush=True)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            forward(out)
+        for k in range(4):
+            feat.normal_(generator=g)
+            pos += 0.25
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            got = out.clone()
+            assert torch.equal(got, forward(torch.empty_like(feat))), "replay %d" % k
+    finally:
+        ctx.close()
